@@ -244,23 +244,15 @@ struct RiemannTape {
 // rho (S-u)(S-S_M) - bn^2 vanishes (relative DegenerateTol) the tangential
 // fields of that side's star state are left unchanged. Region ties go left.
 //
-// EM 1 also gives the coefficients of the UCT-HLLD edge average. At the wave
-// structure of the face the flux of each transverse field component is
-// linear in the outer transverse fields and velocities,
-//   F[B_t] = chiL B_t^L + chiR B_t^R - bn (om v_t^L + (1 - om) v_t^R);
-// the EMF takes om, 1 - om as the weights of v_n B_t on either side,
-// d^L = chiL - om u_L and d^R = (1 - om) u_R - chiR as its diffusion
-// coefficients, and v1, v2 become the om-weighted velocities. Per region
-// (B*_t = zeta B_t and v*_t = v_t - eta B_t on each side; w = 1/(sql + sqr)):
-//   F_L, F*_L:  om = 1, chiL = u_L + S_L (zeta_L - 1), chiR = 0;
-//   F**_L:      om = 1 + S*_L w sql sqr / |bn|,
-//               chiL = u_L + S_L (zeta_L - 1) + S*_L (w (sqr zeta_L + s sql sqr eta_L) - zeta_L),
-//               chiR = S*_L w (sql zeta_R - s sql sqr eta_R), s = sign(bn);
-//   F**_R, F*_R, F_R: the mirror images. For HLL: om = alpha+/(alpha+ + alpha-),
-//   d^L = d^R = alpha+ alpha-/(alpha+ + alpha-).
+// riemann_core evaluates both sides in full: the HLL flux, and the HLLD flux
+// with the tape of the adjoint's reverse sweep (which reads both sides); the
+// forward kernels' HLLD flux is hlld_flux below, with the same expressions.
+// EM 1 (HLL): the UCT-HLLD coefficients om = alpha+/(alpha+ + alpha-),
+// d^L = d^R = alpha+ alpha-/(alpha+ + alpha-).
 template <int RS, class R, class T, int EM = 0>
 __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn,
                                              RiemannOut<R>& o, T& tp) {
+  static_assert(RS == 1 || T::on, "the forward HLLD flux is hlld_flux");
   R ul[7], fl[7], ur[7], fr[7], ptl, ptr;
   const R igm1 = rcp_r(g - R(1));  // 1/(gamma-1)
   phys(igm1, wl, bn, ul, fl, ptl);
@@ -310,14 +302,12 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
     if constexpr (T::on) tp.region = 0;
 #pragma unroll
     for (int q = 0; q < 7; ++q) o.f[q] = fl[q];
-    if (EM == 1) { o.om = R(1); o.dl = R(0); o.dr = R(0); o.v1 = wl[2]; o.v2 = wl[3]; }
     return;
   }
   if (sr < R(0)) {
     if constexpr (T::on) tp.region = 1;
 #pragma unroll
     for (int q = 0; q < 7; ++q) o.f[q] = fr[q];
-    if (EM == 1) { o.om = R(0); o.dl = R(0); o.dr = R(0); o.v1 = wr[2]; o.v2 = wr[3]; }
     return;
   }
   const R dl = sl - wl[1], dr = sr - wr[1];
@@ -332,7 +322,6 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
 
   // star states, one side at a time: s = 0 left, 1 right
   R rs[2], vs[2], ws[2], b1s[2], b2s[2], es[2];
-  R zeta[2], eta[2];  // EM 1: B*_t = zeta B_t, v*_t = v_t - eta B_t
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const R* w = s ? wr : wl;
@@ -348,8 +337,6 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
     const bool deg = abs_r(den) <= R(DegenerateTol<R>::value) * (abs_r(big) + bn2);
     if (deg) {
       vs[s] = w[2]; ws[s] = w[3]; b1s[s] = w[4]; b2s[s] = w[5];
-      zeta[s] = R(1);
-      eta[s] = R(0);
     } else {
       const R iden2 = rcp_r(den);
       const R fv = bn * (sm - w[1]) * iden2;
@@ -358,8 +345,6 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
       const R fb = fma_r(m, d, -bn2) * iden2;
       b1s[s] = w[4] * fb;
       b2s[s] = w[5] * fb;
-      zeta[s] = fb;
-      eta[s] = fv;
       if constexpr (T::on) { tp.iden2[s] = iden2; tp.fv[s] = fv; tp.fb[s] = fb; }
     }
     const R vb = fma_r(w[3], w[5], fma_r(w[2], w[4], w[1] * bn));
@@ -379,13 +364,6 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
 
   if (sls >= R(0)) {  // F*_L
     if constexpr (T::on) tp.region = 3;
-    if (EM == 1) {
-      o.om = R(1);
-      o.dl = sl * (zeta[0] - R(1));
-      o.dr = R(0);
-      o.v1 = wl[2];
-      o.v2 = wl[3];
-    }
     const R us[7] = {rs[0], rs[0] * sm, rs[0] * vs[0], rs[0] * ws[0], b1s[0], b2s[0], es[0]};
 #pragma unroll
     for (int q = 0; q < 7; ++q) o.f[q] = fma_r(sl, us[q] - ul[q], fl[q]);
@@ -402,27 +380,6 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
   if constexpr (T::on) {
     tp.sgn = sgn; tp.isq = isq; tp.ssq = ssq; tp.vss = vss; tp.wss = wss; tp.b1ss = b1ss;
     tp.b2ss = b2ss; tp.vbss = vbss;
-  }
-  if (EM == 1) {
-    // F**_L or F**_R (|bn| > 0 there: S*_L < 0 <= S_M or S_M < 0 <= S*_R)
-    const R ww = isq * sql * sqr;
-    const R cl = fma_r(sgn * sql * sqr, eta[0], sqr * zeta[0]) * isq;  // B** per B_t^L
-    const R cr = fma_r(-sgn * sql * sqr, eta[1], sql * zeta[1]) * isq;  // B** per B_t^R
-    R chiL, chiR;
-    if (sm >= R(0)) {
-      o.om = R(1) - div_r(-sls * ww, abn);
-      chiL = fma_r(sls, cl - zeta[0], fma_r(sl, zeta[0] - R(1), wl[1]));
-      chiR = sls * cr;
-    } else {
-      o.om = div_r(srs * ww, abn);
-      chiR = fma_r(srs, cr - zeta[1], fma_r(sr, zeta[1] - R(1), wr[1]));
-      chiL = srs * cl;
-    }
-    const R omr = R(1) - o.om;
-    o.dl = fma_r(-o.om, wl[1], chiL);
-    o.dr = fma_r(omr, wr[1], -chiR);
-    o.v1 = fma_r(o.om, wl[2], omr * wr[2]);
-    o.v2 = fma_r(o.om, wl[3], omr * wr[3]);
   }
   if (sm >= R(0)) {  // F**_L
     const R ess = fma_r(-sgn * sql, fma_r(vs[0], b1s[0], ws[0] * b2s[0]) - vbss, es[0]);
@@ -449,21 +406,164 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
     return;
   }
   if constexpr (T::on) tp.region = 6;
-  if (EM == 1) {
-    o.om = R(0);
-    o.dl = R(0);
-    o.dr = -sr * (zeta[1] - R(1));
-    o.v1 = wr[2];
-    o.v2 = wr[3];
-  }
 #pragma unroll
   for (int q = 0; q < 7; ++q) o.f[q] = fma_r(sr, us[q] - ur[q], fr[q]);  // F*_R
 }
 
+// HLLD flux of the forward kernels, bitwise that of riemann_core. The flux
+// needs the physical flux, the energy star state and (unless the face lies
+// between the Alfven fronts) the star state of one side only, the side of the
+// contact S_M the face lies on: that side is selected first and only its
+// quantities are formed; the other side's tangential star state and the
+// double-star state follow where a lane of the wave lies between the fronts.
+// (What bounds the face kernels is their FP64 instruction count.)
+//
+// EM 1 also gives the coefficients of the UCT-HLLD edge average. At the wave
+// structure of the face the flux of each transverse field component is
+// linear in the outer transverse fields and velocities,
+//   F[B_t] = chiL B_t^L + chiR B_t^R - bn (om v_t^L + (1 - om) v_t^R);
+// the EMF takes om, 1 - om as the weights of v_n B_t on either side,
+// d^L = chiL - om u_L and d^R = (1 - om) u_R - chiR as its diffusion
+// coefficients, and v1, v2 become the om-weighted velocities. Per region
+// (B*_t = zeta B_t and v*_t = v_t - eta B_t on each side; w = 1/(sql + sqr)):
+//   F_L, F*_L:  om = 1, chiL = u_L + S_L (zeta_L - 1), chiR = 0;
+//   F**_L:      om = 1 + S*_L w sql sqr / |bn|,
+//               chiL = u_L + S_L (zeta_L - 1) + S*_L (w (sqr zeta_L + s sql sqr eta_L) - zeta_L),
+//               chiR = S*_L w (sql zeta_R - s sql sqr eta_R), s = sign(bn);
+//   F**_R, F*_R, F_R: the mirror images.
+template <class R, int EM>
+__device__ __forceinline__ void hlld_flux(R g, const R* wl, const R* wr, R bn, RiemannOut<R>& o) {
+  const R igm1 = rcp_r(g - R(1));  // 1/(gamma-1)
+  const R bn2 = bn * bn;
+  const R ptl = fma_r(R(0.5), fma_r(wl[5], wl[5], fma_r(wl[4], wl[4], bn2)), wl[6]);
+  const R ptr = fma_r(R(0.5), fma_r(wr[5], wr[5], fma_r(wr[4], wr[4], bn2)), wr[6]);
+  const R cm = max_r(cfast(g, wl[0], wl[6], bn, wl[4], wl[5]),
+                     cfast(g, wr[0], wr[6], bn, wr[4], wr[5]));
+  const R sl = min_r(wl[1], wr[1]) - cm;
+  const R sr = max_r(wl[1], wr[1]) + cm;
+  if (EM == 0) {
+    o.ap = max_r(R(0), sr);
+    o.am = max_r(R(0), -sl);
+    const R isum = rcp_r(o.ap + o.am);
+    o.v1 = fma_r(o.ap, wl[2], o.am * wr[2]) * isum;
+    o.v2 = fma_r(o.ap, wl[3], o.am * wr[3]) * isum;
+  }
+  R sm, pts;
+  {
+    const R ml = (sl - wl[1]) * wl[0], mr = (sr - wr[1]) * wr[0];
+    const R iden = rcp_r(mr - ml);
+    sm = fma_r(mr, wr[1], fma_r(-ml, wl[1], ptl - ptr)) * iden;
+    pts = fma_r(ml * mr, wr[1] - wl[1], fma_r(mr, ptl, -ml * ptr)) * iden;
+  }
+  // the side the face lies on: outside the fan the upwind one
+  const bool outl = sl > R(0), outr = !outl && sr < R(0);
+  const bool fan = !outl && !outr;
+  const bool rt = outr || (fan && !(sm >= R(0)));
+  R w[7], u[7], f[7], pt;
+#pragma unroll
+  for (int q = 0; q < 7; ++q) w[q] = rt ? wr[q] : wl[q];
+  phys(igm1, w, bn, u, f, pt);
+  if (EM == 1) {
+    o.om = rt ? R(0) : R(1);
+    o.dl = R(0);
+    o.dr = R(0);
+    o.v1 = w[2];
+    o.v2 = w[3];
+  }
+#pragma unroll
+  for (int q = 0; q < 7; ++q) o.f[q] = f[q];
+  if (!fan) return;
+  // star state of that side (degenerate: v*_t = v_t, B*_t = B_t)
+  const R S = rt ? sr : sl;
+  const R d = S - w[1], m = d * w[0];
+  const R ism = rcp_r(S - sm);
+  const R rs = m * ism;
+  const R sq = sqrt_r(rs);
+  const R abn = abs_r(bn);
+  const R qa = div_r(abn, sq);
+  const R sa = sm + (rt ? qa : -qa);  // its Alfven front
+  R zeta, eta;
+  auto star = [&](R mm, R SS, R un, R dd, R& ze, R& et) {
+    const R big = mm * (SS - sm);
+    const R den = big - bn2;
+    const bool deg = abs_r(den) <= R(DegenerateTol<R>::value) * (abs_r(big) + bn2);
+    const R iden2 = rcp_r(den);  // dropped (maybe not finite) when degenerate
+    const R fv = bn * (sm - un) * iden2;
+    const R fb = fma_r(mm, dd, -bn2) * iden2;
+    et = deg ? R(0) : fv;
+    ze = deg ? R(1) : fb;
+  };
+  star(m, S, w[1], d, zeta, eta);
+  const R vs = fma_r(-w[4], eta, w[2]), ws = fma_r(-w[5], eta, w[3]);
+  const R b1s = w[4] * zeta, b2s = w[5] * zeta;
+  const R vb = fma_r(w[3], w[5], fma_r(w[2], w[4], w[1] * bn));
+  const R vbs = fma_r(ws, b2s, fma_r(vs, b1s, sm * bn));
+  const R es = fma_r(bn, vb - vbs, fma_r(pts, sm, fma_r(d, u[6], -pt * w[1]))) * ism;
+  const R us[7] = {rs, rs * sm, rs * vs, rs * ws, b1s, b2s, es};
+#pragma unroll
+  for (int q = 0; q < 7; ++q) o.f[q] = fma_r(S, us[q] - u[q], f[q]);
+  if (EM == 1) {
+    const R t = S * (zeta - R(1));
+    o.dl = rt ? R(0) : t;
+    o.dr = rt ? -t : R(0);
+  }
+  if ((sa >= R(0)) != rt) return;  // outside the Alfven fronts
+  // F**: the other side's star state, then the double-star state
+  const R so = rt ? sl : sr, uo = rt ? wl[1] : wr[1], rho_o = rt ? wl[0] : wr[0];
+  const R vo = rt ? wl[2] : wr[2], wo = rt ? wl[3] : wr[3];
+  const R b1o = rt ? wl[4] : wr[4], b2o = rt ? wl[5] : wr[5];
+  const R d_o = so - uo, m_o = d_o * rho_o;
+  const R sqo = sqrt_r(m_o * rcp_r(so - sm));
+  R zo, eo;
+  star(m_o, so, uo, d_o, zo, eo);
+  const R vso = fma_r(-b1o, eo, vo), wso = fma_r(-b2o, eo, wo);
+  const R b1so = b1o * zo, b2so = b2o * zo;
+  // left and right in their places
+  const R sql = rt ? sqo : sq, sqr = rt ? sq : sqo;
+  const R vl = rt ? vso : vs, vr = rt ? vs : vso, wsl = rt ? wso : ws, wsr = rt ? ws : wso;
+  const R b1l = rt ? b1so : b1s, b1r = rt ? b1s : b1so;
+  const R b2l = rt ? b2so : b2s, b2r = rt ? b2s : b2so;
+  const R sgn = (bn > R(0)) ? R(1) : ((bn < R(0)) ? R(-1) : R(0));
+  const R isq = rcp_r(sql + sqr);
+  const R ssq = sgn * sql * sqr;
+  const R vss = fma_r(sgn, b1r - b1l, fma_r(sql, vl, sqr * vr)) * isq;
+  const R wss = fma_r(sgn, b2r - b2l, fma_r(sql, wsl, sqr * wsr)) * isq;
+  const R b1ss = fma_r(ssq, vr - vl, fma_r(sql, b1r, sqr * b1l)) * isq;
+  const R b2ss = fma_r(ssq, wsr - wsl, fma_r(sql, b2r, sqr * b2l)) * isq;
+  const R vbss = fma_r(vss, b1ss, wss * b2ss);
+  const R sa_sgn = (rt ? sgn : -sgn) * sq;
+  const R ess = fma_r(sa_sgn, fma_r(vs, b1s, ws * b2s) - vbss, es);
+  const R uss[7] = {rs, rs * sm, rs * vss, rs * wss, b1ss, b2ss, ess};
+#pragma unroll
+  for (int q = 0; q < 7; ++q) o.f[q] = fma_r(sa, uss[q] - us[q], o.f[q]);
+  if (EM == 1) {
+    // (|bn| > 0 there: S*_L < 0 <= S_M or S_M < 0 <= S*_R)
+    const R zl = rt ? zo : zeta, zr = rt ? zeta : zo, el = rt ? eo : eta, er = rt ? eta : eo;
+    const R ww = isq * sql * sqr;
+    const R cl = fma_r(sgn * sql * sqr, el, sqr * zl) * isq;   // B** per B_t^L
+    const R cr = fma_r(-sgn * sql * sqr, er, sql * zr) * isq;  // B** per B_t^R
+    const R ca = rt ? cr : cl, co = rt ? cl : cr;
+    const R t = sa * ww;
+    const R q = div_r(rt ? t : -t, abn);
+    const R chia = fma_r(sa, ca - zeta, fma_r(S, zeta - R(1), w[1])), chio = sa * co;
+    o.om = rt ? q : R(1) - q;
+    const R chiL = rt ? chio : chia, chiR = rt ? chia : chio;
+    const R omr = R(1) - o.om;
+    o.dl = fma_r(-o.om, wl[1], chiL);
+    o.dr = fma_r(omr, wr[1], -chiR);
+    o.v1 = fma_r(o.om, wl[2], omr * wr[2]);
+    o.v2 = fma_r(o.om, wl[3], omr * wr[3]);
+  }
+}
+
 template <int RS, class R, int EM = 0>
 __device__ __forceinline__ void riemann(R g, const R* wl, const R* wr, R bn, RiemannOut<R>& o) {
-  NoTape tp;
-  riemann_core<RS, R, NoTape, EM>(g, wl, wr, bn, o, tp);
+  if constexpr (RS == 0) {
+    hlld_flux<R, EM>(g, wl, wr, bn, o);
+  } else {
+    NoTape tp;
+    riemann_core<RS, R, NoTape, EM>(g, wl, wr, bn, o, tp);
+  }
 }
 
 // Upwind edge EMF for component c with cyclic pair (a, b); the exact value

@@ -784,15 +784,16 @@ __device__ __forceinline__ void stage_rhs(const double* __restrict__ FW,
   const int64_t yp = lin(g, i, wrap(j + 1, g.ny), k);
   const int64_t zp = (DIM == 3) ? lin(g, i, j, wrap(k + 1, g.nz)) : c;
   const double idx = 1.0 / g.dx, idy = 1.0 / g.dy, idz = 1.0 / g.dz;
-  const double* fx = FW;
-  const double* fy = FW + (int64_t)NSLOT * n;
-  const double* fz = FW + (int64_t)2 * NSLOT * n;
-  constexpr int ncell = (DIM == 3) ? 5 : 6;
+  if constexpr (DIM == 3) {  // the cell fields' L as the face kernel left it
 #pragma unroll
-  for (int q = 0; q < ncell; ++q) {
-    double acc = (fx[q * n + xp] - fx[q * n + c]) * idx + (fy[q * n + yp] - fy[q * n + c]) * idy;
-    if (DIM == 3) acc += (fz[q * n + zp] - fz[q * n + c]) * idz;
-    L[q == 5 ? 7 : q] = -acc;
+    for (int q = 0; q < 5; ++q) L[q] = FW[q * n + c];
+  } else {
+    const double* fx = FW;
+    const double* fy = FW + (int64_t)NSLOT * n;
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+      L[q == 5 ? 7 : q] = -((fx[q * n + xp] - fx[q * n + c]) * idx +
+                            (fy[q * n + yp] - fy[q * n + c]) * idy);
   }
   if (DIM == 3) {
     const double* ex = EW;
@@ -1005,6 +1006,7 @@ hipError_t adjoint_impl(const AdjointArgs& a) {
   f.EW = a.EW;
   f.dt = a.dt;
   f.dtp = nullptr;
+  f.keep_rhs = a.dim == 3 && a.want_dtbar;  // L(U) for dt-bar
   f.flag = a.flag;
   f.stream = a.stream;
   f.timer = nullptr;

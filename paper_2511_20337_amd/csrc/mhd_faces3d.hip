@@ -1,0 +1,617 @@
+// 3D PLM stage kernels: the z-marching face kernel, which also differences the
+// fluxes of the cell-averaged fields, and the update of the staggered field.
+//
+// A workgroup owns a 32 x 8 column of cells and walks a run of planes
+// k0 <= k < k1, one cell of each plane per thread. Per plane each thread
+// solves the lower z-, x- and y-face of its cell; the faces above the column
+// (32 y-faces, 8 x-faces) are solved once more by one wave, in turn, so that
+// every flux the column's cells need is at hand: only the inputs of the edge
+// EMFs (alpha+- or the UCT-HLLD coefficients, two velocities: 12 or 15 values
+// per cell) go to memory, and the five flux divergences end in the new state
+// (or L) directly. A face solved twice gives the same bits both times.
+//
+// What bounds it: the instruction count (2250 per cell at 256^3 in FP64, the
+// vector units 71 % busy). Measured against the split it replaces (a face
+// kernel that stored the fluxes, 27 values per cell, and an update that read
+// them back): faces 1.52 -> 1.60 ms, update 0.96 -> 0.43 ms per launch at 256^3
+// in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms. Choices:
+//  - 32 x 8 columns: the extra faces fit one wave (40 lanes; 64 x 4 needs 68),
+//    the halo is 160 cells a plane (64 x 4: 272), and a ragged nx wastes less.
+//  - LDS holds two planes of the column (by the parity of k - k0; the values a
+//    thread needs of planes k-1 and k+1 are its own), one cross halo and the
+//    exchanged fluxes.
+//  - Two waves per SIMD in FP64 (218 VGPRs), three in mixed precision: one more
+//    spills (FP64 2.17 ms against 1.60, mixed 384^3 4.03 against 3.51).
+//  - Two barriers a plane: before the first one everybody reads plane k; then
+//    the halo of plane k+1 and the exchanged fluxes are written; the second
+//    publishes them.
+//  - Lanes past a ragged grid hold the periodic images of the first cells, so
+//    their faces are those of the cells they repeat: they are solved and their
+//    edge inputs stored like any other (the same bits to the same place),
+//    which keeps every path through a plane alike. Only the new state, which
+//    may be updated in place, is written by its owner alone.
+#include "mhd_device.hpp"
+#include "mhd_grid.hpp"
+#include "mhd_kernels.hpp"
+
+namespace mhd {
+
+namespace {
+
+struct March {
+  static constexpr int TX = 32, TY = 8, NCORE = TX * TY;
+  static constexpr int NHX = 4 * TY;           // x halo: columns -2, -1, TX, TX + 1
+  static constexpr int NHALO = NHX + 4 * TX;   // then the y halo rows
+  static constexpr int NQ = 8;                 // primitives per cell: V slots 0..7
+};
+static_assert(March::NCORE == kBlock, "one column cell per thread");
+static_assert(March::NHALO <= March::NCORE, "at most one halo cell per thread");
+static_assert(March::TX + March::TY <= 64, "the faces above the column fit one wave");
+static_assert(March::TX == 32, "a wave holds two rows");
+
+// One stride for every quantity, core or halo, so that a stencil cell is one
+// offset and its quantities lie at constant distances from it.
+template <class R>
+struct MarchLds {
+  R v[March::NQ][2 * March::NCORE + March::NHALO];  // core of two planes, halo
+  R fy[5][March::NCORE];  // y-fluxes of rows 1 .. TY (row r at (r - 1) * TX)
+  R fx[5][March::TY];     // x-fluxes at column TX
+};
+constexpr int kMarchQ = 2 * March::NCORE + March::NHALO;  // quantity stride
+constexpr int kHaloOff = 2 * March::NCORE;
+
+// Position of halo entry h relative to the column origin.
+__device__ __forceinline__ void march_halo_pos(int h, int& x, int& y) {
+  if (h < March::NHX) {
+    const int s = h / March::TY;
+    y = h % March::TY;
+    x = (s < 2) ? s - 2 : March::TX + s - 2;
+  } else {
+    h -= March::NHX;
+    const int s = h / March::TX;
+    x = h % March::TX;
+    y = (s < 2) ? s - 2 : March::TY + s - 2;
+  }
+}
+
+// Offset of cell (xx, yy) of the plane whose core starts at cp (at most one
+// coordinate outside the column).
+__device__ __forceinline__ int march_xy(int cp, int xx, int yy) {
+  if (xx < 0 || xx >= March::TX)
+    return kHaloOff + ((xx < 0) ? xx + 2 : xx - March::TX + 2) * March::TY + yy;
+  if (yy < 0 || yy >= March::TY)
+    return kHaloOff + March::NHX + ((yy < 0) ? yy + 2 : yy - March::TY + 2) * March::TX + xx;
+  return cp + yy * March::TX + xx;
+}
+
+// A value that every lane holds alike, in scalar registers.
+__device__ __forceinline__ double uni(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float uni(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+// The same value, of which the compiler does not know that it is loop
+// invariant: what is derived from it is formed where it is used instead of
+// being carried through the march in registers that the solves need (and an
+// offset is seen as the zero-extended 32 bits that the scalar-base addressing
+// form takes).
+template <class T>
+__device__ __forceinline__ T here(T v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Byte offsets within a plane of one field (FP64) of the values the primitive
+// recovery of cell (i, j) reads (indices wrapped): the cell, and its upper x
+// and y neighbours (staggered B_x, B_y). The staggered B_z above is the
+// cell's own offset in the next plane. 32 bits: a plane holds fewer than
+// 2^29 cells.
+struct PlaneOffs {
+  uint32_t c, xp, yp;
+};
+__device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j) {
+  const int iw = wrap_any(i, g.nx), jw = wrap_any(j, g.ny);
+  PlaneOffs p;
+  p.c = (uint32_t)(jw * g.nx + iw) * 8u;
+  p.xp = (uint32_t)(jw * g.nx + wrap(iw + 1, g.nx)) * 8u;
+  p.yp = (uint32_t)(wrap(jw + 1, g.ny) * g.nx + iw) * 8u;
+  return p;
+}
+// The value at byte offset off of the uniform base b.
+__device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t off) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
+}
+// Raw values of the cell at offsets p in plane kw; the staggered B_z above
+// from plane kw1 (both wrapped into 0..nz-1).
+__device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, const Geom& g,
+                                                  int64_t nxy, int kw, int kw1,
+                                                  const PlaneOffs& p) {
+  const double* pl = U + kw * nxy;
+  const uint32_t c = here(p.c), xp = here(p.xp), yp = here(p.yp);
+  RawCell r;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) r.u[q] = ld_at(pl + q * g.n, c);
+  r.bxp = ld_at(pl + 5 * g.n, xp);
+  r.byp = ld_at(pl + 6 * g.n, yp);
+  r.bzp = ld_at(U + 7 * g.n + kw1 * nxy, c);
+  return r;
+}
+
+// The edge inputs of a lower D-face of the plane whose records start at fwp
+// (slot 0 of direction 0), the cell at byte offset boff.
+template <int D, int EM, class R>
+__device__ __forceinline__ void put_edge(R* __restrict__ fwp, int64_t n, uint32_t boff,
+                                         const RiemannOut<R>& o) {
+  const uint32_t off = here(boff);
+  auto put = [&](int slot, R v) {
+    *reinterpret_cast<R*>(reinterpret_cast<char*>(fwp + ((int64_t)D * NSLOT + slot) * n) +
+                          off) = v;
+  };
+  if (EM == 1) {
+    put(S_AP, o.om);
+    put(S_AM, o.dl);
+    put(S_DR, o.dr);
+  } else {
+    put(S_AP, o.ap);
+    put(S_AM, o.am);
+  }
+  put(S_V1, o.v1);
+  put(S_V2, o.v2);
+}
+
+// Fluxes of (rho, m_x, m_y, m_z, E) through a D-face.
+template <int D, class R>
+__device__ __forceinline__ void cell_fluxes(const RiemannOut<R>& o, R* F) {
+  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+  F[0] = o.f[0];
+  F[1 + D] = o.f[1];
+  F[1 + T1] = o.f[2];
+  F[1 + T2] = o.f[3];
+  F[4] = o.f[6];
+}
+
+// Left and right value at a face from the four cells about it.
+template <int LIM, class R>
+__device__ __forceinline__ void recon_pair(const R* v, R& l, R& r) {
+  l = fma_r(R(0.5), plm_slope<LIM, R>(v[1] - v[0], v[2] - v[1]), v[1]);
+  r = fma_r(R(-0.5), plm_slope<LIM, R>(v[2] - v[1], v[3] - v[2]), v[2]);
+}
+// Reconstructed states of a face from its four stencil cells (offsets o);
+// slot: the quantities of the face frame.
+template <int LIM, class R>
+__device__ __forceinline__ void march_recon(const R* lds, const int* o, const int* slot, R* wl,
+                                            R* wr) {
+#pragma unroll
+  for (int q = 0; q < 7; ++q) {
+    R v[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + slot[q] * kMarchQ];
+    recon_pair<LIM, R>(v, wl[q], wr[q]);
+  }
+}
+
+// The stages' combinations of k_update with u the state L was formed at and
+// u0 the state at the start of the step.
+__device__ __forceinline__ double rk_combine(int stage, double u, double u0, double h, double L) {
+  if (stage == 0) return L;
+  if (stage == 1) return u + h * L;
+  if (stage == 4) return (3.0 * u0 + (u + h * L)) / 4.0;
+  if (stage == 5) return (u0 + 2.0 * (u + h * L)) / 3.0;
+  return 0.5 * (u0 + (u + h * L));
+}
+
+// The same combinations by coefficients, for a stage known at run time without
+// a branch per value: (ca u0 + cb (cu u + h L)) / cd, the quotient by the
+// divisors 1, 2, 4 exact and by 3 corrected to the rounded one.
+struct RkCoef {
+  double cu, h, ca, cb, cc, cd;
+};
+__device__ __forceinline__ RkCoef rk_coef(int stage, double h) {
+  RkCoef c = {1.0, h, 0.0, 1.0, 1.0, 1.0};
+  if (stage == 0) { c.cu = 0.0; c.h = 1.0; }
+  if (stage == 2) { c.ca = 1.0; c.cc = 0.5; c.cd = 2.0; }
+  if (stage == 4) { c.ca = 3.0; c.cc = 0.25; c.cd = 4.0; }
+  if (stage == 5) { c.ca = 1.0; c.cb = 2.0; c.cc = 1.0 / 3.0; c.cd = 3.0; }
+  return c;
+}
+__device__ __forceinline__ double rk_apply(const RkCoef& c, double u, double u0, double L) {
+  const double v = c.ca * u0 + c.cb * (c.cu * u + c.h * L);
+  const double q = v * c.cc;
+  return fma_r(fma_r(-c.cd, q, v), c.cc, q);
+}
+
+// stage: as rk_combine, for the five cell-averaged fields (U0 not null: U
+// where the stage does not use it); 3: edge inputs only. cflp != nullptr: also
+// the CFL bound of the state over the column and run into cflp[blockIdx.x] (a
+// lane past the grid repeats a cell, which a minimum does not mind).
+template <int LIM, int RS, class R, int EM>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 3)))
+void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
+                   double* __restrict__ FW, Geom g, MarchGrid mg, int stage, double dt,
+                   const double* __restrict__ dtp, int* __restrict__ flag,
+                   double* __restrict__ cflp) {
+  using M = March;
+  // face frames (rho, v_n, v_t1, v_t2, B_t1, B_t2, p)
+  constexpr int xslot[7] = {0, 1, 2, 3, 6, 7, 4}, yslot[7] = {0, 2, 3, 1, 7, 5, 4};
+  constexpr int zslot[7] = {0, 3, 1, 2, 5, 6, 4};
+  __shared__ MarchLds<R> L;
+  R* lds = &L.v[0][0];
+  const unsigned b = blockIdx.x;
+  const int tx = (int)(b % (unsigned)mg.ntx);
+  const unsigned r = b / (unsigned)mg.ntx;
+  const int ty = (int)(r % (unsigned)mg.nty);
+  const int zc = (int)(r / (unsigned)mg.nty);
+  const int i0 = tx * M::TX, j0 = ty * M::TY;
+  const int k0 = zc * mg.lz;
+  const int k1 = min(k0 + mg.lz, g.nz);
+  const int t = (int)threadIdx.x;
+  const int x = t % M::TX, y = t / M::TX;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+  const bool inside = (i0 + x < g.nx) && (j0 + y < g.ny);
+  const int64_t n = g.n, nxy = (int64_t)g.nx * g.ny;
+  const R gam = (R)g.gamma;
+  const PlaneOffs po = plane_offs(g, i0 + x, j0 + y);
+  const uint32_t boff = po.c / 8u * (uint32_t)sizeof(R);
+  // halo cell (threads past the halo load a valid cell and drop it)
+  const bool haloer = t < M::NHALO;
+  int hx, hy;
+  march_halo_pos(haloer ? t : M::NHALO - 1, hx, hy);
+  const PlaneOffs ph = plane_offs(g, i0 + hx, j0 + hy);
+  // face above the column of this lane: y-faces of lanes 0 .. 31, x-faces of
+  // lanes 32 .. 39 (further lanes repeat the last); the offset of its cell
+  uint32_t eoff;
+  {
+    const bool ey = lane < M::TX;
+    const int e = ey ? lane : min(lane - M::TX, M::TY - 1);
+    eoff = plane_offs(g, i0 + (ey ? e : M::TX), j0 + (ey ? M::TY : e)).c;
+  }
+  const RkCoef rk = rk_coef(stage, (stage == 0 || stage == 3) ? 0.0 : uni(dtp ? *dtp : dt));
+  const double idx = uni(1.0 / g.dx), idy = uni(1.0 / g.dy), idz = uni(1.0 / g.dz);
+  bool bad = false;
+  double cmin = __builtin_inf();
+  // Prologue: plane k0 (core and halo), V_{k0-1} of the own cell in the other
+  // core plane, the left state of the first z-face, the raw cell of k0 + 1.
+  R zl[7];
+  double bn[3];  // normal fields of the own cell's lower faces, plane k
+  {
+    const int km2 = wrap_any(k0 - 2, g.nz), km1 = wrap_any(k0 - 1, g.nz);
+    const int kp1 = wrap_any(k0 + 1, g.nz);
+    const RawCell rm2 = load_raw_plane(U, g, nxy, km2, km1, po);
+    const RawCell rm1 = load_raw_plane(U, g, nxy, km1, k0, po);
+    const RawCell rc = load_raw_plane(U, g, nxy, k0, kp1, po);
+    const RawCell rh = load_raw_plane(U, g, nxy, k0, kp1, ph);
+    double Wm2[8], Wm1[8], W[8];
+    bad |= !prim_from_raw<3>(rm2, g.gamma, Wm2);
+    bad |= !prim_from_raw<3>(rm1, g.gamma, Wm1);
+    bad |= !prim_from_raw<3>(rc, g.gamma, W);
+    if (cflp) cmin = cfl_bound(g, W, cmin);
+#pragma unroll
+    for (int q = 0; q < M::NQ; ++q) {
+      lds[q * kMarchQ + M::NCORE + t] = (R)Wm1[q];
+      lds[q * kMarchQ + t] = (R)W[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+      const R a = (R)Wm2[zslot[q]], bb = (R)Wm1[zslot[q]], c = (R)W[zslot[q]];
+      zl[q] = fma_r(R(0.5), plm_slope<LIM, R>(bb - a, c - bb), bb);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) bn[d] = rc.u[5 + d];
+    if (haloer) {
+      bad |= !prim_from_raw<3>(rh, g.gamma, W);
+#pragma unroll
+      for (int q = 0; q < M::NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+    }
+  }
+  RawCell nxt = load_raw_plane(U, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
+  __syncthreads();
+  int cp = 0;  // core offset of plane k
+  double acc[5];  // minus L of the cell below, but for its upper z-flux
+  R* const fw0 = reinterpret_cast<R*>(FW);
+  for (int k = k0;; ++k) {
+    const int kw = wrap_any(k, g.nz);
+    R* const fwp = fw0 + kw * nxy;
+    R wl[7], wr[7];
+    RiemannOut<R> o;
+    // z-face: the own cell of plane k + 1, then the slope of cell k, which
+    // gives the right state and the next plane's left state
+    double bnn[3];
+    {
+      double W[8];
+      bad |= !prim_from_raw<3>(nxt, g.gamma, W);
+      if (cflp && k + 1 < k1) cmin = cfl_bound(g, W, cmin);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) bnn[d] = nxt.u[5 + d];
+      const int cn = M::NCORE - cp + t;  // own cell in the other core plane: k - 1, then k + 1
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        const int sq = zslot[q];
+        const R a = lds[cn + sq * kMarchQ];
+        const R bb = lds[cp + t + sq * kMarchQ];
+        const R c = (R)W[sq];
+        const R dlt = plm_slope<LIM, R>(bb - a, c - bb);
+        wl[q] = zl[q];
+        wr[q] = fma_r(R(-0.5), dlt, bb);
+        zl[q] = fma_r(R(0.5), dlt, bb);
+      }
+#pragma unroll
+      for (int q = 0; q < M::NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
+    }
+    riemann<RS, R, EM>(gam, wl, wr, (R)bn[2], o);
+    {
+      R F[5];
+      cell_fluxes<2>(o, F);
+      // the cell below is finished
+      const int64_t cb = (int64_t)(k - 1) * nxy;
+      if (k > k0 && inside && stage != 3) {
+        const uint32_t c = here(po.c);
+        double u[5], u0[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+          u[q] = ld_at(U + q * n + cb, c);
+          u0[q] = ld_at(U0 + q * n + cb, c);
+        }
+#pragma unroll
+        for (int q = 0; q < 5; ++q)
+          *reinterpret_cast<double*>(reinterpret_cast<char*>(out + q * n + cb) + c) =
+              rk_apply(rk, u[q], u0[q], -(acc[q] + (double)F[q] * idz));
+      }
+      if (k == k1) break;
+#pragma unroll
+      for (int q = 0; q < 5; ++q) acc[q] = -(double)F[q] * idz;
+    }
+    put_edge<2, EM>(fwp, n, boff, o);
+    const int ka = wrap_any(k + 1, g.nz), kb = wrap_any(k + 2, g.nz), kc = wrap_any(k + 3, g.nz);
+    // x-face
+    {
+      const int tt = here(t), xx = tt & (M::TX - 1), yy = tt / M::TX;
+      int os[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx - 2 + s, yy);
+      march_recon<LIM, R>(lds, os, xslot, wl, wr);
+    }
+    riemann<RS, R, EM>(gam, wl, wr, (R)bn[0], o);
+    put_edge<0, EM>(fwp, n, boff, o);
+    {
+      R F[5];
+      cell_fluxes<0>(o, F);
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        const R up = __shfl_down(F[q], 1, 64);  // the upper face, but for the last column
+        acc[q] += (x == M::TX - 1) ? -(double)F[q] * idx : ((double)up - (double)F[q]) * idx;
+      }
+    }
+    // y-face
+    {
+      const int tt = here(t), xx = tt & (M::TX - 1), yy = tt / M::TX;
+      int os[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx, yy - 2 + s);
+      march_recon<LIM, R>(lds, os, yslot, wl, wr);
+    }
+    riemann<RS, R, EM>(gam, wl, wr, (R)bn[1], o);
+    put_edge<1, EM>(fwp, n, boff, o);
+    R fy[5];
+    cell_fluxes<1>(o, fy);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) acc[q] -= (double)fy[q] * idy;
+    // the faces above the column: one wave, in turn
+    const bool helper = wave == ((k - k0) & 3);
+    R fe[5];
+    if (helper) {
+      const int l = here(lane);
+      const bool ey = l < M::TX;
+      const int e = ey ? l : min(l - M::TX, M::TY - 1);
+      const double ebn = ld_at(U + (ey ? F_BY : F_BX) * n + kw * nxy, here(eoff));
+      // slots: the x frame's, plus 1 at (v_n, v_t1, B_t1) and minus 2 at
+      // (v_t2, B_t2) for a y-face
+      const int up = ey ? kMarchQ : 0, dn = ey ? -2 * kMarchQ : 0;
+      int os[3][4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        os[0][s] = march_xy(cp, ey ? e : M::TX - 2 + s, ey ? M::TY - 2 + s : e);
+        os[1][s] = os[0][s] + up;
+        os[2][s] = os[0][s] + dn;
+      }
+      constexpr int kind[7] = {0, 1, 1, 2, 1, 2, 0};
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        R v[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) v[s] = lds[os[kind[q]][s] + xslot[q] * kMarchQ];
+        recon_pair<LIM, R>(v, wl[q], wr[q]);
+      }
+      riemann<RS, R, EM>(gam, wl, wr, (R)ebn, o);
+      fe[0] = o.f[0];
+      fe[1] = ey ? o.f[3] : o.f[1];
+      fe[2] = ey ? o.f[1] : o.f[2];
+      fe[3] = ey ? o.f[2] : o.f[3];
+      fe[4] = o.f[6];
+    }
+    // the raw halo cell of plane k + 1 and own cell of plane k + 2 (their
+    // latency passes at the barriers)
+    const RawCell hr = load_raw_plane(U, g, nxy, ka, kb, ph);
+    nxt = load_raw_plane(U, g, nxy, kb, kc, po);
+    __syncthreads();
+    if (y > 0) {
+#pragma unroll
+      for (int q = 0; q < 5; ++q) L.fy[q][t - M::TX] = fy[q];
+    }
+    if (helper && lane < M::TX + M::TY) {
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        if (lane < M::TX) L.fy[q][M::NCORE - M::TX + lane] = fe[q];
+        else L.fx[q][lane - M::TX] = fe[q];
+      }
+    }
+    if (haloer) {
+      double W[8];
+      bad |= !prim_from_raw<3>(hr, g.gamma, W);
+#pragma unroll
+      for (int q = 0; q < M::NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      acc[q] += (double)L.fy[q][t] * idy;
+      if (x == M::TX - 1) acc[q] += (double)L.fx[q][y] * idx;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) bn[d] = bnn[d];
+    cp = M::NCORE - cp;
+  }
+  if (cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
+  if (bad) atomicOr(flag, 1);
+}
+
+// Update of the staggered field by -curl E (and, HYDRO, of the cell fields by
+// the L the face kernel left in Lc, whose time step was not known yet), V
+// cells along x per thread (V = 2 for an even nx: two-wide loads and stores).
+// What bounds it: HBM.
+template <int STAGE, class R, bool HYDRO, int V>
+__global__ __launch_bounds__(kBlock) void k_update_b(const double* __restrict__ U,
+                                                    const double* U0, const double* Lc,
+                                                    double* out, const double* __restrict__ EW,
+                                                    Geom g, MarchGrid tg, double dt,
+                                                    const double* __restrict__ dtp) {
+  // mixed mode (FP32 EMFs): the XCD-grouped order, as in k_update2
+  const unsigned b = (sizeof(R) == 4) ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int tx = (int)(b % (unsigned)tg.ntx);
+  const unsigned r = b / (unsigned)tg.ntx;
+  const int ty = (int)(r % (unsigned)tg.nty);
+  const int k = (int)(r / (unsigned)tg.nty);
+  const int i = (tx * 64 + (int)threadIdx.x % 64) * V;
+  const int j = ty * 4 + (int)threadIdx.x / 64;
+  if (i >= g.nx || j >= g.ny) return;
+  typedef R RV __attribute__((ext_vector_type(V)));
+  typedef double DV __attribute__((ext_vector_type(V)));
+  const int64_t n = g.n, c = lin(g, i, j, k);
+  const double h = (STAGE == 0) ? 0.0 : (dtp ? *dtp : dt);
+  const int64_t xq = lin(g, wrap(i + V, g.nx), j, k);
+  const int64_t yp = lin(g, i, wrap(j + 1, g.ny), k), zp = lin(g, i, j, wrap(k + 1, g.nz));
+  const double idx = 1.0 / g.dx, idy = 1.0 / g.dy, idz = 1.0 / g.dz;
+  const R* ex = reinterpret_cast<const R*>(EW);
+  const R* ey = ex + n;
+  const R* ez = ex + 2 * n;
+  auto ldr = [](const R* p, int64_t q) { return *reinterpret_cast<const RV*>(p + q); };
+  auto ldd = [](const double* p, int64_t q) { return *reinterpret_cast<const DV*>(p + q); };
+  const RV xc = ldr(ex, c), xy = ldr(ex, yp), xz = ldr(ex, zp);
+  const RV yc = ldr(ey, c), yz = ldr(ey, zp);
+  const RV zc = ldr(ez, c), zy = ldr(ez, yp);
+  const R yq = ey[xq], zq = ez[xq];
+  double Lb[V][3];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    const double ezx = (e + 1 < V) ? (double)zc[(e + 1) % V] : (double)zq;
+    const double eyx = (e + 1 < V) ? (double)yc[(e + 1) % V] : (double)yq;
+    const double x0 = (double)xc[e], y0 = (double)yc[e], z0 = (double)zc[e];
+    Lb[e][0] = -(((double)zy[e] - z0) * idy - ((double)yz[e] - y0) * idz);
+    Lb[e][1] = -(((double)xz[e] - x0) * idz - (ezx - z0) * idx);
+    Lb[e][2] = -((eyx - y0) * idx - ((double)xy[e] - x0) * idy);
+  }
+#pragma unroll
+  for (int q = HYDRO ? 0 : 5; q < 8; ++q) {
+    DV u = {}, u0 = {}, v, lc = {};
+    if (STAGE != 0) u = ldd(U + q * n, c);
+    if (STAGE >= 2) u0 = ldd(U0 + q * n, c);
+    if (q < 5) lc = ldd(Lc + q * n, c);
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+      v[e] = rk_combine(STAGE, u[e], u0[e], h, q < 5 ? lc[e] : Lb[e][q < 5 ? 0 : q - 5]);
+    *reinterpret_cast<DV*>(out + q * n + c) = v;
+  }
+}
+
+template <int LIM, int RS, class R, int EM>
+void faces_impl(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+  hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM>), dim3(mg.nblocks), dim3(kBlock), 0, a.stream,
+                     a.U, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag, a.cfl_partial);
+}
+template <int LIM, int RS, class R>
+void faces_em(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+  if (a.emf == 1) faces_impl<LIM, RS, R, 1>(a, mg, stage, out);
+  else faces_impl<LIM, RS, R, 0>(a, mg, stage, out);
+}
+template <int LIM, int RS>
+void faces_prec(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+  if (a.precision == 1) faces_em<LIM, RS, float>(a, mg, stage, out);
+  else faces_em<LIM, RS, double>(a, mg, stage, out);
+}
+
+template <class R, bool HYDRO, int V>
+void update_impl(const StageArgs& a, const double* Lc) {
+  MarchGrid tg;
+  tg.ntx = (a.g.nx + 64 * V - 1) / (64 * V);
+  tg.nty = (a.g.ny + 3) / 4;
+  tg.nblocks = (unsigned)tg.ntx * (unsigned)tg.nty * (unsigned)a.g.nz;
+#define MHD_UPD(ST)                                                                           \
+  hipLaunchKernelGGL((k_update_b<ST, R, HYDRO, V>), dim3(tg.nblocks), dim3(kBlock), 0, a.stream, \
+                     a.U, a.U0, Lc, a.out, a.EW, a.g, tg, a.dt, a.dtp)
+  switch (a.stage) {
+    case 0: MHD_UPD(0); break;
+    case 1: MHD_UPD(1); break;
+    case 4: MHD_UPD(4); break;
+    case 5: MHD_UPD(5); break;
+    default: MHD_UPD(2); break;
+  }
+#undef MHD_UPD
+}
+template <class R, bool HYDRO>
+void update_v(const StageArgs& a, const double* Lc) {
+  if (a.g.nx % 2 == 0) update_impl<R, HYDRO, 2>(a, Lc);
+  else update_impl<R, HYDRO, 1>(a, Lc);
+}
+
+}  // namespace
+
+// Planes per run: a run costs about two planes more (its prologue and the
+// z-faces above it), a longer one leaves fewer workgroups, of which two fit on
+// each of the 256 CUs. The power of two up to 16 that minimises (runs per slot
+// + 1/2) (planes + 2) is within 2 % of the best measured of 1 .. 64 at 32^3
+// (1: 19.5 us a launch, 16: 137), 150 x 131 x 97 (8: 196, 4: 213), 301 x 200 x
+// 233 mixed (16) and 256^3 (16: 1608, 32: 1601, 8: 1654, 4: 1742 us).
+MarchGrid march_grid(const Geom& g) {
+  MarchGrid mg;
+  mg.lx = 5;
+  mg.ntx = (g.nx + March::TX - 1) / March::TX;
+  mg.nty = (g.ny + March::TY - 1) / March::TY;
+  double best = 0.0;
+  mg.lz = 0;
+  for (int lz = 16; lz >= 1; lz /= 2) {
+    const int64_t nb = (int64_t)mg.ntx * mg.nty * ((g.nz + lz - 1) / lz);
+    const double t = ((double)nb / 512.0 + 0.5) * (lz + 2.0);
+    if (mg.lz == 0 || t < 0.97 * best) {
+      best = t;
+      mg.lz = lz;
+    }
+  }
+  mg.nzc = (g.nz + mg.lz - 1) / mg.lz;
+  mg.nblocks = (unsigned)mg.ntx * (unsigned)mg.nty * (unsigned)mg.nzc;
+  return mg;
+}
+
+void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+  if (a.limiter == 0) {
+    if (a.riemann == 0) faces_prec<0, 0>(a, mg, stage, out);
+    else faces_prec<0, 1>(a, mg, stage, out);
+  } else {
+    if (a.riemann == 0) faces_prec<1, 0>(a, mg, stage, out);
+    else faces_prec<1, 1>(a, mg, stage, out);
+  }
+}
+
+void launch_update_b(const StageArgs& a, const double* Lc) {
+  if (a.precision == 1) {
+    if (Lc) update_v<float, true>(a, Lc);
+    else update_v<float, false>(a, Lc);
+  } else {
+    if (Lc) update_v<double, true>(a, Lc);
+    else update_v<double, false>(a, Lc);
+  }
+}
+
+}  // namespace mhd

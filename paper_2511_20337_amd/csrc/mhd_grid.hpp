@@ -135,4 +135,56 @@ __device__ __forceinline__ double plm_adjoint(const double* x, const double* xp,
   return xp[1] + xm[1] + sb[1] * (s1[1] - s2[1]) - sb[2] * s1[2] + sb[0] * s2[0];
 }
 
+__device__ __forceinline__ int wrap_any(int i, int n) {
+  int r = i % n;
+  return r < 0 ? r + n : r;
+}
+
+// Face records (fluxes, alpha+-, HLL-weighted velocities) and edge EMFs are
+// stored in the precision they were computed in: FP64, or FP32 in the mixed
+// mode (exact, and half the bytes for the kernels that read them). The
+// workspace holds dim * NSLOT * n and 3 * n doubles either way.
+template <class R>
+__device__ __forceinline__ R* stored(double* buf) {
+  return reinterpret_cast<R*>(buf);
+}
+template <class R>
+__device__ __forceinline__ const R* stored(const double* buf) {
+  return reinterpret_cast<const R*>(buf);
+}
+
+// CFL bound of one cell from its FP64 primitives: min over directions of
+// dx_d / (|v_d| + c_f,d), the expression of k_cfl.
+__device__ __forceinline__ double cfl_bound(const Geom& g, const double* W, double m) {
+  const double dd[3] = {g.dx, g.dy, g.dz};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double cf = cfast<double>(g.gamma, W[0], W[4], W[5 + d], W[5 + (d + 1) % 3],
+                                    W[5 + (d + 2) % 3]);
+    const double t = dd[d] / (__builtin_fabs(W[1 + d]) + cf);
+    m = (t < m) ? t : m;
+  }
+  return m;
+}
+
+// Minimum of v over the kBlock threads of the workgroup, stored by thread 0
+// to *out. Every thread of the workgroup must call it.
+__device__ __forceinline__ void workgroup_min_store(double v, double* __restrict__ out) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(v, off, 64);
+    v = (o < v) ? o : v;
+  }
+  __shared__ double red[kBlock / 64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (lane == 0) red[wid] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double r = red[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / 64; ++w) r = (red[w] < r) ? red[w] : r;
+    *out = r;
+  }
+}
+
 }  // namespace mhd

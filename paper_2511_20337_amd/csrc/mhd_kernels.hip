@@ -45,24 +45,6 @@ struct RowTile {
   static constexpr int NT = TX * TY;  // workgroup size
 };
 
-// Face records (fluxes, alpha+-, HLL-weighted velocities) and edge EMFs are
-// stored in the precision they were computed in: FP64, or FP32 in the mixed
-// mode (exact, and half the bytes for the kernels that read them). The
-// workspace holds dim * NSLOT * n and 3 * n doubles either way.
-template <class R>
-__device__ __forceinline__ R* stored(double* buf) {
-  return reinterpret_cast<R*>(buf);
-}
-template <class R>
-__device__ __forceinline__ const R* stored(const double* buf) {
-  return reinterpret_cast<const R*>(buf);
-}
-
-struct MarchGrid {
-  int ntx, nty, nzc, lz;  // column tiles in x, y; runs of lz planes along z
-  unsigned nblocks;
-};
-
 struct TileGrid {
   int ntx, nty, ntz;
   unsigned ntiles;
@@ -73,11 +55,6 @@ struct TileGrid {
 // contiguous memory; halo reuse across XCDs is served by the Infinity Cache.
 // (Renumbering tiles so that each XCD owns a contiguous run measured slower
 // at 256^3: face kernel 1.77 vs 1.71 ms, update 1.11 vs 0.98 ms.)
-__device__ __forceinline__ int wrap_any(int i, int n) {
-  int r = i % n;
-  return r < 0 ? r + n : r;
-}
-
 template <int DIM>
 __device__ __forceinline__ void tile_origin(const TileGrid& tg, unsigned t, int& i0, int& j0,
                                             int& k0) {
@@ -211,9 +188,9 @@ __device__ __forceinline__ R emf_comp(const double* __restrict__ U,
 // v and b on those faces two planes down to one up) ride in registers from
 // plane to plane, so each is loaded once per run instead of up to four times.
 struct EmfCol {
-  static constexpr int TX = 64, TY = 4;
-  static constexpr int NT = TX * TY;  // workgroup size
+  static constexpr int NT = 256;  // workgroup size: 64 x 4 or 32 x 8 columns
 };
+constexpr int kEmfRun = 16;  // planes per run (8 and 32 measured no faster at 256^3)
 
 // The coefficients of one face the edge average takes: alpha+ and alpha-
 // (EM 0), or the UCT-HLLD weight and diffusion coefficients (EM 1).
@@ -253,8 +230,8 @@ __device__ __forceinline__ void emf_march(const double* __restrict__ U,
   const unsigned r = b / (unsigned)mg.ntx;
   const int ty = (int)(r % (unsigned)mg.nty);
   const int zc = (int)(r / (unsigned)mg.nty);
-  const int i = tx * EmfCol::TX + (int)threadIdx.x % EmfCol::TX;
-  const int j = ty * EmfCol::TY + (int)threadIdx.x / EmfCol::TX;
+  const int i = (tx << mg.lx) + ((int)threadIdx.x & ((1 << mg.lx) - 1));
+  const int j = ty * (EmfCol::NT >> mg.lx) + ((int)threadIdx.x >> mg.lx);
   if (i >= g.nx || j >= g.ny) return;
   const int k0 = zc * mg.lz;
   const int k1 = min(k0 + mg.lz, g.nz);
@@ -725,40 +702,6 @@ __device__ __forceinline__ void tile_face(const R (*sp)[Tile<DIM>::NPRIM], R bn,
 }
 
 // ---------------------------------------------------------------------------
-// CFL bound of one cell from its FP64 primitives: min over directions of
-// dx_d / (|v_d| + c_f,d), the expression of k_cfl.
-__device__ __forceinline__ double cfl_bound(const Geom& g, const double* W, double m) {
-  const double dd[3] = {g.dx, g.dy, g.dz};
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const double cf = cfast<double>(g.gamma, W[0], W[4], W[5 + d], W[5 + (d + 1) % 3],
-                                    W[5 + (d + 2) % 3]);
-    const double t = dd[d] / (__builtin_fabs(W[1 + d]) + cf);
-    m = (t < m) ? t : m;
-  }
-  return m;
-}
-
-// Minimum of v over the kBlock threads of the workgroup, stored by thread 0
-// to *out. Every thread of the workgroup must call it.
-__device__ __forceinline__ void workgroup_min_store(double v, double* __restrict__ out) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const double o = __shfl_xor(v, off, 64);
-    v = (o < v) ? o : v;
-  }
-  __shared__ double red[kBlock / 64];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) red[wid] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double r = red[0];
-#pragma unroll
-    for (int w = 1; w < kBlock / 64; ++w) r = (red[w] < r) ? red[w] : r;
-    *out = r;
-  }
-}
-
 // Face kernel: primitives of the tile and its cross halo are recovered once
 // (in FP64) into LDS, held in the reconstruction precision R, then each
 // thread solves the lower x/y(/z) faces of its cell. cflp != nullptr: also
@@ -904,334 +847,9 @@ __global__ __launch_bounds__(kBlock) void k_faces_weno(const double* __restrict_
   if (DIM == 3) weno_face<DIM, 2, RS, EM>(PW, U, FW, g, i, j, k, c);
 }
 
-// ---------------------------------------------------------------------------
-// 3D face kernel marching along z. A workgroup owns a 64 x 4 column of cells
-// and walks a run of planes k0 <= k < k1, one cell of each plane per thread.
-// LDS holds the primitives of planes k-1, k, k+1 of the column (a ring of
-// three) and the x/y cross halo (two cells below, one above) of planes k and
-// k+1 (two buffers). The lower z-face of cell k takes its left state
-// V_{k-1} + slope_{k-1}/2 from the previous plane's step, where the thread
-// computed slope_{k-1} for the right state of the face below; each z slope is
-// thus evaluated once. Per plane only the core of plane k+2 and the halo of
-// plane k+1 are recovered. Their raw values are loaded before any face of
-// plane k is solved, so that their latency hides behind the solves, and
-// waiting for them never waits for the face records stored after them (the
-// vector-memory counter retires in issue order); the normal fields of the
-// faces come from raw cells loaded two planes earlier. Neighbours read only
-// plane k of the ring and the current halo buffer, and a thread alone reads
-// its own cells of planes k-1 and k+1, so the recovered plane k+2 (into the
-// slot of plane k-1) and the halo of plane k+1 (into the other buffer) are
-// written without waiting, and one barrier per plane publishes them.
-// (Measured at 256^3 in FP64: 1.53 ms per launch against 1.65 ms for the
-// same arithmetic with the loads issued after the records of the plane and
-// two barriers per plane; 64 x 4 columns beat 16 x 16 ones, and dealing
-// x-neighbour columns to one XCD is slower than the natural order.)
-struct March {
-  static constexpr int TX = 64, TY = 4, NCORE = TX * TY;
-  static constexpr int NHALO = 3 * TY + 3 * TX;  // x-halo then y-halo
-  static constexpr int NQ = 8;                   // primitives per cell: V slots 0..7
-};
-static_assert(March::NCORE == kBlock, "one column cell per thread");
-static_assert(March::NHALO <= March::NCORE, "at most one halo cell per thread");
-
-// Planes per run: the prologue costs two extra planes per run, shorter runs
-// give more workgroups (4096 at 256^3 with 16; 16 measured faster than 32).
-constexpr int kMarchRun = 16;
 // Most CFL partials (2D tiles) that every workgroup of the first stage's
 // update reduces itself instead of a k_cfl_final launch (1024: KH 512^2).
 constexpr unsigned kUpdateCflMax = 1024;
-
-// 73.5 KB in FP64: two workgroups (eight waves) per CU.
-template <class R>
-struct MarchLds {
-  R ring[3][March::NQ][March::NCORE];   // planes by (k - k0 + 1) % 3
-  R halo[2][March::NQ][March::NHALO];   // planes by (k - k0) & 1
-};
-// flat offsets (in R) of the parts
-constexpr int kRingQ = March::NCORE;              // quantity stride in the ring
-constexpr int kRingP = March::NQ * March::NCORE;  // plane stride in the ring
-constexpr int kHaloOff = 3 * kRingP;
-constexpr int kHaloB = March::NQ * March::NHALO;  // halo buffer stride
-
-// Position of halo entry h of a plane, relative to the column origin;
-// s = 0, 1, 2: two cells below the column, then one above.
-__device__ __forceinline__ void march_halo_pos(int h, int& x, int& y) {
-  if (h < 3 * March::TY) {
-    const int s = h / March::TY;
-    y = h % March::TY;
-    x = (s < 2) ? s - 2 : March::TX;
-  } else {
-    h -= 3 * March::TY;
-    const int s = h / March::TX;
-    x = h % March::TX;
-    y = (s < 2) ? s - 2 : March::TY;
-  }
-}
-
-// Byte offsets within a plane of one field (FP64) of the values the primitive
-// recovery of cell (i, j) reads (indices wrapped): the cell, and its upper x
-// and y neighbours (staggered B_x, B_y). The staggered B_z above is the
-// cell's own offset in the next plane. 32 bits: a plane holds fewer than
-// 2^29 cells.
-struct PlaneOffs {
-  uint32_t c, xp, yp;
-};
-__device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j) {
-  const int iw = wrap_any(i, g.nx), jw = wrap_any(j, g.ny);
-  PlaneOffs p;
-  p.c = (uint32_t)(jw * g.nx + iw) * 8u;
-  p.xp = (uint32_t)(jw * g.nx + wrap(iw + 1, g.nx)) * 8u;
-  p.yp = (uint32_t)(wrap(jw + 1, g.ny) * g.nx + iw) * 8u;
-  return p;
-}
-// The value at byte offset off of the uniform base b.
-__device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t off) {
-  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
-}
-// Raw values of the cell at offsets p in plane kw; the staggered B_z above
-// from plane kw1 (both wrapped into 0..nz-1).
-__device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, const Geom& g,
-                                                  int64_t nxy, int kw, int kw1,
-                                                  const PlaneOffs& p) {
-  const double* pl = U + kw * nxy;
-  RawCell r;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) r.u[q] = ld_at(pl + q * g.n, p.c);
-  r.bxp = ld_at(pl + 5 * g.n, p.xp);
-  r.byp = ld_at(pl + 6 * g.n, p.yp);
-  r.bzp = ld_at(U + 7 * g.n + kw1 * nxy, p.c);
-  return r;
-}
-
-// Primitives of a raw cell (FP64 recovery) rounded to R, into LDS at lds[o]
-// with quantity stride st.
-template <class R>
-__device__ __forceinline__ bool march_recover(const RawCell& raw, double gamma, R* lds, int o,
-                                              int st, double* W) {
-  const bool ok = prim_from_raw<3>(raw, gamma, W);
-#pragma unroll
-  for (int q = 0; q < March::NQ; ++q) lds[o + q * st] = (R)W[q];
-  return ok;
-}
-
-// Offsets of plane-k cell (xx, yy) (at most one coordinate outside the
-// column): quantity q at lds[o + q * st]; r is the ring plane of k, hb its
-// halo buffer.
-__device__ __forceinline__ void march_xy(int r, int hb, int xx, int yy, int& o, int& st) {
-  if (xx < 0 || xx >= March::TX || yy < 0 || yy >= March::TY) {
-    const int h = (xx < 0 || xx >= March::TX)
-                      ? ((xx < 0) ? xx + 2 : 2) * March::TY + yy
-                      : 3 * March::TY + ((yy < 0) ? yy + 2 : 2) * March::TX + xx;
-    o = kHaloOff + hb * kHaloB + h;
-    st = March::NHALO;
-  } else {
-    o = r * kRingP + yy * March::TX + xx;
-    st = kRingQ;
-  }
-}
-
-// Writes the nine records of a lower face of the plane whose records start
-// at fwp (slot 0 of direction 0), the cell at byte offset boff.
-template <int D, int EM, class R>
-__device__ __forceinline__ void put_record_at(R* __restrict__ fwp, int64_t n, uint32_t boff,
-                                              const RiemannOut<R>& o) {
-  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  auto put = [&](int slot, R v) {
-    *reinterpret_cast<R*>(reinterpret_cast<char*>(fwp + ((int64_t)D * NSLOT + slot) * n) +
-                          boff) = v;
-  };
-  put(S_RHO, o.f[0]);
-  put(S_MX + D, o.f[1]);
-  put(S_MX + T1, o.f[2]);
-  put(S_MX + T2, o.f[3]);
-  put(S_EN, o.f[6]);
-  if (EM == 1) {
-    put(S_AP, o.om);
-    put(S_AM, o.dl);
-    put(S_DR, o.dr);
-  } else {
-    put(S_AP, o.ap);
-    put(S_AM, o.am);
-  }
-  put(S_V1, o.v1);
-  put(S_V2, o.v2);
-}
-
-template <int D, int RS, class R, int EM>
-__device__ __forceinline__ void march_solve(const R* wl, const R* wr, R bn, R gamma,
-                                            R* __restrict__ fwp, int64_t n, uint32_t boff) {
-  RiemannOut<R> o;
-  riemann<RS, R, EM>(gamma, wl, wr, bn, o);
-  put_record_at<D, EM, R>(fwp, n, boff, o);
-}
-
-// Reconstructed states of the lower x (D = 0) or y (D = 1) face of a cell of
-// plane k: PLM over the four stencil cells (offsets o*, strides s*).
-template <int D, int LIM, class R>
-__device__ __forceinline__ void march_recon_xy(const R* lds, const int* o, const int* st, R* wl,
-                                               R* wr) {
-  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  constexpr int slot[7] = {0, 1 + D, 1 + T1, 1 + T2, 5 + T1, 5 + T2, 4};
-#pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    const int sq = slot[q];
-    R v[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + sq * st[s]];
-    wl[q] = fma_r(R(0.5), plm_slope<LIM, R>(v[1] - v[0], v[2] - v[1]), v[1]);
-    wr[q] = fma_r(R(-0.5), plm_slope<LIM, R>(v[2] - v[1], v[3] - v[2]), v[2]);
-  }
-}
-
-// cflp != nullptr: also the CFL bound of the state, reduced over the cells
-// of this workgroup's column and run (each cell is the own cell of exactly
-// one workgroup and plane) into cflp[blockIdx.x]; k_cfl_final finishes it.
-// FULL: every column lies inside the grid (nx % 64 == 0, ny % 4 == 0), so no
-// thread skips the faces. Then every path through a plane issues the same
-// loads and stores, and the waits for the prefetched cells count exactly the
-// stores issued after them (no skipped-faces path forces waiting for the
-// stores as well).
-template <int LIM, int RS, class R, int EM, bool FULL>
-__global__ __launch_bounds__(kBlock)
-void k_faces_march(const double* __restrict__ U, double* __restrict__ FW, Geom g, MarchGrid mg,
-                   int* __restrict__ flag, double* __restrict__ cflp) {
-  // slots of the z-face frame (rho, v_z, v_x, v_y, B_x, B_y, p)
-  constexpr int zslot[7] = {0, 3, 1, 2, 5, 6, 4};
-  __shared__ MarchLds<R> L;
-  R* lds = &L.ring[0][0][0];
-  const unsigned b = blockIdx.x;
-  const int tx = (int)(b % (unsigned)mg.ntx);
-  const unsigned r = b / (unsigned)mg.ntx;
-  const int ty = (int)(r % (unsigned)mg.nty);
-  const int zc = (int)(r / (unsigned)mg.nty);
-  const int i0 = tx * March::TX, j0 = ty * March::TY;
-  const int k0 = zc * mg.lz;
-  const int k1 = min(k0 + mg.lz, g.nz);
-  const int x = (int)threadIdx.x % March::TX, y = (int)threadIdx.x / March::TX;
-  const int cidx = y * March::TX + x;
-  const int i = i0 + x, j = j0 + y;
-  const bool inside = FULL || ((i < g.nx) && (j < g.ny));
-  const int64_t nxy = (int64_t)g.nx * g.ny;
-  const R gam = (R)g.gamma;
-  // own cell; halo cell (threads past the halo load a valid cell and drop it)
-  const PlaneOffs po = plane_offs(g, i, j);
-  const bool haloer = (int)threadIdx.x < March::NHALO;
-  int hx, hy;
-  march_halo_pos(haloer ? (int)threadIdx.x : March::NHALO - 1, hx, hy);
-  const PlaneOffs ph = plane_offs(g, i0 + hx, j0 + hy);
-  bool bad = false;
-  // Prologue: own cells of planes k0-2 .. k0+1, the ring gets k0-1, k0,
-  // k0+1 (slots 0, 1, 2), halo buffer 0 the halo of plane k0; the left state
-  // of the first z-face. The staggered normal fields of the own cell (the
-  // raw B of its lower faces) of planes k and k+1 are carried in registers:
-  // each plane's are taken from the raw cell loaded two planes earlier.
-  R zl[7];
-  double cmin = __builtin_inf();  // CFL bound over this thread's own cells
-  double bn0[3], bn1[3];          // normal fields of planes k, k+1
-  {
-    const int km2 = wrap_any(k0 - 2, g.nz), km1 = wrap_any(k0 - 1, g.nz);
-    const int kp1 = wrap_any(k0 + 1, g.nz), kp2 = wrap_any(k0 + 2, g.nz);
-    double Wm2[8], Wm1[8], W[8];
-    bad |= !prim_from_raw<3>(load_raw_plane(U, g, nxy, km2, km1, po), g.gamma, Wm2);
-    bad |= !march_recover<R>(load_raw_plane(U, g, nxy, km1, k0, po), g.gamma, lds,
-                             0 * kRingP + cidx, kRingQ, Wm1);
-    R zm2[7], zm1[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      zm2[q] = (R)Wm2[zslot[q]];
-      zm1[q] = (R)Wm1[zslot[q]];
-    }
-    const RawCell c0 = load_raw_plane(U, g, nxy, k0, kp1, po);
-    bad |= !march_recover<R>(c0, g.gamma, lds, 1 * kRingP + cidx, kRingQ, W);
-    if (cflp && inside) cmin = cfl_bound(g, W, cmin);
-#pragma unroll
-    for (int q = 0; q < 7; ++q)
-      zl[q] = fma_r(R(0.5), plm_slope<LIM, R>(zm1[q] - zm2[q], (R)W[zslot[q]] - zm1[q]), zm1[q]);
-    const RawCell c1 = load_raw_plane(U, g, nxy, kp1, kp2, po);
-    bad |= !march_recover<R>(c1, g.gamma, lds, 2 * kRingP + cidx, kRingQ, W);
-    if (cflp && inside && k0 + 1 < k1) cmin = cfl_bound(g, W, cmin);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      bn0[d] = c0.u[5 + d];
-      bn1[d] = c1.u[5 + d];
-    }
-    if (haloer)
-      bad |= !march_recover<R>(load_raw_plane(U, g, nxy, k0, kp1, ph), g.gamma, lds,
-                               kHaloOff + (int)threadIdx.x, March::NHALO, W);
-  }
-  __syncthreads();
-  int rm = 0, r0 = 1, rp = 2, hb = 0;
-  R* const fw0 = stored<R>(FW);
-  const uint32_t boff = (uint32_t)(j * g.nx + i) * (uint32_t)sizeof(R);  // valid when inside
-  for (int k = k0; k < k1; ++k) {
-    const bool more = k + 1 < k1;
-    // The raw halo cell of plane k+1 and the raw own cell of plane k+2,
-    // loaded by every thread (in-bounds, wrapped indices) before any face
-    // record of this plane is stored.
-    const int ka = wrap_any(k + 1, g.nz), kb = wrap_any(k + 2, g.nz), kc = wrap_any(k + 3, g.nz);
-    const RawCell hr = load_raw_plane(U, g, nxy, ka, kb, ph);
-    const RawCell nxt = load_raw_plane(U, g, nxy, kb, kc, po);
-    R* const fwp = fw0 + k * nxy;
-    R wl[7], wr[7];
-    int o[4], st[4];
-    if (inside) {
-      march_xy(r0, hb, x - 2, y, o[0], st[0]);
-      march_xy(r0, hb, x - 1, y, o[1], st[1]);
-      march_xy(r0, hb, x, y, o[2], st[2]);
-      march_xy(r0, hb, x + 1, y, o[3], st[3]);
-      march_recon_xy<0, LIM, R>(lds, o, st, wl, wr);
-    }
-    // the halo of plane k+1 into the other buffer (read by no one before the
-    // barrier below), once the x reconstruction has covered its latency
-    if (more && haloer) {
-      double W[8];
-      bad |= !march_recover<R>(hr, g.gamma, lds, kHaloOff + (hb ^ 1) * kHaloB + (int)threadIdx.x,
-                               March::NHALO, W);
-    }
-    if (inside) {
-      march_solve<0, RS, R, EM>(wl, wr, (R)bn0[0], gam, fwp, g.n, boff);
-      march_xy(r0, hb, x, y - 2, o[0], st[0]);
-      march_xy(r0, hb, x, y - 1, o[1], st[1]);
-      march_xy(r0, hb, x, y + 1, o[3], st[3]);
-      march_recon_xy<1, LIM, R>(lds, o, st, wl, wr);
-      march_solve<1, RS, R, EM>(wl, wr, (R)bn0[1], gam, fwp, g.n, boff);
-      // z face: left state carried from the plane below; the slope of cell k
-      // gives the right state and the next plane's left state
-#pragma unroll
-      for (int q = 0; q < 7; ++q) {
-        const int sq = zslot[q];
-        const R a = lds[rm * kRingP + sq * kRingQ + cidx];
-        const R bb = lds[r0 * kRingP + sq * kRingQ + cidx];
-        const R cc = lds[rp * kRingP + sq * kRingQ + cidx];
-        const R dlt = plm_slope<LIM, R>(bb - a, cc - bb);
-        wl[q] = zl[q];
-        wr[q] = fma_r(R(-0.5), dlt, bb);
-        zl[q] = fma_r(R(0.5), dlt, bb);
-      }
-      march_solve<2, RS, R, EM>(wl, wr, (R)bn0[2], gam, fwp, g.n, boff);
-    }
-    if (more) {
-      // plane k+2 into the ring slot of plane k-1 (own cell, read by no
-      // other thread)
-      double W[8];
-      bad |= !march_recover<R>(nxt, g.gamma, lds, rm * kRingP + cidx, kRingQ, W);
-      if (cflp && inside && k + 2 < k1) cmin = cfl_bound(g, W, cmin);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        bn0[d] = bn1[d];
-        bn1[d] = nxt.u[5 + d];
-      }
-      __syncthreads();
-    }
-    const int t = rm;
-    rm = r0;
-    r0 = rp;
-    rp = t;
-    hb ^= 1;
-  }
-  if (cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
-  if (bad) atomicOr(flag, 1);
-}
 
 // CFL: per-cell min over directions of dx_d / (|v_d| + c_f,d); grid-stride,
 // wave64 shuffle + LDS reduction to one partial per block.
@@ -1522,18 +1140,74 @@ TileGrid tile_grid(const Geom& g) {
   return tg;
 }
 
-MarchGrid march_grid(const Geom& g) {
+// Columns and runs of the EMF march: 32 x 8 columns where 64 x 4 ones would
+// leave more lanes past the grid; runs of 16 planes, shorter where those
+// would not give every CU its two workgroups.
+MarchGrid emf_grid(const Geom& g) {
   MarchGrid mg;
-  mg.ntx = (g.nx + March::TX - 1) / March::TX;
-  mg.nty = (g.ny + March::TY - 1) / March::TY;
-  mg.lz = g.nz < kMarchRun ? g.nz : kMarchRun;
+  const int w64 = (g.nx + 63) / 64 * 64, w32 = (g.nx + 31) / 32 * 32;
+  mg.lx = (w32 < w64) ? 5 : 6;
+  const int TX = 1 << mg.lx, TY = EmfCol::NT / TX;
+  mg.ntx = (g.nx + TX - 1) / TX;
+  mg.nty = (g.ny + TY - 1) / TY;
+  mg.lz = g.nz < kEmfRun ? g.nz : kEmfRun;
+  while (mg.lz > 1 && (int64_t)mg.ntx * mg.nty * ((g.nz + mg.lz - 1) / mg.lz) < 512) mg.lz /= 2;
   mg.nzc = (g.nz + mg.lz - 1) / mg.lz;
   mg.nblocks = (unsigned)mg.ntx * (unsigned)mg.nty * (unsigned)mg.nzc;
   return mg;
 }
 
+template <int LIM, class R, int EM>
+void launch_emf_march(const StageArgs& a) {
+  const MarchGrid eg = emf_grid(a.g);
+  if constexpr (EM == 1)
+    MHD_TIMED(a, K_EMF,
+              hipLaunchKernelGGL((k_emf_march_hlld<LIM, R>), dim3(eg.nblocks), dim3(EmfCol::NT), 0,
+                                 a.stream, a.U, a.FW, a.EW, a.g, eg));
+  else
+    MHD_TIMED(a, K_EMF,
+              hipLaunchKernelGGL((k_emf_march<LIM, R>), dim3(eg.nblocks), dim3(EmfCol::NT), 0,
+                                 a.stream, a.U, a.FW, a.EW, a.g, eg));
+}
+
+// 3D PLM stage: the face kernel finishes the cell-averaged fields itself,
+// then the EMFs and the update of the staggered field. Where the time step is
+// the CFL bound of U (not known before that kernel ends) or L(U) is wanted
+// beside the state, the face kernel leaves L and the update finishes all
+// eight fields.
+hipError_t stage_plm3d(const StageArgs& a) {
+  const MarchGrid mg = march_grid(a.g);
+  const bool late = a.cfl_partial || a.keep_rhs;
+  double* Lc = a.cfl_partial ? a.out : a.FW;  // FW: slots S_RHO .. S_EN of direction 0
+  MHD_TIMED(a, K_FACES, launch_faces_march(a, mg, late ? 0 : a.stage, late ? Lc : a.out));
+  if (a.cfl_partial)
+    MHD_TIMED(a, K_CFL_FINAL,
+              hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, a.cfl_partial,
+                                 (int)mg.nblocks, a.cfl, a.dt_out));
+  if (a.precision == 1) {
+    if (a.limiter == 0) {
+      if (a.emf == 1) launch_emf_march<0, float, 1>(a);
+      else launch_emf_march<0, float, 0>(a);
+    } else {
+      if (a.emf == 1) launch_emf_march<1, float, 1>(a);
+      else launch_emf_march<1, float, 0>(a);
+    }
+  } else {
+    if (a.limiter == 0) {
+      if (a.emf == 1) launch_emf_march<0, double, 1>(a);
+      else launch_emf_march<0, double, 0>(a);
+    } else {
+      if (a.emf == 1) launch_emf_march<1, double, 1>(a);
+      else launch_emf_march<1, double, 0>(a);
+    }
+  }
+  if (a.stage != 3) MHD_TIMED(a, K_UPDATE, launch_update_b(a, late ? Lc : nullptr));
+  return hipGetLastError();
+}
+
 template <int DIM, int LIM, int RS, class R, int EM>
 hipError_t stage_impl(const StageArgs& a) {
+  static_assert(DIM == 2 || LIM == 2, "3D PLM is stage_plm3d");
   // LIM 2 (WENO-Z, FP64): faces by k_faces_weno, edge values by van Leer PLM
   constexpr int ELIM = (LIM == 2) ? 1 : LIM;
   const TileGrid rg = tile_grid<RowTile>(a.g);
@@ -1552,22 +1226,6 @@ hipError_t stage_impl(const StageArgs& a) {
     MHD_TIMED(a, K_FACES,
               hipLaunchKernelGGL((k_faces_weno<DIM, RS, EM>), dim3(nl), dim3(kBlock), 0, a.stream,
                                  a.PW, a.U, a.FW, a.g));
-  } else if constexpr (DIM == 3) {
-    const MarchGrid mg = march_grid(a.g);
-    if (a.g.nx % March::TX == 0 && a.g.ny % March::TY == 0)
-      MHD_TIMED(a, K_FACES,
-                hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM, true>), dim3(mg.nblocks),
-                                   dim3(kBlock), 0, a.stream, a.U, a.FW, a.g, mg, a.flag,
-                                   a.cfl_partial));
-    else
-      MHD_TIMED(a, K_FACES,
-                hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM, false>), dim3(mg.nblocks),
-                                   dim3(kBlock), 0, a.stream, a.U, a.FW, a.g, mg, a.flag,
-                                   a.cfl_partial));
-    if (a.cfl_partial)  // dt of the state U, before the update kernels read it
-      MHD_TIMED(a, K_CFL_FINAL,
-                hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, a.cfl_partial,
-                                   (int)mg.nblocks, a.cfl, a.dt_out));
   } else {
     const TileGrid tg = tile_grid<Tile<DIM>>(a.g);
     MHD_TIMED(a, K_FACES,
@@ -1582,20 +1240,7 @@ hipError_t stage_impl(const StageArgs& a) {
                                    (int)tg.ntiles, a.cfl, a.dt_out));
   }
   if constexpr (DIM == 3) {
-    MarchGrid eg;
-    eg.ntx = (a.g.nx + EmfCol::TX - 1) / EmfCol::TX;
-    eg.nty = (a.g.ny + EmfCol::TY - 1) / EmfCol::TY;
-    eg.lz = a.g.nz < kMarchRun ? a.g.nz : kMarchRun;
-    eg.nzc = (a.g.nz + eg.lz - 1) / eg.lz;
-    eg.nblocks = (unsigned)eg.ntx * (unsigned)eg.nty * (unsigned)eg.nzc;
-    if constexpr (EM == 1)
-      MHD_TIMED(a, K_EMF,
-                hipLaunchKernelGGL((k_emf_march_hlld<ELIM, R>), dim3(eg.nblocks),
-                                   dim3(EmfCol::NT), 0, a.stream, a.U, a.FW, a.EW, a.g, eg));
-    else
-      MHD_TIMED(a, K_EMF,
-                hipLaunchKernelGGL((k_emf_march<ELIM, R>), dim3(eg.nblocks), dim3(EmfCol::NT), 0,
-                                   a.stream, a.U, a.FW, a.EW, a.g, eg));
+    launch_emf_march<ELIM, R, EM>(a);
   } else if (a.stage == 3) {  // 2D records only; the 2D stages fuse the EMF into the update
     MHD_TIMED(a, K_EMF,
               hipLaunchKernelGGL((k_emf<DIM, ELIM, R, EM>), dim3(nb), dim3(RowTile::NT), 0, a.stream, a.U,
@@ -1717,14 +1362,18 @@ hipError_t stage_lim(const StageArgs& a) {
     return a.riemann == 0 ? stage_impl<DIM, 2, 0, double, EM>(a)
                           : stage_impl<DIM, 2, 1, double, EM>(a);
   }
-  if (a.limiter == 0) {
+  if constexpr (DIM == 3) {
+    return stage_plm3d(a);
+  } else {
+    if (a.limiter == 0) {
+      if (a.riemann == 0)
+        return mixed ? stage_impl<DIM, 0, 0, float, EM>(a) : stage_impl<DIM, 0, 0, double, EM>(a);
+      return mixed ? stage_impl<DIM, 0, 1, float, EM>(a) : stage_impl<DIM, 0, 1, double, EM>(a);
+    }
     if (a.riemann == 0)
-      return mixed ? stage_impl<DIM, 0, 0, float, EM>(a) : stage_impl<DIM, 0, 0, double, EM>(a);
-    return mixed ? stage_impl<DIM, 0, 1, float, EM>(a) : stage_impl<DIM, 0, 1, double, EM>(a);
+      return mixed ? stage_impl<DIM, 1, 0, float, EM>(a) : stage_impl<DIM, 1, 0, double, EM>(a);
+    return mixed ? stage_impl<DIM, 1, 1, float, EM>(a) : stage_impl<DIM, 1, 1, double, EM>(a);
   }
-  if (a.riemann == 0)
-    return mixed ? stage_impl<DIM, 1, 0, float, EM>(a) : stage_impl<DIM, 1, 0, double, EM>(a);
-  return mixed ? stage_impl<DIM, 1, 1, float, EM>(a) : stage_impl<DIM, 1, 1, double, EM>(a);
 }
 
 }  // namespace

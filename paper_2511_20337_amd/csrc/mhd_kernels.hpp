@@ -46,6 +46,16 @@ struct StageArgs {
   double* cfl_partial;
   double cfl;
   double* dt_out;
+  // 3D PLM only: L(U) of the five cell-averaged fields is left in FW (n
+  // doubles each from its start, space no edge input uses) besides
+  bool keep_rhs;
+};
+
+// Column tiles in x, y (of 1 << lx cells along x, where that varies) and runs
+// of lz planes along z.
+struct MarchGrid {
+  int ntx, nty, nzc, lz, lx;
+  unsigned nblocks;
 };
 
 struct CflArgs {
@@ -75,6 +85,11 @@ size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm);
 // GLM: the CFL time step of U through its primitive kernel (writes PW too)
 hipError_t launch_glm_cfl(const CflArgs& a, double* PW);
 hipError_t launch_cfl(const CflArgs& a);
+// 3D PLM face kernel (stage 3: edge inputs only) and the update that follows
+// the EMFs (Lc: the cell fields' L where they are not finished yet, or null).
+MarchGrid march_grid(const Geom& g);
+void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out);
+void launch_update_b(const StageArgs& a, const double* Lc);
 // Partials of the allocation-free CFL time step (a file-scope device array of
 // that many doubles plus the flag; nblocks must not exceed it).
 constexpr int kNoAllocPartials = 2048;

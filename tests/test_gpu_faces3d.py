@@ -1,0 +1,52 @@
+"""The 3D PLM face kernel at the sizes where its columns (32 x 8 cells), the
+faces solved above them and its runs along z can go wrong, against the oracle:
+FP64 to the repository's 1e-12 per field, mixed precision to the mixed path's
+stated 2e-5."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2511_20337_amd import workloads as W
+from tests.test_gpu_parity import rel_err
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# one column; a column and one cell, or one row, more; a cell and a row less;
+# the smallest grid; more than one plane per run, the last run shorter
+GRIDS = [(32, 8, 4), (33, 9, 5), (31, 7, 6), (4, 4, 4), (64, 16, 9), (5, 40, 4), (65, 17, 709)]
+
+
+@pytest.mark.parametrize("grid", GRIDS)
+@pytest.mark.parametrize("scheme", ["hlld", "hll_uct_hlld", "hlld_uct_hlld_rk3", "mixed_rk3"])
+def test_columns_and_runs(grid, scheme):
+    from paper_2511_20337_amd import mhd
+    nx, ny, nz = grid
+    s, U0 = W.generic_state(3, nx, ny, nz, "minmod" if scheme == "hlld" else "vanleer",
+                            "hll" if scheme.startswith("hll_") else "hlld", seed=nx + nz)
+    s = dict(s, emf="uct_hlld" if "uct_hlld" in scheme else "uct_hll",
+             integrator="rk3" if "rk3" in scheme else "rk2",
+             precision="mixed" if "mixed" in scheme else "fp64")
+    tol = 2e-5 if "mixed" in scheme else 1e-12
+    print("columns and runs", grid, scheme, flush=True)
+    ctx = mhd.Context(s, "cuda:0")
+    U = torch.from_numpy(U0).cuda()
+    c = O.cfg_from(s)
+    err = rel_err(ctx.rhs(U).cpu().numpy(), O.rhs(c, U0))
+    assert (err <= tol).all(), err
+    # dt inside the step (its update finishes the cell fields) and beforehand
+    # (the face kernel does): the same bits
+    Ub, dts = U.clone(), []
+    for _ in range(2):
+        ctx.step_cfl(U)
+        ctx.step_device_dt(Ub, ctx.dt_dev)
+        dts.append(ctx.dt_dev.item())
+        assert torch.equal(U, Ub)
+    ctx.check()
+    got = U.cpu().numpy()
+    err = rel_err(got, O.run_dts(c, U0, np.array(dts)))
+    assert (err <= tol).all(), err
+    # the two sides of a column's edge take the same flux
+    for q in range(5):
+        mag = np.abs(U0[q]).sum() + np.abs(U0[1:4]).sum() * (1 <= q <= 3)
+        assert abs(got[q].sum() - U0[q].sum()) <= 1e-12 * mag, q

@@ -609,8 +609,7 @@ __device__ __forceinline__ void pw_states(const double (&v)[7][4], double* wl, d
 #pragma unroll
   for (int q = 0; q < 7; ++q) {
     const double a = v[q][0], b = v[q][1], c = v[q][2], e = v[q][3];
-    wl[q] = fma_r(0.5, plm_slope<LIM, double>(b - a, c - b), b);
-    wr[q] = fma_r(-0.5, plm_slope<LIM, double>(c - b, e - c), c);
+    plm_pair<LIM, double>(a, b, c, e, wl[q], wr[q]);
   }
 }
 

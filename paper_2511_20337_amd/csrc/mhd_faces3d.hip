@@ -174,12 +174,6 @@ __device__ __forceinline__ void cell_fluxes(const RiemannOut<R>& o, R* F) {
   F[4] = o.f[6];
 }
 
-// Left and right value at a face from the four cells about it.
-template <int LIM, class R>
-__device__ __forceinline__ void recon_pair(const R* v, R& l, R& r) {
-  l = fma_r(R(0.5), plm_slope<LIM, R>(v[1] - v[0], v[2] - v[1]), v[1]);
-  r = fma_r(R(-0.5), plm_slope<LIM, R>(v[2] - v[1], v[3] - v[2]), v[2]);
-}
 // Reconstructed states of a face from its four stencil cells (offsets o);
 // slot: the quantities of the face frame.
 template <int LIM, class R>
@@ -190,7 +184,7 @@ __device__ __forceinline__ void march_recon(const R* lds, const int* o, const in
     R v[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + slot[q] * kMarchQ];
-    recon_pair<LIM, R>(v, wl[q], wr[q]);
+    plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
   }
 }
 
@@ -288,7 +282,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     bad |= !prim_from_raw<3>(rm2, g.gamma, Wm2);
     bad |= !prim_from_raw<3>(rm1, g.gamma, Wm1);
     bad |= !prim_from_raw<3>(rc, g.gamma, W);
-    if (cflp) cmin = cfl_bound(g, W, cmin);
+    if (cflp) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
     for (int q = 0; q < M::NQ; ++q) {
       lds[q * kMarchQ + M::NCORE + t] = (R)Wm1[q];
@@ -297,7 +291,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
       const R a = (R)Wm2[zslot[q]], bb = (R)Wm1[zslot[q]], c = (R)W[zslot[q]];
-      zl[q] = fma_r(R(0.5), plm_slope<LIM, R>(bb - a, c - bb), bb);
+      zl[q] = plm_up<LIM, R>(plm_slope<LIM, R>(bb - a, c - bb), bb);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) bn[d] = rc.u[5 + d];
@@ -323,7 +317,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     {
       double W[8];
       bad |= !prim_from_raw<3>(nxt, g.gamma, W);
-      if (cflp && k + 1 < k1) cmin = cfl_bound(g, W, cmin);
+      if (cflp && k + 1 < k1) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
       for (int d = 0; d < 3; ++d) bnn[d] = nxt.u[5 + d];
       const int cn = M::NCORE - cp + t;  // own cell in the other core plane: k - 1, then k + 1
@@ -335,8 +329,8 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
         const R c = (R)W[sq];
         const R dlt = plm_slope<LIM, R>(bb - a, c - bb);
         wl[q] = zl[q];
-        wr[q] = fma_r(R(-0.5), dlt, bb);
-        zl[q] = fma_r(R(0.5), dlt, bb);
+        wr[q] = plm_lo<LIM, R>(dlt, bb);
+        zl[q] = plm_up<LIM, R>(dlt, bb);
       }
 #pragma unroll
       for (int q = 0; q < M::NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
@@ -423,7 +417,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
         R v[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) v[s] = lds[os[kind[q]][s] + xslot[q] * kMarchQ];
-        recon_pair<LIM, R>(v, wl[q], wr[q]);
+        plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
       }
       riemann<RS, R, EM>(gam, wl, wr, (R)ebn, o);
       fe[0] = o.f[0];

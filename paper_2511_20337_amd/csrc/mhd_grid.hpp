@@ -59,7 +59,7 @@ __device__ __forceinline__ bool prim_from_raw(const RawCell& r, double gamma, do
   const double bx = 0.5 * (r.u[5] + r.bxp);
   const double by = 0.5 * (r.u[6] + r.byp);
   const double bz = (DIM == 3) ? 0.5 * (r.u[7] + r.bzp) : r.u[7];
-  const double irho = 1.0 / rho;
+  const double irho = rcp_r(rho);
   const double vx = mx * irho, vy = my * irho, vz = mz * irho;
   const double kin = 0.5 * fma_r(mz, vz, fma_r(my, vy, mx * vx));
   const double mag = 0.5 * fma_r(bz, bz, fma_r(by, by, bx * bx));
@@ -95,8 +95,7 @@ __device__ __forceinline__ void face_inputs(const double* __restrict__ U, const 
   for (int q = 0; q < 7; ++q) {
     const int s = slot[q];
     const double a = V[0][s], b = V[1][s], c = V[2][s], e = V[3][s];
-    wl[q] = fma_r(0.5, plm_slope<LIM, double>(b - a, c - b), b);
-    wr[q] = fma_r(-0.5, plm_slope<LIM, double>(c - b, e - c), c);
+    plm_pair<LIM, double>(a, b, c, e, wl[q], wr[q]);
   }
   bn = U[(F_BX + D) * g.n + lin(g, i, j, k)];
 }
@@ -154,14 +153,15 @@ __device__ __forceinline__ const R* stored(const double* buf) {
 }
 
 // CFL bound of one cell from its FP64 primitives: min over directions of
-// dx_d / (|v_d| + c_f,d), the expression of k_cfl.
+// dx_d / (|v_d| + c_f,d).
+template <int DIM>
 __device__ __forceinline__ double cfl_bound(const Geom& g, const double* W, double m) {
   const double dd[3] = {g.dx, g.dy, g.dz};
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
+  for (int d = 0; d < DIM; ++d) {
     const double cf = cfast<double>(g.gamma, W[0], W[4], W[5 + d], W[5 + (d + 1) % 3],
                                     W[5 + (d + 2) % 3]);
-    const double t = dd[d] / (__builtin_fabs(W[1 + d]) + cf);
+    const double t = div_r(dd[d], __builtin_fabs(W[1 + d]) + cf);
     m = (t < m) ? t : m;
   }
   return m;

@@ -693,8 +693,7 @@ __device__ __forceinline__ void tile_face(const R (*sp)[Tile<DIM>::NPRIM], R bn,
   for (int q = 0; q < 7; ++q) {
     const R* P = sp[slot[q]];
     const R a = P[e[0]], b = P[e[1]], cc = P[e[2]], d = P[e[3]];
-    wl[q] = fma_r(R(0.5), plm_slope<LIM, R>(b - a, cc - b), b);
-    wr[q] = fma_r(R(-0.5), plm_slope<LIM, R>(cc - b, d - cc), cc);
+    plm_pair<LIM, R>(a, b, cc, d, wl[q], wr[q]);
   }
   RiemannOut<R> o;
   riemann<RS, R, EM>((R)g.gamma, wl, wr, bn, o);
@@ -741,7 +740,7 @@ __global__ __launch_bounds__(Tile<DIM>::NCORE) void k_faces_tiled(const double* 
 #pragma unroll
     for (int q = 0; q < 8; ++q) sp[q][e] = (R)V[q];
     // the core comes first, thread t's first entry is its own cell
-    if (cflp && inside && e == (int)threadIdx.x) cmin = cfl_bound(g, V, cmin);
+    if (cflp && inside && e == (int)threadIdx.x) cmin = cfl_bound<DIM>(g, V, cmin);
   }
   if (bad) atomicOr(flag, 1);
   __syncthreads();
@@ -789,7 +788,7 @@ __global__ __launch_bounds__(kBlock) void k_prim_weno(const double* __restrict__
 #pragma unroll
     for (int q = 0; q < 8; ++q) PW[q * g.n + c] = V[q];
     if (!ok) atomicOr(flag, 1);
-    if (DIM == 3 && cflp) cmin = cfl_bound(g, V, cmin);
+    if (DIM == 3 && cflp) cmin = cfl_bound<3>(g, V, cmin);
   }
   if (DIM == 3 && cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
 }
@@ -864,14 +863,7 @@ __global__ __launch_bounds__(kBlock) void k_cfl(const double* __restrict__ U, Ge
     coords(g, c, i, j, k);
     double V[8];
     if (!prim_at<DIM>(U, g, i, j, k, V)) atomicOr(flag, 1);
-    const double dd[3] = {g.dx, g.dy, g.dz};
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      const double cf = cfast<double>(g.gamma, V[0], V[4], V[5 + d], V[5 + (d + 1) % 3],
-                                      V[5 + (d + 2) % 3]);
-      const double t = dd[d] / (__builtin_fabs(V[1 + d]) + cf);
-      m = (t < m) ? t : m;
-    }
+    m = cfl_bound<DIM>(g, V, m);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -921,19 +913,6 @@ __global__ __launch_bounds__(1024) void k_cfl_final(const double* __restrict__ p
 // the damping of psi in the last stage).
 constexpr int kGlmFields = 9;
 
-template <int DIM>
-__device__ __forceinline__ double cfl_bound_dim(const Geom& g, const double* W, double m) {
-  const double dd[3] = {g.dx, g.dy, g.dz};
-#pragma unroll
-  for (int d = 0; d < DIM; ++d) {
-    const double cf = cfast<double>(g.gamma, W[0], W[4], W[5 + d], W[5 + (d + 1) % 3],
-                                    W[5 + (d + 2) % 3]);
-    const double t = dd[d] / (__builtin_fabs(W[1 + d]) + cf);
-    m = (t < m) ? t : m;
-  }
-  return m;
-}
-
 // Primitives (rho, v_x, v_y, v_z, p, B_x, B_y, B_z, psi) of every cell into
 // PW[9][n] (FP64; the field is already cell-centred), the workgroup's CFL
 // partial into cflp[blockIdx.x] (nullable).
@@ -951,7 +930,7 @@ __global__ __launch_bounds__(kBlock) void k_glm_prim(const double* __restrict__ 
     const double rho = U[c];
     const double mx = U[n + c], my = U[2 * n + c], mz = U[3 * n + c], en = U[4 * n + c];
     const double bx = U[5 * n + c], by = U[6 * n + c], bz = U[7 * n + c];
-    const double irho = 1.0 / rho;
+    const double irho = rcp_r(rho);
     const double vx = mx * irho, vy = my * irho, vz = mz * irho;
     const double kin = 0.5 * fma_r(mz, vz, fma_r(my, vy, mx * vx));
     const double mag = 0.5 * fma_r(bz, bz, fma_r(by, by, bx * bx));
@@ -962,7 +941,7 @@ __global__ __launch_bounds__(kBlock) void k_glm_prim(const double* __restrict__ 
     const bool ok = (rho > 0.0) && (p > 0.0) && __builtin_isfinite(p) &&
                     __builtin_isfinite(vx) && __builtin_isfinite(vy) && __builtin_isfinite(vz);
     if (!ok) atomicOr(flag, 1);
-    if (cflp) cmin = cfl_bound_dim<DIM>(g, V, cmin);
+    if (cflp) cmin = cfl_bound<DIM>(g, V, cmin);
   }
   if (cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
 }
@@ -1008,8 +987,7 @@ __device__ __forceinline__ void glm_face(const double* __restrict__ PW, double* 
       R v[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) v[s] = (R)v8[s];
-      wl[q] = fma_r(R(0.5), plm_slope<LIM, R>(v[1] - v[0], v[2] - v[1]), v[1]);
-      wr[q] = fma_r(R(-0.5), plm_slope<LIM, R>(v[2] - v[1], v[3] - v[2]), v[2]);
+      plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
     }
   }
   const R bns = R(0.5) * (wl[7] + wr[7]) - div_r(wr[8] - wl[8], R(2) * ch);

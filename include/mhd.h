@@ -173,6 +173,14 @@ mhd_status mhd_step_device_dt(mhd_ctx* ctx, double* U, const double* dt_dev, voi
 mhd_status mhd_step_cfl(mhd_ctx* ctx, double* U, double* dt_dev, void* ws, size_t ws_bytes,
                         void* stream);
 
+/* nsteps (>= 0) steps as by mhd_step_cfl, the same states and time steps;
+ * *dt_dev holds the last step's dt at the end. No host synchronisation. In 2D
+ * with PLM and CT the last stage of a step reduces the CFL bound of the state
+ * it writes, which the next step then takes, so that the state lies in the
+ * workspace after every other of the steps (in U after the last). */
+mhd_status mhd_run(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,
+                   size_t ws_bytes, void* stream);
+
 /* Right-hand side L(U) of the semi-discrete equations for all eight stored
  * fields (same layout as U), without time integration. U and L must not
  * alias. */

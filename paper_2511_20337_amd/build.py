@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libmhd.so")
-SOURCES = ["mhd_api.hip", "mhd_kernels.hip", "mhd_faces3d.hip", "mhd_adjoint.hip"]
+SOURCES = ["mhd_api.hip", "mhd_kernels.hip", "mhd_adjoint.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -1005,6 +1005,7 @@ hipError_t adjoint_impl(const AdjointArgs& a) {
   f.EW = a.EW;
   f.dt = a.dt;
   f.dtp = nullptr;
+  f.records = a.dim == 2;
   f.keep_rhs = a.dim == 3 && a.want_dtbar;  // L(U) for dt-bar
   f.flag = a.flag;
   f.stream = a.stream;

@@ -219,6 +219,59 @@ mhd_status run_step(mhd_ctx* ctx, double* U, double dt, const double* dtp, void*
   return MHD_OK;
 }
 
+// nsteps steps with the 2D PLM stages, dt of each step in *dt_dev. The last
+// stage of a step leaves the CFL partials of the state it writes to the next
+// step, which needs the state it reads left alone: the steps alternate between
+// U and a second state, and the last one ends in U. The second state and the
+// partials take the space of the face records, which these stages do not use.
+mhd_status run_2d(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,
+                  hipStream_t s) {
+  double* alt = reinterpret_cast<double*>(base(ws) + ctx->off_fw);
+  const size_t n = (size_t)ctx->g.n;
+  const int np = mhd::stage_2d_tiles(ctx->g, ctx->cfg.precision, ctx->cfg.emf);
+  double* part[2] = {alt + 8 * n, alt + 8 * n + np};
+  double* U1 = reinterpret_cast<double*>(base(ws) + ctx->off_u1);
+  double* U2 = reinterpret_cast<double*>(base(ws) + ctx->off_u2);
+  const bool rk3 = ctx->cfg.integrator == MHD_SSP_RK3;
+  double* cur = U;
+  for (int64_t k = 0; k < nsteps; ++k) {
+    const bool last = k + 1 == nsteps;
+    double* next = last ? U : (cur == U ? alt : U);
+    mhd::StageArgs a = stage_args(ctx, ws, s);
+    a.dtp = dt_dev;
+    a.cfl = ctx->cfg.cfl;
+    a.dt_out = dt_dev;
+    a.stage = 1;
+    a.U = cur;
+    a.out = U1;
+    a.cfl_partial = reinterpret_cast<double*>(base(ws) + ctx->off_partial);
+    if (k > 0) {
+      a.cfl_prev = part[k % 2];
+      a.ncfl = np;
+    }
+    hipError_t e = mhd::launch_stage(a);
+    if (e != hipSuccess) return device_fail(ctx, e, "stage 1");
+    a.cfl_partial = nullptr;
+    a.cfl_prev = nullptr;
+    a.U0 = cur;
+    a.U = U1;
+    if (rk3) {
+      a.stage = 4;
+      a.out = U2;
+      e = mhd::launch_stage(a);
+      if (e != hipSuccess) return device_fail(ctx, e, "stage 2");
+      a.U = U2;
+    }
+    a.stage = rk3 ? 5 : 2;
+    a.out = next;
+    if (!last) a.cfl_next = part[(k + 1) % 2];
+    e = mhd::launch_stage(a);
+    if (e != hipSuccess) return device_fail(ctx, e, "last stage");
+    cur = next;
+  }
+  return MHD_OK;
+}
+
 mhd_status cfl_to(mhd_ctx* ctx, const double* U, void* ws, double* dt_dev, hipStream_t s) {
   if (ctx->cfg.divb == MHD_DIVB_GLM) {  // through the GLM primitive kernel
     mhd::CflArgs a{};
@@ -397,6 +450,20 @@ mhd_status mhd_step_cfl(mhd_ctx* ctx, double* U, double* dt_dev, void* ws, size_
   mhd_status st = cfl_to(ctx, U, ws, dt_dev, s);  // 2D WENO-Z: the separate CFL pass
   if (st != MHD_OK) return st;
   return run_step(ctx, U, 0.0, dt_dev, ws, s);
+}
+
+mhd_status mhd_run(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,
+                   size_t ws_bytes, void* stream) {
+  if (!ctx) return MHD_ERR_INVALID;
+  if (!U || !dt_dev || nsteps < 0) return MHD_ERR_INVALID;
+  if (!ws_ok(ctx, ws, ws_bytes, false)) return MHD_ERR_WORKSPACE;
+  if (ctx->cfg.dim == 2 && ctx->cfg.divb == MHD_DIVB_CT && ctx->cfg.limiter != MHD_LIM_WENOZ)
+    return run_2d(ctx, U, nsteps, dt_dev, ws, static_cast<hipStream_t>(stream));
+  for (int64_t k = 0; k < nsteps; ++k) {
+    const mhd_status st = mhd_step_cfl(ctx, U, dt_dev, ws, ws_bytes, stream);
+    if (st != MHD_OK) return st;
+  }
+  return MHD_OK;
 }
 
 mhd_status mhd_rhs(mhd_ctx* ctx, const double* U, double* L, void* ws, size_t ws_bytes,

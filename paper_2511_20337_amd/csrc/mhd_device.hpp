@@ -621,4 +621,43 @@ __device__ __forceinline__ void edge_pair(R xm2, R xm1, R x0, R xp1, R& lo, R& h
   plm_pair<LIM, R>(xm2, xm1, x0, xp1, lo, hi);
 }
 
+// Upwind edge EMF from its inputs: alpha+- of the two a-faces touching the
+// edge (below the edge along B, then the cell's own), of the two b-faces
+// (below along A, then own); the face velocity v_A and the field b_B on the
+// b-faces at A-offsets -2..+1, and v_B and b_A on the a-faces at B-offsets
+// -2..+1, each reconstructed toward the edge.
+template <int LIM, class R>
+__device__ __forceinline__ R emf_core(R apa_m, R apa_c, R ama_m, R ama_c, R apb_m, R apb_c,
+                                      R amb_m, R amb_c, const R* vbA, const R* bB, const R* vaB,
+                                      const R* bA) {
+  const R apa = max_r(apa_m, apa_c), ama = max_r(ama_m, ama_c);
+  const R apb = max_r(apb_m, apb_c), amb = max_r(amb_m, amb_c);
+  R vW, vE, bW, bE, vS, vN, bS, bN;
+  edge_pair<LIM, R>(vbA[0], vbA[1], vbA[2], vbA[3], vW, vE);
+  edge_pair<LIM, R>(bB[0], bB[1], bB[2], bB[3], bW, bE);
+  edge_pair<LIM, R>(vaB[0], vaB[1], vaB[2], vaB[3], vS, vN);
+  edge_pair<LIM, R>(bA[0], bA[1], bA[2], bA[3], bS, bN);
+  return uct<R>(apa, ama, vW, bW, vE, bE, apb, amb, vS, bS, vN, bN);
+}
+
+// UCT-HLLD edge EMF from its inputs: om, d^L, d^R of the two a-faces (below
+// the edge along B, then the cell's own) and of the two b-faces, averaged;
+// the reconstructed values as for emf_core.
+template <int LIM, class R>
+__device__ __forceinline__ R emf_core_hlld(R oma_m, R oma_c, R dla_m, R dla_c, R dra_m, R dra_c,
+                                           R omb_m, R omb_c, R dlb_m, R dlb_c, R drb_m, R drb_c,
+                                           const R* vbA, const R* bB, const R* vaB,
+                                           const R* bA) {
+  const R aa = R(0.5) * (oma_m + oma_c), dla = R(0.5) * (dla_m + dla_c);
+  const R dra = R(0.5) * (dra_m + dra_c);
+  const R ab = R(0.5) * (omb_m + omb_c), dlb = R(0.5) * (dlb_m + dlb_c);
+  const R drb = R(0.5) * (drb_m + drb_c);
+  R vW, vE, bW, bE, vS, vN, bS, bN;
+  edge_pair<LIM, R>(vbA[0], vbA[1], vbA[2], vbA[3], vW, vE);
+  edge_pair<LIM, R>(bB[0], bB[1], bB[2], bB[3], bW, bE);
+  edge_pair<LIM, R>(vaB[0], vaB[1], vaB[2], vaB[3], vS, vN);
+  edge_pair<LIM, R>(bA[0], bA[1], bA[2], bA[3], bS, bN);
+  return uct_hlld<R>(aa, dla, dra, vW, bW, vE, bE, ab, dlb, drb, vS, bS, vN, bN);
+}
+
 }  // namespace mhd

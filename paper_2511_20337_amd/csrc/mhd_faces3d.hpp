@@ -30,6 +30,7 @@
 //    edge inputs stored like any other (the same bits to the same place),
 //    which keeps every path through a plane alike. Only the new state, which
 //    may be updated in place, is written by its owner alone.
+#pragma once
 #include "mhd_device.hpp"
 #include "mhd_grid.hpp"
 #include "mhd_kernels.hpp"
@@ -186,36 +187,6 @@ __device__ __forceinline__ void march_recon(const R* lds, const int* o, const in
     for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + slot[q] * kMarchQ];
     plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
   }
-}
-
-// The stages' combinations of k_update with u the state L was formed at and
-// u0 the state at the start of the step.
-__device__ __forceinline__ double rk_combine(int stage, double u, double u0, double h, double L) {
-  if (stage == 0) return L;
-  if (stage == 1) return u + h * L;
-  if (stage == 4) return (3.0 * u0 + (u + h * L)) / 4.0;
-  if (stage == 5) return (u0 + 2.0 * (u + h * L)) / 3.0;
-  return 0.5 * (u0 + (u + h * L));
-}
-
-// The same combinations by coefficients, for a stage known at run time without
-// a branch per value: (ca u0 + cb (cu u + h L)) / cd, the quotient by the
-// divisors 1, 2, 4 exact and by 3 corrected to the rounded one.
-struct RkCoef {
-  double cu, h, ca, cb, cc, cd;
-};
-__device__ __forceinline__ RkCoef rk_coef(int stage, double h) {
-  RkCoef c = {1.0, h, 0.0, 1.0, 1.0, 1.0};
-  if (stage == 0) { c.cu = 0.0; c.h = 1.0; }
-  if (stage == 2) { c.ca = 1.0; c.cc = 0.5; c.cd = 2.0; }
-  if (stage == 4) { c.ca = 3.0; c.cc = 0.25; c.cd = 4.0; }
-  if (stage == 5) { c.ca = 1.0; c.cb = 2.0; c.cc = 1.0 / 3.0; c.cd = 3.0; }
-  return c;
-}
-__device__ __forceinline__ double rk_apply(const RkCoef& c, double u, double u0, double L) {
-  const double v = c.ca * u0 + c.cb * (c.cu * u + c.h * L);
-  const double q = v * c.cc;
-  return fma_r(fma_r(-c.cd, q, v), c.cc, q);
 }
 
 // stage: as rk_combine, for the five cell-averaged fields (U0 not null: U

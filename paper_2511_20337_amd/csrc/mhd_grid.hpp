@@ -76,30 +76,6 @@ __device__ __forceinline__ bool prim_at(const double* __restrict__ U, const Geom
   return prim_from_raw<DIM>(load_raw<DIM>(U, g, i, j, k), g.gamma, V);
 }
 
-// Reconstructed face-frame states of the lower D-face of cell (i,j,k):
-// w = (rho, v_n, v_t1, v_t2, B_t1, B_t2, p) from PLM over cells c-2..c+1
-// along D, and the staggered normal field bn (FP64).
-template <int DIM, int D, int LIM>
-__device__ __forceinline__ void face_inputs(const double* __restrict__ U, const Geom& g, int i,
-                                            int j, int k, double* wl, double* wr, double& bn) {
-  constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
-  constexpr int slot[7] = {0, 1 + D, 1 + T1, 1 + T2, 5 + T1, 5 + T2, 4};
-  double V[4][8];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int o = s - 2;
-    prim_at<DIM>(U, g, D == 0 ? wrap(i + o, g.nx) : i, D == 1 ? wrap(j + o, g.ny) : j,
-                 D == 2 ? wrap(k + o, g.nz) : k, V[s]);
-  }
-#pragma unroll
-  for (int q = 0; q < 7; ++q) {
-    const int s = slot[q];
-    const double a = V[0][s], b = V[1][s], c = V[2][s], e = V[3][s];
-    plm_pair<LIM, double>(a, b, c, e, wl[q], wr[q]);
-  }
-  bn = U[(F_BX + D) * g.n + lin(g, i, j, k)];
-}
-
 // Partial derivatives (d slope/d dm, d slope/d dp) of the limited slope.
 template <int LIM>
 __device__ __forceinline__ void plm_slope_grad(double dm, double dp, double& s1, double& s2) {
@@ -185,6 +161,36 @@ __device__ __forceinline__ void workgroup_min_store(double v, double* __restrict
     for (int w = 1; w < kBlock / 64; ++w) r = (red[w] < r) ? red[w] : r;
     *out = r;
   }
+}
+
+// The stages' combinations of k_update with u the state L was formed at and
+// u0 the state at the start of the step.
+__device__ __forceinline__ double rk_combine(int stage, double u, double u0, double h, double L) {
+  if (stage == 0) return L;
+  if (stage == 1) return u + h * L;
+  if (stage == 4) return (3.0 * u0 + (u + h * L)) / 4.0;
+  if (stage == 5) return (u0 + 2.0 * (u + h * L)) / 3.0;
+  return 0.5 * (u0 + (u + h * L));
+}
+
+// The same combinations by coefficients, for a stage known at run time without
+// a branch per value: (ca u0 + cb (cu u + h L)) / cd, the quotient by the
+// divisors 1, 2, 4 exact and by 3 corrected to the rounded one.
+struct RkCoef {
+  double cu, h, ca, cb, cc, cd;
+};
+__device__ __forceinline__ RkCoef rk_coef(int stage, double h) {
+  RkCoef c = {1.0, h, 0.0, 1.0, 1.0, 1.0};
+  if (stage == 0) { c.cu = 0.0; c.h = 1.0; }
+  if (stage == 2) { c.ca = 1.0; c.cc = 0.5; c.cd = 2.0; }
+  if (stage == 4) { c.ca = 3.0; c.cc = 0.25; c.cd = 4.0; }
+  if (stage == 5) { c.ca = 1.0; c.cb = 2.0; c.cc = 1.0 / 3.0; c.cd = 3.0; }
+  return c;
+}
+__device__ __forceinline__ double rk_apply(const RkCoef& c, double u, double u0, double L) {
+  const double v = c.ca * u0 + c.cb * (c.cu * u + c.h * L);
+  const double q = v * c.cc;
+  return fma_r(fma_r(-c.cd, q, v), c.cc, q);
 }
 
 }  // namespace mhd

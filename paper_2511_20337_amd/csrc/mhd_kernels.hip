@@ -1,25 +1,24 @@
 // HIP kernels of the ideal-MHD step for gfx950, and their launchers.
 //
-// One stage of the SSP-RK2 step is three launches:
-//   k_faces_march — 3D: 64 x 4 columns of cells marching along z, with the
-//                   primitives of three planes and a cross halo in LDS; per
-//                   cell its lower x/y/z faces: PLM, HLL/HLLD; writes the
-//                   face fluxes and the alpha+-, HLL-weighted velocities the
-//                   EMF needs (k_faces_tiled does the same on 2D tiles);
-//   k_emf         — per cell, the upwind CT EMF on its lower edges;
-//   k_update      — per cell, flux divergence of the cell fields, -curl E of
-//                   the face fields, and the RK combination (or the bare RHS).
-// The CFL time step is a per-cell minimum reduced with wave64 shuffles and a
-// block LDS step into per-block partials, then one finishing block; in the 3D
-// step the first stage's face kernel computes those partials itself.
+// One stage of a PLM step is three launches in 3D (the z-marching face kernel
+// of mhd_faces3d.hpp, which finishes the cell-averaged fields; k_emf_march, per
+// cell the upwind CT EMF on its lower edges; the update of the staggered field)
+// and one in 2D (mhd_stage2d.hpp). WENO-Z stages are k_prim_weno, k_faces_weno, the
+// EMFs and k_update (2D: k_emf_update_2d), GLM stages k_glm_prim, k_glm_faces
+// and k_glm_update. The CFL time step is a per-cell minimum reduced with wave64
+// shuffles and a block LDS step into per-block partials (by a first kernel of
+// the step itself where it recovers every cell's primitives anyway), then one
+// finishing block.
 //
 // Layout: state and workspace arrays are field-major SoA, x fastest, so a
 // wavefront of 64 consecutive cells reads 512 contiguous bytes per field.
 #include <mutex>
 
 #include "mhd_device.hpp"
+#include "mhd_faces3d.hpp"
 #include "mhd_grid.hpp"
 #include "mhd_kernels.hpp"
+#include "mhd_stage2d.hpp"
 
 namespace mhd {
 
@@ -108,45 +107,6 @@ __device__ __forceinline__ void put_record(double* __restrict__ FW, int64_t n, i
   }
   fw[S_V1 * n] = o.v1;
   fw[S_V2 * n] = o.v2;
-}
-
-// Upwind edge EMF from its inputs: alpha+- of the two a-faces touching the
-// edge (below the edge along B, then the cell's own), of the two b-faces
-// (below along A, then own); the face velocity v_A and the field b_B on the
-// b-faces at A-offsets -2..+1, and v_B and b_A on the a-faces at B-offsets
-// -2..+1, each reconstructed toward the edge.
-template <int LIM, class R>
-__device__ __forceinline__ R emf_core(R apa_m, R apa_c, R ama_m, R ama_c, R apb_m, R apb_c,
-                                      R amb_m, R amb_c, const R* vbA, const R* bB, const R* vaB,
-                                      const R* bA) {
-  const R apa = max_r(apa_m, apa_c), ama = max_r(ama_m, ama_c);
-  const R apb = max_r(apb_m, apb_c), amb = max_r(amb_m, amb_c);
-  R vW, vE, bW, bE, vS, vN, bS, bN;
-  edge_pair<LIM, R>(vbA[0], vbA[1], vbA[2], vbA[3], vW, vE);
-  edge_pair<LIM, R>(bB[0], bB[1], bB[2], bB[3], bW, bE);
-  edge_pair<LIM, R>(vaB[0], vaB[1], vaB[2], vaB[3], vS, vN);
-  edge_pair<LIM, R>(bA[0], bA[1], bA[2], bA[3], bS, bN);
-  return uct<R>(apa, ama, vW, bW, vE, bE, apb, amb, vS, bS, vN, bN);
-}
-
-// UCT-HLLD edge EMF from its inputs: om, d^L, d^R of the two a-faces (below
-// the edge along B, then the cell's own) and of the two b-faces, averaged;
-// the reconstructed values as for emf_core.
-template <int LIM, class R>
-__device__ __forceinline__ R emf_core_hlld(R oma_m, R oma_c, R dla_m, R dla_c, R dra_m, R dra_c,
-                                           R omb_m, R omb_c, R dlb_m, R dlb_c, R drb_m, R drb_c,
-                                           const R* vbA, const R* bB, const R* vaB,
-                                           const R* bA) {
-  const R aa = R(0.5) * (oma_m + oma_c), dla = R(0.5) * (dla_m + dla_c);
-  const R dra = R(0.5) * (dra_m + dra_c);
-  const R ab = R(0.5) * (omb_m + omb_c), dlb = R(0.5) * (dlb_m + dlb_c);
-  const R drb = R(0.5) * (drb_m + drb_c);
-  R vW, vE, bW, bE, vS, vN, bS, bN;
-  edge_pair<LIM, R>(vbA[0], vbA[1], vbA[2], vbA[3], vW, vE);
-  edge_pair<LIM, R>(bB[0], bB[1], bB[2], bB[3], bW, bE);
-  edge_pair<LIM, R>(vaB[0], vaB[1], vaB[2], vaB[3], vS, vN);
-  edge_pair<LIM, R>(bA[0], bA[1], bA[2], bA[3], bS, bN);
-  return uct_hlld<R>(aa, dla, dra, vW, bW, vE, bE, ab, dlb, drb, vS, bS, vN, bN);
 }
 
 // Edge EMF of component C at cell (i,j,k): the edge at the lower A- and
@@ -432,34 +392,16 @@ __global__ __launch_bounds__(RowTile::NT) void k_update(const double* __restrict
 // the row above and of the column to the right, all into LDS behind one
 // barrier; then each cell of the grid is updated as k_update<2> does it
 // (bitwise equal), and its own E_z is stored for the adjoint's records.
-// cflp != nullptr (first stage of a step whose face kernel left npart CFL
-// partials): every workgroup reduces the partials itself to the minimum
-// k_cfl_final forms (a minimum is exact in any order), dt = cfl * min, and
-// workgroup 0 writes it to *dt_out; for small grids this replaces the
-// k_cfl_final launch.
+// (WENO-Z stages, and the adjoint's, which keep their records.)
 template <int LIM, int STAGE, class R, int EM>
 __global__ __launch_bounds__(RowTile::NT) void k_emf_update_2d(const double* __restrict__ U,
                                                                const double* U0, double* out,
                                                                const double* __restrict__ FW,
                                                                double* __restrict__ EW, Geom g,
                                                                TileGrid tg, double dt,
-                                                               const double* __restrict__ dtp,
-                                                               const double* __restrict__ cflp,
-                                                               int npart, double cfl,
-                                                               double* __restrict__ dt_out) {
+                                                               const double* __restrict__ dtp) {
   constexpr int TX = RowTile::TX, TY = RowTile::TY, SX = TX + 1;
   __shared__ R ezs[(TY + 1) * SX];
-  __shared__ double red[RowTile::NT / 64];
-  if (cflp) {
-    double m = __builtin_inf();
-    for (int b = (int)threadIdx.x; b < npart; b += RowTile::NT) m = (cflp[b] < m) ? cflp[b] : m;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const double o = __shfl_xor(m, off, 64);
-      m = (o < m) ? o : m;
-    }
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  }
   const unsigned t = (sizeof(R) == 4) ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
   const int i0 = (int)(t % (unsigned)tg.ntx) * TX;
   const int j0 = (int)(t / (unsigned)tg.ntx) * TY;
@@ -480,18 +422,7 @@ __global__ __launch_bounds__(RowTile::NT) void k_emf_update_2d(const double* __r
     ezs[hy * SX + hx] = emf_comp<2, LIM, R, EM>(U, FW, g, iw, jw, 0, lin(g, iw, jw, 0));
   }
   __syncthreads();
-  double h;
-  if (STAGE == 0) {
-    h = 0.0;
-  } else if (cflp) {
-    double m = red[0];
-#pragma unroll
-    for (int w = 1; w < RowTile::NT / 64; ++w) m = (red[w] < m) ? red[w] : m;
-    h = cfl * m;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *dt_out = h;
-  } else {
-    h = dtp ? *dtp : dt;
-  }
+  const double h = (STAGE == 0) ? 0.0 : (dtp ? *dtp : dt);
   if (!inside) return;
   const int64_t c = lin(g, i, j, 0);
   const int64_t xp = lin(g, wrap(i + 1, g.nx), j, 0);
@@ -703,18 +634,14 @@ __device__ __forceinline__ void tile_face(const R (*sp)[Tile<DIM>::NPRIM], R bn,
 // ---------------------------------------------------------------------------
 // Face kernel: primitives of the tile and its cross halo are recovered once
 // (in FP64) into LDS, held in the reconstruction precision R, then each
-// thread solves the lower x/y(/z) faces of its cell. cflp != nullptr: also
-// the CFL bound of the state over the tile's own cells (the core, each cell
-// the own cell of exactly one tile) into cflp[blockIdx.x]; k_cfl_final
-// finishes it.
+// thread solves the lower x- and y-face of its cell. The adjoint's 2D records;
+// the steps run k_stage_2d.
 template <int DIM, int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(Tile<DIM>::NCORE) void k_faces_tiled(const double* __restrict__ U,
                                                         double* __restrict__ FW, Geom g,
-                                                        TileGrid tg, int* __restrict__ flag,
-                                                        double* __restrict__ cflp) {
+                                                        TileGrid tg, int* __restrict__ flag) {
   static_assert(DIM == 2, "the 3D grid uses k_faces_march");
   using T = Tile<DIM>;
-  static_assert(T::NCORE == kBlock, "workgroup_min_store reduces over kBlock threads");
   __shared__ R sp[8][T::NPRIM];
   int i0, j0, k0;
   tile_origin<DIM>(tg, blockIdx.x, i0, j0, k0);
@@ -730,7 +657,6 @@ __global__ __launch_bounds__(Tile<DIM>::NCORE) void k_faces_tiled(const double* 
 #pragma unroll
   for (int d = 0; d < DIM; ++d) bn[d] = (R)U[(F_BX + d) * g.n + c];
   bool bad = false;
-  double cmin = __builtin_inf();  // CFL bound of this thread's own cell
   for (int e = threadIdx.x; e < T::NPRIM; e += T::NCORE) {
     int x, y, z;
     pslot_pos<DIM>(e, x, y, z);
@@ -739,8 +665,6 @@ __global__ __launch_bounds__(Tile<DIM>::NCORE) void k_faces_tiled(const double* 
                          wrap_any(k0 + z, g.nz), V);
 #pragma unroll
     for (int q = 0; q < 8; ++q) sp[q][e] = (R)V[q];
-    // the core comes first, thread t's first entry is its own cell
-    if (cflp && inside && e == (int)threadIdx.x) cmin = cfl_bound<DIM>(g, V, cmin);
   }
   if (bad) atomicOr(flag, 1);
   __syncthreads();
@@ -749,7 +673,6 @@ __global__ __launch_bounds__(Tile<DIM>::NCORE) void k_faces_tiled(const double* 
     tile_face<DIM, 1, LIM, RS, R, EM>(sp, bn[1], FW, g, x, y, z, c);
     if (DIM == 3) tile_face<DIM, 2, LIM, RS, R, EM>(sp, bn[DIM - 1], FW, g, x, y, z, c);
   }
-  if (cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
 }
 
 // Cell of this thread when each workgroup of kBlock threads takes kBlock
@@ -845,10 +768,6 @@ __global__ __launch_bounds__(kBlock) void k_faces_weno(const double* __restrict_
   weno_face<DIM, 1, RS, EM>(PW, U, FW, g, i, j, k, c);
   if (DIM == 3) weno_face<DIM, 2, RS, EM>(PW, U, FW, g, i, j, k, c);
 }
-
-// Most CFL partials (2D tiles) that every workgroup of the first stage's
-// update reduces itself instead of a k_cfl_final launch (1024: KH 512^2).
-constexpr unsigned kUpdateCflMax = 1024;
 
 // CFL: per-cell min over directions of dx_d / (|v_d| + c_f,d); grid-stride,
 // wave64 shuffle + LDS reduction to one partial per block.
@@ -1208,14 +1127,7 @@ hipError_t stage_impl(const StageArgs& a) {
     const TileGrid tg = tile_grid<Tile<DIM>>(a.g);
     MHD_TIMED(a, K_FACES,
               hipLaunchKernelGGL((k_faces_tiled<DIM, LIM, RS, R, EM>), dim3(tg.ntiles),
-                                 dim3(Tile<DIM>::NCORE), 0, a.stream, a.U, a.FW, a.g, tg, a.flag,
-                                 a.cfl_partial));
-    // dt of the state U before the update reads it: for a few partials the
-    // update's workgroups reduce them themselves, else k_cfl_final
-    if (a.cfl_partial && tg.ntiles > kUpdateCflMax)
-      MHD_TIMED(a, K_CFL_FINAL,
-                hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, a.cfl_partial,
-                                   (int)tg.ntiles, a.cfl, a.dt_out));
+                                 dim3(Tile<DIM>::NCORE), 0, a.stream, a.U, a.FW, a.g, tg, a.flag));
   }
   if constexpr (DIM == 3) {
     launch_emf_march<ELIM, R, EM>(a);
@@ -1225,10 +1137,6 @@ hipError_t stage_impl(const StageArgs& a) {
                                  a.FW, a.EW, a.g, rg));
   }
   if constexpr (DIM == 2) {
-    // the stage-1 CFL partials of the tiled face kernel, when few
-    const unsigned ntile = tile_grid<Tile<DIM>>(a.g).ntiles;
-    const double* ucfl = (a.cfl_partial && ntile <= kUpdateCflMax) ? a.cfl_partial : nullptr;
-    const int unp = (int)ntile;
     switch (a.stage) {
       case 3:
         break;
@@ -1236,31 +1144,31 @@ hipError_t stage_impl(const StageArgs& a) {
         MHD_TIMED(a, K_UPDATE,
                   hipLaunchKernelGGL((k_emf_update_2d<ELIM, 0, R, EM>), dim3(nb), dim3(RowTile::NT),
                                      0, a.stream, a.U, a.U0, a.out, a.FW, a.EW, a.g, rg, a.dt,
-                                     a.dtp, ucfl, unp, a.cfl, a.dt_out));
+                                     a.dtp));
         break;
       case 1:
         MHD_TIMED(a, K_UPDATE,
                   hipLaunchKernelGGL((k_emf_update_2d<ELIM, 1, R, EM>), dim3(nb), dim3(RowTile::NT),
                                      0, a.stream, a.U, a.U0, a.out, a.FW, a.EW, a.g, rg, a.dt,
-                                     a.dtp, ucfl, unp, a.cfl, a.dt_out));
+                                     a.dtp));
         break;
       case 4:
         MHD_TIMED(a, K_UPDATE,
                   hipLaunchKernelGGL((k_emf_update_2d<ELIM, 4, R, EM>), dim3(nb), dim3(RowTile::NT),
                                      0, a.stream, a.U, a.U0, a.out, a.FW, a.EW, a.g, rg, a.dt,
-                                     a.dtp, ucfl, unp, a.cfl, a.dt_out));
+                                     a.dtp));
         break;
       case 5:
         MHD_TIMED(a, K_UPDATE,
                   hipLaunchKernelGGL((k_emf_update_2d<ELIM, 5, R, EM>), dim3(nb), dim3(RowTile::NT),
                                      0, a.stream, a.U, a.U0, a.out, a.FW, a.EW, a.g, rg, a.dt,
-                                     a.dtp, ucfl, unp, a.cfl, a.dt_out));
+                                     a.dtp));
         break;
       default:
         MHD_TIMED(a, K_UPDATE,
                   hipLaunchKernelGGL((k_emf_update_2d<ELIM, 2, R, EM>), dim3(nb), dim3(RowTile::NT),
                                      0, a.stream, a.U, a.U0, a.out, a.FW, a.EW, a.g, rg, a.dt,
-                                     a.dtp, ucfl, unp, a.cfl, a.dt_out));
+                                     a.dtp));
         break;
     }
     return hipGetLastError();
@@ -1342,15 +1250,15 @@ hipError_t stage_lim(const StageArgs& a) {
   }
   if constexpr (DIM == 3) {
     return stage_plm3d(a);
+  } else if constexpr (EM == 0) {  // the adjoint's records: FP64, the HLL average
+    if (mixed) return hipErrorInvalidValue;
+    if (a.limiter == 0)
+      return a.riemann == 0 ? stage_impl<DIM, 0, 0, double, 0>(a)
+                            : stage_impl<DIM, 0, 1, double, 0>(a);
+    return a.riemann == 0 ? stage_impl<DIM, 1, 0, double, 0>(a)
+                          : stage_impl<DIM, 1, 1, double, 0>(a);
   } else {
-    if (a.limiter == 0) {
-      if (a.riemann == 0)
-        return mixed ? stage_impl<DIM, 0, 0, float, EM>(a) : stage_impl<DIM, 0, 0, double, EM>(a);
-      return mixed ? stage_impl<DIM, 0, 1, float, EM>(a) : stage_impl<DIM, 0, 1, double, EM>(a);
-    }
-    if (a.riemann == 0)
-      return mixed ? stage_impl<DIM, 1, 0, float, EM>(a) : stage_impl<DIM, 1, 0, double, EM>(a);
-    return mixed ? stage_impl<DIM, 1, 1, float, EM>(a) : stage_impl<DIM, 1, 1, double, EM>(a);
+    return hipErrorInvalidValue;
   }
 }
 
@@ -1358,7 +1266,6 @@ hipError_t stage_lim(const StageArgs& a) {
 
 size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm) {
   if (glm || limiter == 2) return (size_t)((g.n + kBlock - 1) / kBlock);
-  if (g.nz == 1) return tile_grid<Tile<2>>(g).ntiles;  // 2D (3D grids have nz >= 4)
   return march_grid(g).nblocks;
 }
 
@@ -1378,7 +1285,33 @@ hipError_t launch_glm_cfl(const CflArgs& a, double* PW) {
   return hipGetLastError();
 }
 
+// 2D PLM stage (a.records false): one kernel. Where the time step is the CFL
+// bound of U, its partials come from the stage that wrote U or a pass over it;
+// the stage's workgroups reduce up to kInlineCfl2d of them themselves on grids
+// of about as many tiles, else k_cfl_final does it once.
+hipError_t stage_plm2d(const StageArgs& a) {
+  const double* cflp = a.cfl_prev;
+  int np = a.ncfl;
+  if (a.cfl_partial && !cflp) {
+    const int64_t need = (a.g.n + kBlock - 1) / kBlock;
+    np = (int)(need < kInlineCfl2d ? need : kInlineCfl2d);
+    cflp = a.cfl_partial;
+    MHD_TIMED(a, K_CFL,
+              hipLaunchKernelGGL((k_cfl<2>), dim3(np), dim3(kBlock), 0, a.stream, a.U, a.g,
+                                 a.cfl_partial, a.flag));
+  }
+  if (cflp && (np > kInlineCfl2d || stage_2d_tiles(a.g, a.precision, a.emf) > 2 * kInlineCfl2d)) {
+    MHD_TIMED(a, K_CFL_FINAL,
+              hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, cflp, np, a.cfl,
+                                 a.dt_out));
+    cflp = nullptr;
+  }
+  MHD_TIMED(a, K_FACES, launch_stage_2d(a, cflp, np));
+  return hipGetLastError();
+}
+
 hipError_t launch_stage(const StageArgs& a) {
+  if (a.dim == 2 && !a.glm && a.limiter != 2 && !a.records) return stage_plm2d(a);
   if (a.glm) return (a.dim == 3) ? glm_stage_lim<3>(a) : glm_stage_lim<2>(a);
   if (a.emf == 1) return (a.dim == 3) ? stage_lim<3, 1>(a) : stage_lim<2, 1>(a);
   return (a.dim == 3) ? stage_lim<3, 0>(a) : stage_lim<2, 0>(a);

@@ -1,0 +1,317 @@
+// 2D PLM stage in one kernel: a workgroup recovers the primitives of its tile
+// of W x H cells and two cells around it, solves every face that the tile's
+// flux differences and corner EMFs read, forms E_z at the tile's corners and
+// updates its cells, all through LDS.
+//
+// What bounds it: on small grids the latency of this chain (the launches it
+// replaces cost more), on large ones the instruction count. Measured against
+// the two kernels per stage it replaces (tiled faces with 9 stored values each,
+// EMF and update): 128^2 30.5 -> 15.2 us a step, KH 512^2 72.8 -> 60 us, 1500 x
+// 1001 mixed with UCT-HLLD 341 -> 193 us. Choices:
+//  - The faces are one list, x-faces then y-faces, dealt to the threads in
+//    turn, so that the two extra rows and columns do not leave waves idle; a
+//    lane's direction is two LDS offsets and a few selects.
+//  - Large grids: 32 x 8 cells, 512 threads: 720 faces are 12 waves' work for 8
+//    waves, and two workgroups fit a CU (16 waves, four per SIMD at 128
+//    VGPRs); KH 512^2 with 256 threads 36.6 us a launch against 34.2, 384: 47.6,
+//    32 x 16 cells and 1024 threads: 34.9, 8 x 8 cells: 43.7. Small ones: 8 x 8 cells, 216 faces for 256 threads, one each: the
+//    shortest chain, and four times the workgroups.
+//  - The time step of the CFL bound is reduced from its partials by every
+//    workgroup itself (a minimum is exact in any order), and between the steps
+//    of one run the stage that writes a state leaves its partials, which saves
+//    the pass over U (128^2: 17.0 -> 15.2 us a step).
+#pragma once
+#include "mhd_device.hpp"
+#include "mhd_grid.hpp"
+#include "mhd_kernels.hpp"
+
+namespace mhd {
+
+namespace {
+
+template <int W_, int H_, int NT_>
+struct Tile2 {
+  static constexpr int W = W_, H = H_, NT = NT_;
+  static constexpr int PW = W + 4, NP = PW * (H + 4);         // cells recovered
+  static constexpr int NX = (W + 1) * (H + 4);                // x-faces solved
+  static constexpr int NF = NX + (W + 4) * (H + 1);           // and y-faces
+  static constexpr int FX = (W + 1) * H, FN = FX + W * (H + 1);  // those with fluxes
+  static constexpr int NC = (W + 1) * (H + 1);                // corners
+};
+
+template <class R, class T, int EM>
+struct Lds2 {
+  R v[10][T::NP];          // the eight primitives, then b_x and b_y
+  R fl[6][T::FN];          // fluxes of rho, m_x, m_y, m_z, E, B_z
+  R ed[EM == 1 ? 4 : 3][T::NF];  // alpha+-, (or om, d^L, d^R,) the EMF's velocity
+  R ez[T::NC];
+  double red[T::NT / 64];
+};
+
+// i in [-2, n + W + 1] to its periodic image (n may be smaller than a tile)
+__device__ __forceinline__ int wrap_near(int i, int n) {
+  if (i < 0) return i + n;
+  if (i < n) return i;
+  i -= n;
+  return (i < n) ? i : i % n;
+}
+
+// stage: as rk_coef. cflp != nullptr: dt = cfl times the minimum of the npart
+// partials, written to *dt_out by workgroup 0; else *dtp or dt. cfl_next !=
+// nullptr (the last stage of a step that another follows; out then is neither
+// U nor U0, whose values above the tile are read): also the CFL bound of the
+// new state over the tile into cfl_next[blockIdx.x].
+template <class T, int LIM, int RS, class R, int EM>
+__global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(T::NT == 512 ? 4 : 2)))
+void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geom g, int ntx,
+                int stage, double dt, const double* __restrict__ dtp,
+                const double* __restrict__ cflp, int npart, double cfl,
+                double* __restrict__ dt_out, double* __restrict__ cfl_next,
+                int* __restrict__ flag) {
+  constexpr int W = T::W, H = T::H, NT = T::NT, PW = T::PW, NP = T::NP, NX = T::NX, NF = T::NF;
+  __shared__ Lds2<R, T, EM> L;
+  const int t = (int)threadIdx.x;
+  const int i0 = (int)(blockIdx.x % (unsigned)ntx) * W, j0 = (int)(blockIdx.x / (unsigned)ntx) * H;
+  const int64_t n = g.n;
+  bool bad = false;
+  for (int e = t; e < NP; e += NT) {
+    const int i = wrap_near(i0 + e % PW - 2, g.nx), j = wrap_near(j0 + e / PW - 2, g.ny);
+    const RawCell raw = load_raw<2>(U, g, i, j, 0);
+    double V[8];
+    bad |= !prim_from_raw<2>(raw, g.gamma, V);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) L.v[q][e] = (R)V[q];
+    L.v[8][e] = (R)raw.u[5];
+    L.v[9][e] = (R)raw.u[6];
+  }
+  if (cflp) {
+    double m = __builtin_inf();
+    for (int b = t; b < npart; b += NT) m = (cflp[b] < m) ? cflp[b] : m;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const double o = __shfl_xor(m, off, 64);
+      m = (o < m) ? o : m;
+    }
+    if ((t & 63) == 0) L.red[t >> 6] = m;
+  }
+  if (bad) atomicOr(flag, 1);
+  __syncthreads();
+  const R* v = &L.v[0][0];
+  for (int f = t; f < NF; f += NT) {
+    const bool yf = f >= NX;
+    // the face's place: column and row of its cell in the list's rectangle
+    const int q0 = yf ? f - NX : f, w0 = yf ? W + 4 : W + 1;
+    const int fr = q0 / w0, fc = q0 - fr * w0;
+    const int o = fr * PW + fc, st = yf ? PW : 1;  // first stencil cell, step
+    // slots of the x frame, plus 1 at (v_n, v_t1, B_t1) and minus 2 at
+    // (v_t2, B_t2) for a y-face
+    constexpr int slot[7] = {0, 1, 2, 3, 6, 7, 4}, kind[7] = {0, 1, 1, 2, 1, 2, 0};
+    const int ok[3] = {o, o + (yf ? NP : 0), o - (yf ? 2 * NP : 0)};
+    R wl[7], wr[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) {
+      const R* p = v + ok[kind[q]] + slot[q] * NP;
+      plm_pair<LIM, R>(p[0], p[st], p[2 * st], p[3 * st], wl[q], wr[q]);
+    }
+    const R bn = v[o + 2 * st + (yf ? 9 : 8) * NP];
+    RiemannOut<R> r;
+    riemann<RS, R, EM>((R)g.gamma, wl, wr, bn, r);
+    if (EM == 1) {
+      L.ed[0][f] = r.om;
+      L.ed[1][f] = r.dl;
+      L.ed[2][f] = r.dr;
+    } else {
+      L.ed[0][f] = r.ap;
+      L.ed[1][f] = r.am;
+    }
+    L.ed[EM == 1 ? 3 : 2][f] = yf ? r.v2 : r.v1;  // v_x on y-faces, v_y on x-faces
+    const int fi = yf ? T::FX + fr * W + fc - 2 : (fr - 2) * (W + 1) + fc;
+    if (yf ? (fc >= 2 && fc < W + 2) : (fr >= 2 && fr < H + 2)) {
+      L.fl[0][fi] = r.f[0];
+      L.fl[1][fi] = yf ? r.f[3] : r.f[1];
+      L.fl[2][fi] = yf ? r.f[1] : r.f[2];
+      L.fl[3][fi] = yf ? r.f[2] : r.f[3];
+      L.fl[4][fi] = r.f[6];
+      L.fl[5][fi] = yf ? r.f[4] : r.f[5];
+    }
+  }
+  __syncthreads();
+  // own cell (the first W * H threads; past the grid its periodic image, which
+  // another tile owns); its state is loaded ahead of the EMFs
+  const int x = t % W, y = t / W;
+  const bool cell = t < W * H;
+  const bool own = cell && i0 + x < g.nx && j0 + y < g.ny;
+  const bool used = own || (cell && cfl_next);
+  const int64_t c =
+      used ? (int64_t)wrap_near(j0 + y, g.ny) * g.nx + wrap_near(i0 + x, g.nx) : 0;
+  double u[8], u0[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    u[q] = used ? U[q * n + c] : 0.0;
+    u0[q] = used ? U0[q * n + c] : 0.0;
+  }
+  // cfl_next: the faces above the tile, one each for the next H + W threads
+  static_assert(T::NT >= W * H + W + H, "a thread for each face above the tile");
+  const int ab = t - W * H;  // 0 .. H - 1: b_x at column W; H .. H + W - 1: b_y at row H
+  const bool above = cfl_next && ab >= 0 && ab < H + W;
+  double ua = 0.0, ua0 = 0.0;
+  if (above) {
+    const int64_t ca = (ab < H) ? (int64_t)wrap_near(j0 + ab, g.ny) * g.nx + wrap_near(i0 + W, g.nx)
+                                : (int64_t)wrap_near(j0 + H, g.ny) * g.nx + wrap_near(i0 + ab - H, g.nx);
+    const int64_t fo = (ab < H ? F_BX : F_BY) * n + ca;
+    ua = U[fo];
+    ua0 = U0[fo];
+  }
+  for (int e = t; e < T::NC; e += NT) {
+    const int cj = e / (W + 1), ci = e - cj * (W + 1);
+    const int xf = (cj + 2) * (W + 1) + ci;         // the x-face above the corner
+    const int yf = NX + cj * (W + 4) + ci + 2;      // the y-face to its right
+    constexpr int VS = EM == 1 ? 3 : 2;
+    R wv[4], wb[4], sv[4], sb[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      wv[s] = L.ed[VS][yf - 2 + s];
+      wb[s] = L.v[9][(cj + 2) * PW + ci + s];
+      sv[s] = L.ed[VS][xf + (s - 2) * (W + 1)];
+      sb[s] = L.v[8][(cj + s) * PW + ci + 2];
+    }
+    const int xm = xf - (W + 1), ym = yf - 1;
+    if constexpr (EM == 1)
+      L.ez[e] = emf_core_hlld<LIM, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf],
+                                      L.ed[2][xm], L.ed[2][xf], L.ed[0][ym], L.ed[0][yf],
+                                      L.ed[1][ym], L.ed[1][yf], L.ed[2][ym], L.ed[2][yf], wv, wb,
+                                      sv, sb);
+    else
+      L.ez[e] = emf_core<LIM, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf], L.ed[0][ym],
+                                 L.ed[0][yf], L.ed[1][ym], L.ed[1][yf], wv, wb, sv, sb);
+  }
+  __syncthreads();
+  double h = 0.0;
+  if (cflp) {
+    double m = L.red[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
+    h = cfl * m;
+    if (blockIdx.x == 0 && t == 0) *dt_out = h;
+  } else if (stage != 0) {
+    h = dtp ? *dtp : dt;
+  }
+  const RkCoef rk = rk_coef(stage, h);
+  const double idx = 1.0 / g.dx, idy = 1.0 / g.dy;
+  double v1[8];
+  if (used) {
+    const int fx = y * (W + 1) + x, fy = T::FX + y * W + x, ec = y * (W + 1) + x;
+    double Lq[8];
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+      Lq[q == 5 ? 7 : q] = -(((double)L.fl[q][fx + 1] - (double)L.fl[q][fx]) * idx +
+                             ((double)L.fl[q][fy + W] - (double)L.fl[q][fy]) * idy);
+    const double e0 = (double)L.ez[ec];
+    Lq[5] = -(((double)L.ez[ec + W + 1] - e0) * idy);
+    Lq[6] = ((double)L.ez[ec + 1] - e0) * idx;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v1[q] = rk_apply(rk, u[q], u0[q], Lq[q]);
+    if (own) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) out[q * n + c] = v1[q];
+    }
+  }
+  if (!cfl_next) return;
+  // the new staggered field, in the place of the primitives
+  static_assert(sizeof(double) * (T::FX + W * (H + 1)) <= sizeof(R) * 8 * NP, "it fits there");
+  double* const nbx = reinterpret_cast<double*>(&L.v[0][0]);
+  double* const nby = nbx + T::FX;
+  if (used) {
+    nbx[y * (W + 1) + x] = v1[5];
+    nby[y * W + x] = v1[6];
+  }
+  if (above) {
+    if (ab < H) {
+      const int ec = ab * (W + 1) + W;
+      nbx[ec] = rk_apply(rk, ua, ua0, -(((double)L.ez[ec + W + 1] - (double)L.ez[ec]) * idy));
+    } else {
+      const int ec = H * (W + 1) + ab - H;
+      nby[H * W + ab - H] =
+          rk_apply(rk, ua, ua0, ((double)L.ez[ec + 1] - (double)L.ez[ec]) * idx);
+    }
+  }
+  __syncthreads();
+  double m = __builtin_inf();
+  if (own) {
+    RawCell raw;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) raw.u[q] = v1[q];
+    raw.bxp = nbx[y * (W + 1) + x + 1];
+    raw.byp = nby[(y + 1) * W + x];
+    raw.bzp = 0.0;
+    double V[8];
+    prim_from_raw<2>(raw, g.gamma, V);  // (an unphysical cell is the next stage's to report)
+    m = cfl_bound<2>(g, V, m);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(m, off, 64);
+    m = (o < m) ? o : m;
+  }
+  if ((t & 63) == 0) L.red[t >> 6] = m;
+  __syncthreads();
+  if (t == 0) {
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
+    cfl_next[blockIdx.x] = m;
+  }
+}
+
+template <class T, int LIM, int RS, class R, int EM>
+void stage_2d(const StageArgs& a, const double* cflp, int npart) {
+  const int ntx = (a.g.nx + T::W - 1) / T::W, nty = (a.g.ny + T::H - 1) / T::H;
+  hipLaunchKernelGGL((k_stage_2d<T, LIM, RS, R, EM>), dim3((unsigned)ntx * (unsigned)nty),
+                     dim3(T::NT), 0, a.stream, a.U, a.U0 ? a.U0 : a.U, a.out, a.g, ntx, a.stage,
+                     a.dt, a.dtp, cflp, npart, a.cfl, a.dt_out, a.cfl_next, a.flag);
+}
+// FP64 with the UCT-HLLD average keeps four values a face: 28 x 8 cells are
+// what two workgroups of a CU have LDS for.
+using Small2 = Tile2<8, 8, 256>;
+template <class R, int EM>
+using Large2 = Tile2<(EM == 1 && sizeof(R) == 8) ? 28 : 32, 8, 512>;
+
+bool small_tiles(const Geom& g) {
+  return (int64_t)((g.nx + 31) / 32) * ((g.ny + 7) / 8) <= kSmallTiles2d;
+}
+
+template <int LIM, int RS, class R, int EM>
+void stage_2d_tile(const StageArgs& a, const double* cflp, int npart) {
+  if (small_tiles(a.g)) stage_2d<Small2, LIM, RS, R, EM>(a, cflp, npart);
+  else stage_2d<Large2<R, EM>, LIM, RS, R, EM>(a, cflp, npart);
+}
+template <int LIM, int RS>
+void stage_2d_prec(const StageArgs& a, const double* cflp, int npart) {
+  if (a.precision == 1) {
+    if (a.emf == 1) stage_2d_tile<LIM, RS, float, 1>(a, cflp, npart);
+    else stage_2d_tile<LIM, RS, float, 0>(a, cflp, npart);
+  } else {
+    if (a.emf == 1) stage_2d_tile<LIM, RS, double, 1>(a, cflp, npart);
+    else stage_2d_tile<LIM, RS, double, 0>(a, cflp, npart);
+  }
+}
+
+}  // namespace
+
+int stage_2d_tiles(const Geom& g, int precision, int emf) {
+  const int W = small_tiles(g) ? Small2::W : (emf == 1 && precision == 0)
+                                                 ? Large2<double, 1>::W : Large2<double, 0>::W;
+  static_assert(Small2::H == 8 && Large2<double, 1>::H == 8 && Large2<double, 0>::H == 8, "");
+  return ((g.nx + W - 1) / W) * ((g.ny + 7) / 8);
+}
+
+void launch_stage_2d(const StageArgs& a, const double* cflp, int npart) {
+  if (a.limiter == 0) {
+    if (a.riemann == 0) stage_2d_prec<0, 0>(a, cflp, npart);
+    else stage_2d_prec<0, 1>(a, cflp, npart);
+  } else {
+    if (a.riemann == 0) stage_2d_prec<1, 0>(a, cflp, npart);
+    else stage_2d_prec<1, 1>(a, cflp, npart);
+  }
+}
+
+}  // namespace mhd

@@ -32,7 +32,8 @@ DIVB = {"ct": 0, "glm": 1}
 
 # Every symbol include/mhd.h declares.
 SYMBOLS = ("mhd_init", "mhd_destroy", "mhd_workspace_bytes", "mhd_dt", "mhd_dt_device",
-           "mhd_dt_device_noalloc", "mhd_step", "mhd_step_device_dt", "mhd_step_cfl", "mhd_rhs",
+           "mhd_dt_device_noalloc", "mhd_step", "mhd_step_device_dt", "mhd_step_cfl", "mhd_run",
+           "mhd_rhs",
            "mhd_adjoint_step",
            "mhd_adjoint_step_device", "mhd_check",
            "mhd_timing", "mhd_timing_read", "mhd_strerror", "mhd_last_error")
@@ -84,6 +85,7 @@ def lib():
             "mhd_step": ([vp, vp, ctypes.c_double, vp, sz, vp], st),
             "mhd_step_device_dt": ([vp, vp, vp, vp, sz, vp], st),
             "mhd_step_cfl": ([vp, vp, vp, vp, sz, vp], st),
+            "mhd_run": ([vp, vp, ctypes.c_int64, vp, vp, sz, vp], st),
             "mhd_rhs": ([vp, vp, vp, vp, sz, vp], st),
             "mhd_adjoint_step": ([vp, vp, ctypes.c_double, vp, vp, dp, vp, sz, vp], st),
             "mhd_adjoint_step_device": ([vp, vp, ctypes.c_double, vp, vp, vp, vp, sz, vp], st),
@@ -189,6 +191,12 @@ def mhd_step_cfl(ctx, U, dt_dev, ws) -> None:
     rc = lib().mhd_step_cfl(ctx, U.data_ptr(), dt_dev.data_ptr(), ws.data_ptr(), ws.numel(),
                             _stream(U.device))
     _raise(ctx, rc, "mhd_step_cfl")
+
+
+def mhd_run(ctx, U, nsteps: int, dt_dev, ws) -> None:
+    rc = lib().mhd_run(ctx, U.data_ptr(), int(nsteps), dt_dev.data_ptr(), ws.data_ptr(),
+                       ws.numel(), _stream(U.device))
+    _raise(ctx, rc, "mhd_run")
 
 
 def mhd_rhs(ctx, U, L, ws) -> None:
@@ -330,6 +338,6 @@ class Context:
 
     def run(self, U, nsteps: int):
         """nsteps CFL-limited steps, dt computed on the device each step."""
-        for _ in range(nsteps):
-            self.step_cfl(U)
+        if nsteps > 0:
+            mhd_run(self.ctx, self._state(U), nsteps, self.dt_dev, self.ws)
         return U

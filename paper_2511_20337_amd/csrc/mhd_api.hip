@@ -273,21 +273,6 @@ mhd_status run_2d(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void*
 }
 
 mhd_status cfl_to(mhd_ctx* ctx, const double* U, void* ws, double* dt_dev, hipStream_t s) {
-  if (ctx->cfg.divb == MHD_DIVB_GLM) {  // through the GLM primitive kernel
-    mhd::CflArgs a{};
-    a.dim = ctx->cfg.dim;
-    a.g = ctx->g;
-    a.U = U;
-    a.partial = reinterpret_cast<double*>(base(ws) + ctx->off_partial);
-    a.cfl = ctx->cfg.cfl;
-    a.dt_out = dt_dev;
-    a.flag = ws_flag(ws);
-    a.stream = s;
-    a.timer = ctx->timer;
-    hipError_t e = mhd::launch_glm_cfl(a, reinterpret_cast<double*>(base(ws) + ctx->off_pw));
-    if (e != hipSuccess) return device_fail(ctx, e, "cfl");
-    return MHD_OK;
-  }
   mhd::CflArgs a{};
   a.dim = ctx->cfg.dim;
   a.g = ctx->g;
@@ -299,7 +284,7 @@ mhd_status cfl_to(mhd_ctx* ctx, const double* U, void* ws, double* dt_dev, hipSt
   a.flag = ws_flag(ws);
   a.stream = s;
   a.timer = ctx->timer;
-  hipError_t e = mhd::launch_cfl(a);
+  hipError_t e = ctx->cfg.divb == MHD_DIVB_GLM ? mhd::launch_glm_cfl(a) : mhd::launch_cfl(a);
   if (e != hipSuccess) return device_fail(ctx, e, "cfl");
   return MHD_OK;
 }

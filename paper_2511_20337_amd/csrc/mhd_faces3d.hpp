@@ -10,11 +10,16 @@
 // per cell) go to memory, and the five flux divergences end in the new state
 // (or L) directly. A face solved twice gives the same bits both times.
 //
+// With GLM cleaning (nine cell-centred fields, no edge EMFs) this kernel is the
+// whole stage.
+//
 // What bounds it: the instruction count (2250 per cell at 256^3 in FP64, the
 // vector units 71 % busy). Measured against the split it replaces (a face
 // kernel that stored the fluxes, 27 values per cell, and an update that read
 // them back): faces 1.52 -> 1.60 ms, update 0.96 -> 0.43 ms per launch at 256^3
-// in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms. Choices:
+// in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms; with GLM (before:
+// primitives 0.44, faces 1.97 and update 1.32 ms per stage through memory) 1.62
+// ms per stage, the step 7.50 -> 3.40 ms. Choices:
 //  - 32 x 8 columns: the extra faces fit one wave (40 lanes; 64 x 4 needs 68),
 //    the halo is 160 cells a plane (64 x 4: 272), and a ragged nx wastes less.
 //  - LDS holds two planes of the column (by the parity of k - k0; the values a
@@ -43,7 +48,6 @@ struct March {
   static constexpr int TX = 32, TY = 8, NCORE = TX * TY;
   static constexpr int NHX = 4 * TY;           // x halo: columns -2, -1, TX, TX + 1
   static constexpr int NHALO = NHX + 4 * TX;   // then the y halo rows
-  static constexpr int NQ = 8;                 // primitives per cell: V slots 0..7
 };
 static_assert(March::NCORE == kBlock, "one column cell per thread");
 static_assert(March::NHALO <= March::NCORE, "at most one halo cell per thread");
@@ -52,11 +56,11 @@ static_assert(March::TX == 32, "a wave holds two rows");
 
 // One stride for every quantity, core or halo, so that a stencil cell is one
 // offset and its quantities lie at constant distances from it.
-template <class R>
+template <class R, int NQ, int NF>
 struct MarchLds {
-  R v[March::NQ][2 * March::NCORE + March::NHALO];  // core of two planes, halo
-  R fy[5][March::NCORE];  // y-fluxes of rows 1 .. TY (row r at (r - 1) * TX)
-  R fx[5][March::TY];     // x-fluxes at column TX
+  R v[NQ][2 * March::NCORE + March::NHALO];  // core of two planes, halo
+  R fy[NF][March::NCORE];  // y-fluxes of rows 1 .. TY (row r at (r - 1) * TX)
+  R fx[NF][March::TY];     // x-fluxes at column TX
 };
 constexpr int kMarchQ = 2 * March::NCORE + March::NHALO;  // quantity stride
 constexpr int kHaloOff = 2 * March::NCORE;
@@ -127,7 +131,9 @@ __device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t o
   return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
 }
 // Raw values of the cell at offsets p in plane kw; the staggered B_z above
-// from plane kw1 (both wrapped into 0..nz-1).
+// from plane kw1 (both wrapped into 0..nz-1). GLM (EM 2): the nine
+// cell-centred values, psi in bzp.
+template <int EM>
 __device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, const Geom& g,
                                                   int64_t nxy, int kw, int kw1,
                                                   const PlaneOffs& p) {
@@ -136,10 +142,30 @@ __device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, 
   RawCell r;
 #pragma unroll
   for (int q = 0; q < 8; ++q) r.u[q] = ld_at(pl + q * g.n, c);
+  if constexpr (EM == 2) {
+    r.bxp = r.byp = 0.0;
+    r.bzp = ld_at(pl + 8 * g.n, c);
+    return r;
+  }
   r.bxp = ld_at(pl + 5 * g.n, xp);
   r.byp = ld_at(pl + 6 * g.n, yp);
   r.bzp = ld_at(U + 7 * g.n + kw1 * nxy, c);
   return r;
+}
+
+// The primitives of a raw cell (GLM: with psi as the ninth).
+template <int EM>
+__device__ __forceinline__ bool march_prim(const RawCell& r, double gamma, double* W) {
+  if constexpr (EM == 2) {
+    RawCell c = r;  // a mean of two equal faces is the cell's field, exactly
+    c.bxp = r.u[5];
+    c.byp = r.u[6];
+    c.bzp = r.u[7];
+    W[8] = r.bzp;
+    return prim_from_raw<3>(c, gamma, W);
+  } else {
+    return prim_from_raw<3>(r, gamma, W);
+  }
 }
 
 // The edge inputs of a lower D-face of the plane whose records start at fwp
@@ -164,24 +190,49 @@ __device__ __forceinline__ void put_edge(R* __restrict__ fwp, int64_t n, uint32_
   put(S_V2, o.v2);
 }
 
-// Fluxes of (rho, m_x, m_y, m_z, E) through a D-face.
-template <int D, class R>
-__device__ __forceinline__ void cell_fluxes(const RiemannOut<R>& o, R* F) {
+// Solve of a face with normal field bn, or (GLM) the exact interface values of
+// the (B_n, psi) subsystem from the reconstructed wl[7..8] | wr[7..8],
+//   bn = (bn_L + bn_R)/2 - (psi_R - psi_L)/(2 c_h),
+//   psi = (psi_L + psi_R)/2 - c_h (bn_R - bn_L)/2,
+// then the MHD solve with bn; psi and c_h^2 bn are the fluxes of B_n and psi.
+template <int RS, class R, int EM>
+__device__ __forceinline__ void march_solve(R gam, const R* wl, const R* wr, R bn, R ch,
+                                            RiemannOut<R>& o, R& psi, R& fpsi) {
+  if constexpr (EM == 2) {
+    bn = R(0.5) * (wl[7] + wr[7]) - div_r(wr[8] - wl[8], R(2) * ch);
+    psi = R(0.5) * (wl[8] + wr[8]) - R(0.5) * ch * (wr[7] - wl[7]);
+    fpsi = ch * ch * bn;
+    riemann<RS, R, 0>(gam, wl, wr, bn, o);
+  } else {
+    riemann<RS, R, EM>(gam, wl, wr, bn, o);
+  }
+}
+
+// Fluxes of (rho, m_x, m_y, m_z, E), with GLM also of (B_x, B_y, B_z, psi),
+// through a D-face.
+template <int D, int EM, class R>
+__device__ __forceinline__ void cell_fluxes(const RiemannOut<R>& o, R psi, R fpsi, R* F) {
   constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   F[0] = o.f[0];
   F[1 + D] = o.f[1];
   F[1 + T1] = o.f[2];
   F[1 + T2] = o.f[3];
   F[4] = o.f[6];
+  if constexpr (EM == 2) {
+    F[5 + D] = psi;
+    F[5 + T1] = o.f[4];
+    F[5 + T2] = o.f[5];
+    F[8] = fpsi;
+  }
 }
 
 // Reconstructed states of a face from its four stencil cells (offsets o);
 // slot: the quantities of the face frame.
-template <int LIM, class R>
+template <int LIM, int NW, class R>
 __device__ __forceinline__ void march_recon(const R* lds, const int* o, const int* slot, R* wl,
                                             R* wr) {
 #pragma unroll
-  for (int q = 0; q < 7; ++q) {
+  for (int q = 0; q < NW; ++q) {
     R v[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + slot[q] * kMarchQ];
@@ -192,18 +243,22 @@ __device__ __forceinline__ void march_recon(const R* lds, const int* o, const in
 // stage: as rk_combine, for the five cell-averaged fields (U0 not null: U
 // where the stage does not use it); 3: edge inputs only. cflp != nullptr: also
 // the CFL bound of the state over the column and run into cflp[blockIdx.x] (a
-// lane past the grid repeats a cell, which a minimum does not mind).
+// lane past the grid repeats a cell, which a minimum does not mind). EM 2: GLM
+// cleaning, nine cell-centred fields and no edge inputs, c_h = ch0 / dt, psi
+// times decay in a step's last stage; no CFL bound (c_h needs the dt).
 template <int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 3)))
 void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
                    double* __restrict__ FW, Geom g, MarchGrid mg, int stage, double dt,
                    const double* __restrict__ dtp, int* __restrict__ flag,
-                   double* __restrict__ cflp) {
+                   double* __restrict__ cflp, double ch0, double decay) {
   using M = March;
-  // face frames (rho, v_n, v_t1, v_t2, B_t1, B_t2, p)
-  constexpr int xslot[7] = {0, 1, 2, 3, 6, 7, 4}, yslot[7] = {0, 2, 3, 1, 7, 5, 4};
-  constexpr int zslot[7] = {0, 3, 1, 2, 5, 6, 4};
-  __shared__ MarchLds<R> L;
+  constexpr bool GLM = EM == 2;
+  constexpr int NQ = GLM ? 9 : 8, NF = GLM ? 9 : 5, NW = GLM ? 9 : 7;
+  // face frames (rho, v_n, v_t1, v_t2, B_t1, B_t2, p), GLM: and (B_n, psi)
+  constexpr int xslot[9] = {0, 1, 2, 3, 6, 7, 4, 5, 8}, yslot[9] = {0, 2, 3, 1, 7, 5, 4, 6, 8};
+  constexpr int zslot[9] = {0, 3, 1, 2, 5, 6, 4, 7, 8};
+  __shared__ MarchLds<R, NQ, NF> L;
   R* lds = &L.v[0][0];
   const unsigned b = blockIdx.x;
   const int tx = (int)(b % (unsigned)mg.ntx);
@@ -234,66 +289,68 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     const int e = ey ? lane : min(lane - M::TX, M::TY - 1);
     eoff = plane_offs(g, i0 + (ey ? e : M::TX), j0 + (ey ? M::TY : e)).c;
   }
-  const RkCoef rk = rk_coef(stage, (stage == 0 || stage == 3) ? 0.0 : uni(dtp ? *dtp : dt));
+  const double h = (stage == 0 || stage == 3) ? 0.0 : uni(dtp ? *dtp : dt);
+  const RkCoef rk = rk_coef(stage, h);
+  const R ch = GLM ? uni((R)(ch0 / h)) : R(0);
   const double idx = uni(1.0 / g.dx), idy = uni(1.0 / g.dy), idz = uni(1.0 / g.dz);
   bool bad = false;
   double cmin = __builtin_inf();
   // Prologue: plane k0 (core and halo), V_{k0-1} of the own cell in the other
   // core plane, the left state of the first z-face, the raw cell of k0 + 1.
-  R zl[7];
+  R zl[NW];
   double bn[3];  // normal fields of the own cell's lower faces, plane k
   {
     const int km2 = wrap_any(k0 - 2, g.nz), km1 = wrap_any(k0 - 1, g.nz);
     const int kp1 = wrap_any(k0 + 1, g.nz);
-    const RawCell rm2 = load_raw_plane(U, g, nxy, km2, km1, po);
-    const RawCell rm1 = load_raw_plane(U, g, nxy, km1, k0, po);
-    const RawCell rc = load_raw_plane(U, g, nxy, k0, kp1, po);
-    const RawCell rh = load_raw_plane(U, g, nxy, k0, kp1, ph);
-    double Wm2[8], Wm1[8], W[8];
-    bad |= !prim_from_raw<3>(rm2, g.gamma, Wm2);
-    bad |= !prim_from_raw<3>(rm1, g.gamma, Wm1);
-    bad |= !prim_from_raw<3>(rc, g.gamma, W);
+    const RawCell rm2 = load_raw_plane<EM>(U, g, nxy, km2, km1, po);
+    const RawCell rm1 = load_raw_plane<EM>(U, g, nxy, km1, k0, po);
+    const RawCell rc = load_raw_plane<EM>(U, g, nxy, k0, kp1, po);
+    const RawCell rh = load_raw_plane<EM>(U, g, nxy, k0, kp1, ph);
+    double Wm2[9], Wm1[9], W[9];
+    bad |= !march_prim<EM>(rm2, g.gamma, Wm2);
+    bad |= !march_prim<EM>(rm1, g.gamma, Wm1);
+    bad |= !march_prim<EM>(rc, g.gamma, W);
     if (cflp) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
-    for (int q = 0; q < M::NQ; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       lds[q * kMarchQ + M::NCORE + t] = (R)Wm1[q];
       lds[q * kMarchQ + t] = (R)W[q];
     }
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
+    for (int q = 0; q < NW; ++q) {
       const R a = (R)Wm2[zslot[q]], bb = (R)Wm1[zslot[q]], c = (R)W[zslot[q]];
       zl[q] = plm_up<LIM, R>(plm_slope<LIM, R>(bb - a, c - bb), bb);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) bn[d] = rc.u[5 + d];
     if (haloer) {
-      bad |= !prim_from_raw<3>(rh, g.gamma, W);
+      bad |= !march_prim<EM>(rh, g.gamma, W);
 #pragma unroll
-      for (int q = 0; q < M::NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
     }
   }
-  RawCell nxt = load_raw_plane(U, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
+  RawCell nxt = load_raw_plane<EM>(U, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
   __syncthreads();
   int cp = 0;  // core offset of plane k
-  double acc[5];  // minus L of the cell below, but for its upper z-flux
+  double acc[NF];  // minus L of the cell below, but for its upper z-flux
   R* const fw0 = reinterpret_cast<R*>(FW);
   for (int k = k0;; ++k) {
     const int kw = wrap_any(k, g.nz);
     R* const fwp = fw0 + kw * nxy;
-    R wl[7], wr[7];
+    R wl[NW], wr[NW], psi = R(0), fpsi = R(0);
     RiemannOut<R> o;
     // z-face: the own cell of plane k + 1, then the slope of cell k, which
     // gives the right state and the next plane's left state
     double bnn[3];
     {
-      double W[8];
-      bad |= !prim_from_raw<3>(nxt, g.gamma, W);
+      double W[9];
+      bad |= !march_prim<EM>(nxt, g.gamma, W);
       if (cflp && k + 1 < k1) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
       for (int d = 0; d < 3; ++d) bnn[d] = nxt.u[5 + d];
       const int cn = M::NCORE - cp + t;  // own cell in the other core plane: k - 1, then k + 1
 #pragma unroll
-      for (int q = 0; q < 7; ++q) {
+      for (int q = 0; q < NW; ++q) {
         const int sq = zslot[q];
         const R a = lds[cn + sq * kMarchQ];
         const R bb = lds[cp + t + sq * kMarchQ];
@@ -304,32 +361,34 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
         zl[q] = plm_up<LIM, R>(dlt, bb);
       }
 #pragma unroll
-      for (int q = 0; q < M::NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
     }
-    riemann<RS, R, EM>(gam, wl, wr, (R)bn[2], o);
+    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[2], ch, o, psi, fpsi);
     {
-      R F[5];
-      cell_fluxes<2>(o, F);
+      R F[NF];
+      cell_fluxes<2, EM>(o, psi, fpsi, F);
       // the cell below is finished
       const int64_t cb = (int64_t)(k - 1) * nxy;
       if (k > k0 && inside && stage != 3) {
         const uint32_t c = here(po.c);
-        double u[5], u0[5];
+        double u[NF], u0[NF];
 #pragma unroll
-        for (int q = 0; q < 5; ++q) {
+        for (int q = 0; q < NF; ++q) {
           u[q] = ld_at(U + q * n + cb, c);
           u0[q] = ld_at(U0 + q * n + cb, c);
         }
 #pragma unroll
-        for (int q = 0; q < 5; ++q)
-          *reinterpret_cast<double*>(reinterpret_cast<char*>(out + q * n + cb) + c) =
-              rk_apply(rk, u[q], u0[q], -(acc[q] + (double)F[q] * idz));
+        for (int q = 0; q < NF; ++q) {
+          double v = rk_apply(rk, u[q], u0[q], -(acc[q] + (double)F[q] * idz));
+          if (GLM && q == 8) v *= decay;
+          *reinterpret_cast<double*>(reinterpret_cast<char*>(out + q * n + cb) + c) = v;
+        }
       }
       if (k == k1) break;
 #pragma unroll
-      for (int q = 0; q < 5; ++q) acc[q] = -(double)F[q] * idz;
+      for (int q = 0; q < NF; ++q) acc[q] = -(double)F[q] * idz;
     }
-    put_edge<2, EM>(fwp, n, boff, o);
+    if constexpr (!GLM) put_edge<2, EM>(fwp, n, boff, o);
     const int ka = wrap_any(k + 1, g.nz), kb = wrap_any(k + 2, g.nz), kc = wrap_any(k + 3, g.nz);
     // x-face
     {
@@ -337,15 +396,15 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
       int os[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx - 2 + s, yy);
-      march_recon<LIM, R>(lds, os, xslot, wl, wr);
+      march_recon<LIM, NW>(lds, os, xslot, wl, wr);
     }
-    riemann<RS, R, EM>(gam, wl, wr, (R)bn[0], o);
-    put_edge<0, EM>(fwp, n, boff, o);
+    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[0], ch, o, psi, fpsi);
+    if constexpr (!GLM) put_edge<0, EM>(fwp, n, boff, o);
     {
-      R F[5];
-      cell_fluxes<0>(o, F);
+      R F[NF];
+      cell_fluxes<0, EM>(o, psi, fpsi, F);
 #pragma unroll
-      for (int q = 0; q < 5; ++q) {
+      for (int q = 0; q < NF; ++q) {
         const R up = __shfl_down(F[q], 1, 64);  // the upper face, but for the last column
         acc[q] += (x == M::TX - 1) ? -(double)F[q] * idx : ((double)up - (double)F[q]) * idx;
       }
@@ -356,23 +415,24 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
       int os[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx, yy - 2 + s);
-      march_recon<LIM, R>(lds, os, yslot, wl, wr);
+      march_recon<LIM, NW>(lds, os, yslot, wl, wr);
     }
-    riemann<RS, R, EM>(gam, wl, wr, (R)bn[1], o);
-    put_edge<1, EM>(fwp, n, boff, o);
-    R fy[5];
-    cell_fluxes<1>(o, fy);
+    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[1], ch, o, psi, fpsi);
+    if constexpr (!GLM) put_edge<1, EM>(fwp, n, boff, o);
+    R fy[NF];
+    cell_fluxes<1, EM>(o, psi, fpsi, fy);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) acc[q] -= (double)fy[q] * idy;
+    for (int q = 0; q < NF; ++q) acc[q] -= (double)fy[q] * idy;
     // the faces above the column: one wave, in turn
     const bool helper = wave == ((k - k0) & 3);
-    R fe[5];
+    R fe[NF];
     if (helper) {
       const int l = here(lane);
       const bool ey = l < M::TX;
       const int e = ey ? l : min(l - M::TX, M::TY - 1);
-      const double ebn = ld_at(U + (ey ? F_BY : F_BX) * n + kw * nxy, here(eoff));
-      // slots: the x frame's, plus 1 at (v_n, v_t1, B_t1) and minus 2 at
+      const double ebn =
+          GLM ? 0.0 : ld_at(U + (ey ? F_BY : F_BX) * n + kw * nxy, here(eoff));
+      // slots: the x frame's, plus 1 at (v_n, v_t1, B_t1, B_n) and minus 2 at
       // (v_t2, B_t2) for a y-face
       const int up = ey ? kMarchQ : 0, dn = ey ? -2 * kMarchQ : 0;
       int os[3][4];
@@ -382,46 +442,52 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
         os[1][s] = os[0][s] + up;
         os[2][s] = os[0][s] + dn;
       }
-      constexpr int kind[7] = {0, 1, 1, 2, 1, 2, 0};
+      constexpr int kind[9] = {0, 1, 1, 2, 1, 2, 0, 1, 0};
 #pragma unroll
-      for (int q = 0; q < 7; ++q) {
+      for (int q = 0; q < NW; ++q) {
         R v[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) v[s] = lds[os[kind[q]][s] + xslot[q] * kMarchQ];
         plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
       }
-      riemann<RS, R, EM>(gam, wl, wr, (R)ebn, o);
+      march_solve<RS, R, EM>(gam, wl, wr, (R)ebn, ch, o, psi, fpsi);
       fe[0] = o.f[0];
       fe[1] = ey ? o.f[3] : o.f[1];
       fe[2] = ey ? o.f[1] : o.f[2];
       fe[3] = ey ? o.f[2] : o.f[3];
       fe[4] = o.f[6];
+      if constexpr (GLM) {
+        fe[5] = ey ? o.f[5] : psi;
+        fe[6] = ey ? psi : o.f[4];
+        fe[7] = ey ? o.f[4] : o.f[5];
+        fe[8] = fpsi;
+      }
     }
     // the raw halo cell of plane k + 1 and own cell of plane k + 2 (their
     // latency passes at the barriers)
-    const RawCell hr = load_raw_plane(U, g, nxy, ka, kb, ph);
-    nxt = load_raw_plane(U, g, nxy, kb, kc, po);
+    const RawCell hr = load_raw_plane<EM>(U, g, nxy, ka, kb, ph);
+    nxt = load_raw_plane<EM>(U, g, nxy, kb, kc, po);
     __syncthreads();
     if (y > 0) {
 #pragma unroll
-      for (int q = 0; q < 5; ++q) L.fy[q][t - M::TX] = fy[q];
+      for (int q = 0; q < NF; ++q) L.fy[q][t - M::TX] = fy[q];
     }
     if (helper && lane < M::TX + M::TY) {
 #pragma unroll
-      for (int q = 0; q < 5; ++q) {
+      for (int q = 0; q < NF; ++q) {
         if (lane < M::TX) L.fy[q][M::NCORE - M::TX + lane] = fe[q];
         else L.fx[q][lane - M::TX] = fe[q];
       }
     }
     if (haloer) {
-      double W[8];
-      bad |= !prim_from_raw<3>(hr, g.gamma, W);
+      double W[9];
+      bad |= !march_prim<EM>(hr, g.gamma, W);
 #pragma unroll
-      for (int q = 0; q < M::NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
+    for (int q = 0; q < NF; ++q) {
       acc[q] += (double)L.fy[q][t] * idy;
       if (x == M::TX - 1) acc[q] += (double)L.fx[q][y] * idx;
     }
@@ -494,11 +560,13 @@ __global__ __launch_bounds__(kBlock) void k_update_b(const double* __restrict__ 
 template <int LIM, int RS, class R, int EM>
 void faces_impl(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
   hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM>), dim3(mg.nblocks), dim3(kBlock), 0, a.stream,
-                     a.U, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag, a.cfl_partial);
+                     a.U, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag, a.cfl_partial, a.cfl * a.glm_dmin,
+                     (stage == 2 || stage == 5) ? a.glm_decay : 1.0);
 }
 template <int LIM, int RS, class R>
 void faces_em(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
-  if (a.emf == 1) faces_impl<LIM, RS, R, 1>(a, mg, stage, out);
+  if (a.glm) faces_impl<LIM, RS, R, 2>(a, mg, stage, out);
+  else if (a.emf == 1) faces_impl<LIM, RS, R, 1>(a, mg, stage, out);
   else faces_impl<LIM, RS, R, 0>(a, mg, stage, out);
 }
 template <int LIM, int RS>

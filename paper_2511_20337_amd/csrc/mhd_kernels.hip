@@ -832,6 +832,20 @@ __global__ __launch_bounds__(1024) void k_cfl_final(const double* __restrict__ p
 // the damping of psi in the last stage).
 constexpr int kGlmFields = 9;
 
+// Primitives (rho, v_x, v_y, v_z, p, B_x, B_y, B_z, psi) of cell c; false for an
+// unphysical one.
+__device__ __forceinline__ bool glm_prim(const double* __restrict__ U, int64_t n, int64_t c,
+                                         double gamma, double* V) {
+  RawCell r;  // (the mean of two equal faces is the cell's field, exactly)
+#pragma unroll
+  for (int q = 0; q < 8; ++q) r.u[q] = U[q * n + c];
+  r.bxp = r.u[5];
+  r.byp = r.u[6];
+  r.bzp = r.u[7];
+  V[8] = U[8 * n + c];
+  return prim_from_raw<3>(r, gamma, V);
+}
+
 // Primitives (rho, v_x, v_y, v_z, p, B_x, B_y, B_z, psi) of every cell into
 // PW[9][n] (FP64; the field is already cell-centred), the workgroup's CFL
 // partial into cflp[blockIdx.x] (nullable).
@@ -846,19 +860,10 @@ __global__ __launch_bounds__(kBlock) void k_glm_prim(const double* __restrict__ 
   double cmin = __builtin_inf();
   if (inside) {
     const int64_t n = g.n;
-    const double rho = U[c];
-    const double mx = U[n + c], my = U[2 * n + c], mz = U[3 * n + c], en = U[4 * n + c];
-    const double bx = U[5 * n + c], by = U[6 * n + c], bz = U[7 * n + c];
-    const double irho = rcp_r(rho);
-    const double vx = mx * irho, vy = my * irho, vz = mz * irho;
-    const double kin = 0.5 * fma_r(mz, vz, fma_r(my, vy, mx * vx));
-    const double mag = 0.5 * fma_r(bz, bz, fma_r(by, by, bx * bx));
-    const double p = (g.gamma - 1.0) * (en - kin - mag);
-    const double V[9] = {rho, vx, vy, vz, p, bx, by, bz, U[8 * n + c]};
+    double V[9];
+    const bool ok = glm_prim(U, n, c, g.gamma, V);
 #pragma unroll
     for (int q = 0; q < kGlmFields; ++q) PW[q * n + c] = V[q];
-    const bool ok = (rho > 0.0) && (p > 0.0) && __builtin_isfinite(p) &&
-                    __builtin_isfinite(vx) && __builtin_isfinite(vy) && __builtin_isfinite(vz);
     if (!ok) atomicOr(flag, 1);
     if (cflp) cmin = cfl_bound<DIM>(g, V, cmin);
   }
@@ -979,6 +984,23 @@ __global__ __launch_bounds__(kBlock) void k_glm_update(const double* __restrict_
   }
 }
 
+// The CFL bound of a GLM state (nullable flag bits as k_cfl), grid-stride, one
+// partial per block.
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_glm_cfl(const double* __restrict__ U, Geom g,
+                                                    double* __restrict__ partial,
+                                                    int* __restrict__ flag) {
+  double m = __builtin_inf();
+  const int64_t n = g.n;
+  for (int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x; c < n;
+       c += (int64_t)gridDim.x * kBlock) {
+    double V[9];
+    if (!glm_prim(U, n, c, g.gamma, V)) atomicOr(flag, 1);
+    m = cfl_bound<DIM>(g, V, m);
+  }
+  workgroup_min_store(m, partial + blockIdx.x);
+}
+
 template <int DIM, int LIM, int RS, class R>
 hipError_t glm_stage_impl(const StageArgs& a) {
   const unsigned nl = (unsigned)((a.g.n + kBlock - 1) / kBlock);
@@ -1016,14 +1038,16 @@ hipError_t glm_stage_lim(const StageArgs& a) {
     return a.riemann == 0 ? glm_stage_impl<DIM, 2, 0, double>(a)
                           : glm_stage_impl<DIM, 2, 1, double>(a);
   }
-  if (a.limiter == 0) {
+  if constexpr (DIM == 3) return hipErrorInvalidValue;  // stage_glm3d
+  else if (a.limiter == 0) {
     if (a.riemann == 0)
       return mixed ? glm_stage_impl<DIM, 0, 0, float>(a) : glm_stage_impl<DIM, 0, 0, double>(a);
     return mixed ? glm_stage_impl<DIM, 0, 1, float>(a) : glm_stage_impl<DIM, 0, 1, double>(a);
   }
-  if (a.riemann == 0)
+  else if (a.riemann == 0)
     return mixed ? glm_stage_impl<DIM, 1, 0, float>(a) : glm_stage_impl<DIM, 1, 0, double>(a);
-  return mixed ? glm_stage_impl<DIM, 1, 1, float>(a) : glm_stage_impl<DIM, 1, 1, double>(a);
+  else
+    return mixed ? glm_stage_impl<DIM, 1, 1, float>(a) : glm_stage_impl<DIM, 1, 1, double>(a);
 }
 
 
@@ -1269,19 +1293,43 @@ size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm) {
   return march_grid(g).nblocks;
 }
 
-hipError_t launch_glm_cfl(const CflArgs& a, double* PW) {
-  const unsigned nl = (unsigned)((a.g.n + kBlock - 1) / kBlock);
+hipError_t launch_glm_cfl(const CflArgs& a) {
   if (a.dim == 3)
     MHD_TIMED(a, K_CFL,
-              hipLaunchKernelGGL((k_glm_prim<3>), dim3(nl), dim3(kBlock), 0, a.stream, a.U, PW,
-                                 a.g, a.flag, a.partial));
+              hipLaunchKernelGGL((k_glm_cfl<3>), dim3(a.nblocks), dim3(kBlock), 0, a.stream, a.U,
+                                 a.g, a.partial, a.flag));
   else
     MHD_TIMED(a, K_CFL,
-              hipLaunchKernelGGL((k_glm_prim<2>), dim3(nl), dim3(kBlock), 0, a.stream, a.U, PW,
-                                 a.g, a.flag, a.partial));
+              hipLaunchKernelGGL((k_glm_cfl<2>), dim3(a.nblocks), dim3(kBlock), 0, a.stream, a.U,
+                                 a.g, a.partial, a.flag));
   MHD_TIMED(a, K_CFL_FINAL,
-            hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, a.partial, (int)nl,
+            hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, a.partial, a.nblocks,
                                a.cfl, a.dt_out));
+  return hipGetLastError();
+}
+
+// 3D PLM stage with GLM cleaning: the marching face kernel finishes all nine
+// fields. c_h needs the time step, so a CFL step's bound is a pass of its own.
+hipError_t stage_glm3d(const StageArgs& a) {
+  StageArgs f = a;
+  if (a.cfl_partial) {
+    CflArgs c{};
+    c.dim = 3;
+    c.g = a.g;
+    c.U = a.U;
+    c.partial = a.cfl_partial;
+    const int64_t need = (a.g.n + kBlock - 1) / kBlock;
+    c.nblocks = (int)(need < 2048 ? need : 2048);
+    c.cfl = a.cfl;
+    c.dt_out = a.dt_out;
+    c.flag = a.flag;
+    c.stream = a.stream;
+    c.timer = a.timer;
+    const hipError_t e = launch_glm_cfl(c);
+    if (e != hipSuccess) return e;
+    f.cfl_partial = nullptr;
+  }
+  MHD_TIMED(a, K_FACES, launch_faces_march(f, march_grid(a.g), a.stage, a.out));
   return hipGetLastError();
 }
 
@@ -1311,6 +1359,7 @@ hipError_t stage_plm2d(const StageArgs& a) {
 }
 
 hipError_t launch_stage(const StageArgs& a) {
+  if (a.dim == 3 && a.glm && a.limiter != 2) return stage_glm3d(a);
   if (a.dim == 2 && !a.glm && a.limiter != 2 && !a.records) return stage_plm2d(a);
   if (a.glm) return (a.dim == 3) ? glm_stage_lim<3>(a) : glm_stage_lim<2>(a);
   if (a.emf == 1) return (a.dim == 3) ? stage_lim<3, 1>(a) : stage_lim<2, 1>(a);

@@ -92,8 +92,8 @@ hipError_t launch_stage(const StageArgs& a);
 // number of CFL partials the 3D face kernel (WENO-Z, GLM: primitive kernel)
 // writes (one per workgroup)
 size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm);
-// GLM: the CFL time step of U through its primitive kernel (writes PW too)
-hipError_t launch_glm_cfl(const CflArgs& a, double* PW);
+// GLM: the CFL time step of U
+hipError_t launch_glm_cfl(const CflArgs& a);
 hipError_t launch_cfl(const CflArgs& a);
 // 3D PLM face kernel (stage 3: edge inputs only) and the update that follows
 // the EMFs (Lc: the cell fields' L where they are not finished yet, or null).

@@ -50,3 +50,35 @@ def test_columns_and_runs(grid, scheme):
     for q in range(5):
         mag = np.abs(U0[q]).sum() + np.abs(U0[1:4]).sum() * (1 <= q <= 3)
         assert abs(got[q].sum() - U0[q].sum()) <= 1e-12 * mag, q
+
+
+@pytest.mark.parametrize("grid", GRIDS)
+@pytest.mark.parametrize("scheme", ["hlld", "hll_rk3", "mixed"])
+def test_columns_and_runs_glm(grid, scheme):
+    """The same kernel on the nine cell-centred fields of GLM cleaning."""
+    from paper_2511_20337_amd import mhd
+    from tests.test_gpu_glm import rel_err9
+    nx, ny, nz = grid
+    s, U = W.generic_state(3, nx, ny, nz, "minmod" if scheme == "mixed" else "vanleer",
+                           "hll" if scheme == "hll_rk3" else "hlld", seed=nx + nz)
+    s, U0 = W.glm_from_ct(s, U)
+    U0[8] = 0.02 * np.random.default_rng(17).normal(size=U0[8].shape)
+    s = dict(s, integrator="rk3" if scheme == "hll_rk3" else "rk2",
+             precision="mixed" if scheme == "mixed" else "fp64")
+    print("columns and runs, GLM", grid, scheme, flush=True)
+    ctx = mhd.Context(s, "cuda:0")
+    Ua = torch.from_numpy(U0).cuda()
+    Ub, dts = Ua.clone(), []
+    for _ in range(2):
+        dts.append(ctx.dt(Ua))
+        ctx.step(Ua, dts[-1])
+        ctx.step_cfl(Ub)
+        assert ctx.dt_dev.item() == dts[-1]
+        assert torch.equal(Ua, Ub)
+    ctx.check()
+    got = Ua.cpu().numpy()
+    err = rel_err9(got, O.glm_run_dts(O.cfg_from(s), U0, np.array(dts)))
+    assert (err <= (2e-5 if scheme == "mixed" else 1e-12)).all(), err
+    for q in range(8):  # the same flux on both sides of a column's edge
+        mag = np.abs(U0[q]).sum() + np.abs(U0[1:4]).sum() * (1 <= q <= 3)
+        assert abs(got[q].sum() - U0[q].sum()) <= 1e-12 * mag, q

@@ -99,17 +99,6 @@ __device__ __forceinline__ double uni(double v) {
 __device__ __forceinline__ float uni(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
-// The same value, of which the compiler does not know that it is loop
-// invariant: what is derived from it is formed where it is used instead of
-// being carried through the march in registers that the solves need (and an
-// offset is seen as the zero-extended 32 bits that the scalar-base addressing
-// form takes).
-template <class T>
-__device__ __forceinline__ T here(T v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // Byte offsets within a plane of one field (FP64) of the values the primitive
 // recovery of cell (i, j) reads (indices wrapped): the cell, and its upper x
 // and y neighbours (staggered B_x, B_y). The staggered B_z above is the
@@ -125,10 +114,6 @@ __device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j) {
   p.xp = (uint32_t)(jw * g.nx + wrap(iw + 1, g.nx)) * 8u;
   p.yp = (uint32_t)(wrap(jw + 1, g.ny) * g.nx + iw) * 8u;
   return p;
-}
-// The value at byte offset off of the uniform base b.
-__device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t off) {
-  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
 }
 // Raw values of the cell at offsets p in plane kw; the staggered B_z above
 // from plane kw1 (both wrapped into 0..nz-1). GLM (EM 2): the nine

@@ -28,6 +28,21 @@ __device__ __forceinline__ int64_t shifted(const Geom& g, int i, int j, int k, i
   return lin(g, i, j, wrap(k + s, g.nz));
 }
 
+// The same value, of which the compiler does not know that it is: what is
+// derived from it is formed where it is used instead of being hoisted out of a
+// loop, or shared between faces, in registers that the solves need (and an
+// offset is seen as the zero-extended 32 bits that the scalar-base addressing
+// form takes).
+template <class T>
+__device__ __forceinline__ T here(T v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// The value at byte offset off of the uniform base b.
+__device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t off) {
+  return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
+}
 // The stored values primitive recovery at a cell reads: its 8 fields and
 // the staggered field on its three upper faces.
 struct RawCell {

@@ -167,15 +167,14 @@ mhd_status mhd_step_device_dt(mhd_ctx* ctx, double* U, const double* dt_dev, voi
 /* One step of the configured integrator whose dt is the CFL time step of U
  * (as mhd_dt computes it, bit for bit), written to the device double *dt_dev
  * and used by the step; no host synchronisation. The CFL reduction runs
- * inside the first stage's face kernel (in 3D with WENO-Z, its primitive
- * kernel; with GLM, the GLM primitive kernel) instead of as a separate pass
- * over U, except in 2D with WENO-Z, which keeps the separate pass. */
+ * inside a first kernel of the step that recovers the primitives anyway (3D
+ * with CT), else as a pass over U. */
 mhd_status mhd_step_cfl(mhd_ctx* ctx, double* U, double* dt_dev, void* ws, size_t ws_bytes,
                         void* stream);
 
 /* nsteps (>= 0) steps as by mhd_step_cfl, the same states and time steps;
  * *dt_dev holds the last step's dt at the end. No host synchronisation. In 2D
- * with PLM and CT the last stage of a step reduces the CFL bound of the state
+ * the last stage of a step reduces the CFL bound of the state
  * it writes, which the next step then takes, so that the state lies in the
  * workspace after every other of the steps (in U after the last). */
 mhd_status mhd_run(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,

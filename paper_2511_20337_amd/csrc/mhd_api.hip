@@ -174,8 +174,8 @@ mhd::StageArgs stage_args(mhd_ctx* ctx, void* ws, hipStream_t s) {
   return a;
 }
 
-// One SSP-RK2 or SSP-RK3 step. dt_cfl (not for 2D WENO-Z): dt is the CFL step of U,
-// reduced by the stage-1 face kernel and written to dt_cfl, which is also dtp.
+// One SSP-RK2 or SSP-RK3 step. dt_cfl: dt is the CFL step of U, which the first
+// stage reduces and writes to dt_cfl, which is also dtp.
 mhd_status run_step(mhd_ctx* ctx, double* U, double dt, const double* dtp, void* ws,
                     hipStream_t s, double* dt_cfl = nullptr) {
   double* U1 = reinterpret_cast<double*>(base(ws) + ctx->off_u1);
@@ -219,7 +219,7 @@ mhd_status run_step(mhd_ctx* ctx, double* U, double dt, const double* dtp, void*
   return MHD_OK;
 }
 
-// nsteps steps with the 2D PLM stages, dt of each step in *dt_dev. The last
+// nsteps steps with the 2D stages, dt of each step in *dt_dev. The last
 // stage of a step leaves the CFL partials of the state it writes to the next
 // step, which needs the state it reads left alone: the steps alternate between
 // U and a second state, and the last one ends in U. The second state and the
@@ -228,8 +228,10 @@ mhd_status run_2d(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void*
                   hipStream_t s) {
   double* alt = reinterpret_cast<double*>(base(ws) + ctx->off_fw);
   const size_t n = (size_t)ctx->g.n;
-  const int np = mhd::stage_2d_tiles(ctx->g, ctx->cfg.precision, ctx->cfg.emf);
-  double* part[2] = {alt + 8 * n, alt + 8 * n + np};
+  const bool glm = ctx->cfg.divb == MHD_DIVB_GLM;
+  const int np = mhd::stage_2d_tiles(ctx->g, ctx->cfg.limiter, ctx->cfg.emf, ctx->cfg.precision,
+                                     glm);
+  double* part[2] = {alt + (glm ? 9 : 8) * n, alt + (glm ? 9 : 8) * n + np};
   double* U1 = reinterpret_cast<double*>(base(ws) + ctx->off_u1);
   double* U2 = reinterpret_cast<double*>(base(ws) + ctx->off_u2);
   const bool rk3 = ctx->cfg.integrator == MHD_SSP_RK3;
@@ -430,11 +432,7 @@ mhd_status mhd_step_cfl(mhd_ctx* ctx, double* U, double* dt_dev, void* ws, size_
   if (!U || !dt_dev) return MHD_ERR_INVALID;
   if (!ws_ok(ctx, ws, ws_bytes, false)) return MHD_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (ctx->cfg.dim == 3 || ctx->cfg.divb == MHD_DIVB_GLM || ctx->cfg.limiter != MHD_LIM_WENOZ)
-    return run_step(ctx, U, 0.0, dt_dev, ws, s, dt_dev);
-  mhd_status st = cfl_to(ctx, U, ws, dt_dev, s);  // 2D WENO-Z: the separate CFL pass
-  if (st != MHD_OK) return st;
-  return run_step(ctx, U, 0.0, dt_dev, ws, s);
+  return run_step(ctx, U, 0.0, dt_dev, ws, s, dt_dev);
 }
 
 mhd_status mhd_run(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,
@@ -442,7 +440,7 @@ mhd_status mhd_run(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void
   if (!ctx) return MHD_ERR_INVALID;
   if (!U || !dt_dev || nsteps < 0) return MHD_ERR_INVALID;
   if (!ws_ok(ctx, ws, ws_bytes, false)) return MHD_ERR_WORKSPACE;
-  if (ctx->cfg.dim == 2 && ctx->cfg.divb == MHD_DIVB_CT && ctx->cfg.limiter != MHD_LIM_WENOZ)
+  if (ctx->cfg.dim == 2)
     return run_2d(ctx, U, nsteps, dt_dev, ws, static_cast<hipStream_t>(stream));
   for (int64_t k = 0; k < nsteps; ++k) {
     const mhd_status st = mhd_step_cfl(ctx, U, dt_dev, ws, ws_bytes, stream);

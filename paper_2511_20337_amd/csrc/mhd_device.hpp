@@ -465,6 +465,24 @@ __device__ __forceinline__ void riemann(R g, const R* wl, const R* wr, R bn, Rie
   }
 }
 
+// Solve of a face with normal field bn, or (GLM) the exact interface values of
+// the (B_n, psi) subsystem from the reconstructed wl[7..8] | wr[7..8],
+//   bn = (bn_L + bn_R)/2 - (psi_R - psi_L)/(2 c_h),
+//   psi = (psi_L + psi_R)/2 - c_h (bn_R - bn_L)/2,
+// then the MHD solve with bn; psi and c_h^2 bn are the fluxes of B_n and psi.
+template <int RS, class R, int EM>
+__device__ __forceinline__ void face_solve(R gam, const R* wl, const R* wr, R bn, R ch,
+                                            RiemannOut<R>& o, R& psi, R& fpsi) {
+  if constexpr (EM == 2) {
+    bn = R(0.5) * (wl[7] + wr[7]) - div_r(wr[8] - wl[8], R(2) * ch);
+    psi = R(0.5) * (wl[8] + wr[8]) - R(0.5) * ch * (wr[7] - wl[7]);
+    fpsi = ch * ch * bn;
+    riemann<RS, R, 0>(gam, wl, wr, bn, o);
+  } else {
+    riemann<RS, R, EM>(gam, wl, wr, bn, o);
+  }
+}
+
 // Upwind edge EMF for component c with cyclic pair (a, b); the exact value
 // is v_b B_a - v_a B_b. a-bracket: v_a B_b upwinded along a from the two
 // b-faces (W, E) reconstructed toward the edge, with the largest alpha+-

@@ -175,24 +175,6 @@ __device__ __forceinline__ void put_edge(R* __restrict__ fwp, int64_t n, uint32_
   put(S_V2, o.v2);
 }
 
-// Solve of a face with normal field bn, or (GLM) the exact interface values of
-// the (B_n, psi) subsystem from the reconstructed wl[7..8] | wr[7..8],
-//   bn = (bn_L + bn_R)/2 - (psi_R - psi_L)/(2 c_h),
-//   psi = (psi_L + psi_R)/2 - c_h (bn_R - bn_L)/2,
-// then the MHD solve with bn; psi and c_h^2 bn are the fluxes of B_n and psi.
-template <int RS, class R, int EM>
-__device__ __forceinline__ void march_solve(R gam, const R* wl, const R* wr, R bn, R ch,
-                                            RiemannOut<R>& o, R& psi, R& fpsi) {
-  if constexpr (EM == 2) {
-    bn = R(0.5) * (wl[7] + wr[7]) - div_r(wr[8] - wl[8], R(2) * ch);
-    psi = R(0.5) * (wl[8] + wr[8]) - R(0.5) * ch * (wr[7] - wl[7]);
-    fpsi = ch * ch * bn;
-    riemann<RS, R, 0>(gam, wl, wr, bn, o);
-  } else {
-    riemann<RS, R, EM>(gam, wl, wr, bn, o);
-  }
-}
-
 // Fluxes of (rho, m_x, m_y, m_z, E), with GLM also of (B_x, B_y, B_z, psi),
 // through a D-face.
 template <int D, int EM, class R>
@@ -348,7 +330,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
 #pragma unroll
       for (int q = 0; q < NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
     }
-    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[2], ch, o, psi, fpsi);
+    face_solve<RS, R, EM>(gam, wl, wr, (R)bn[2], ch, o, psi, fpsi);
     {
       R F[NF];
       cell_fluxes<2, EM>(o, psi, fpsi, F);
@@ -383,7 +365,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
       for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx - 2 + s, yy);
       march_recon<LIM, NW>(lds, os, xslot, wl, wr);
     }
-    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[0], ch, o, psi, fpsi);
+    face_solve<RS, R, EM>(gam, wl, wr, (R)bn[0], ch, o, psi, fpsi);
     if constexpr (!GLM) put_edge<0, EM>(fwp, n, boff, o);
     {
       R F[NF];
@@ -402,7 +384,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
       for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx, yy - 2 + s);
       march_recon<LIM, NW>(lds, os, yslot, wl, wr);
     }
-    march_solve<RS, R, EM>(gam, wl, wr, (R)bn[1], ch, o, psi, fpsi);
+    face_solve<RS, R, EM>(gam, wl, wr, (R)bn[1], ch, o, psi, fpsi);
     if constexpr (!GLM) put_edge<1, EM>(fwp, n, boff, o);
     R fy[NF];
     cell_fluxes<1, EM>(o, psi, fpsi, fy);
@@ -435,7 +417,7 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
         for (int s = 0; s < 4; ++s) v[s] = lds[os[kind[q]][s] + xslot[q] * kMarchQ];
         plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
       }
-      march_solve<RS, R, EM>(gam, wl, wr, (R)ebn, ch, o, psi, fpsi);
+      face_solve<RS, R, EM>(gam, wl, wr, (R)ebn, ch, o, psi, fpsi);
       fe[0] = o.f[0];
       fe[1] = ey ? o.f[3] : o.f[1];
       fe[2] = ey ? o.f[1] : o.f[2];

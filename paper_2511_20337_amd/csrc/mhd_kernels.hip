@@ -1333,22 +1333,27 @@ hipError_t stage_glm3d(const StageArgs& a) {
   return hipGetLastError();
 }
 
-// 2D PLM stage (a.records false): one kernel. Where the time step is the CFL
+// 2D stage (a.records false): one kernel. Where the time step is the CFL
 // bound of U, its partials come from the stage that wrote U or a pass over it;
 // the stage's workgroups reduce up to kInlineCfl2d of them themselves on grids
 // of about as many tiles, else k_cfl_final does it once.
-hipError_t stage_plm2d(const StageArgs& a) {
+hipError_t stage2d(const StageArgs& a) {
   const double* cflp = a.cfl_prev;
   int np = a.ncfl;
   if (a.cfl_partial && !cflp) {
     const int64_t need = (a.g.n + kBlock - 1) / kBlock;
     np = (int)(need < kInlineCfl2d ? need : kInlineCfl2d);
     cflp = a.cfl_partial;
-    MHD_TIMED(a, K_CFL,
-              hipLaunchKernelGGL((k_cfl<2>), dim3(np), dim3(kBlock), 0, a.stream, a.U, a.g,
-                                 a.cfl_partial, a.flag));
+    if (a.glm)
+      MHD_TIMED(a, K_CFL,
+                hipLaunchKernelGGL((k_glm_cfl<2>), dim3(np), dim3(kBlock), 0, a.stream, a.U, a.g,
+                                   a.cfl_partial, a.flag));
+    else
+      MHD_TIMED(a, K_CFL,
+                hipLaunchKernelGGL((k_cfl<2>), dim3(np), dim3(kBlock), 0, a.stream, a.U, a.g,
+                                   a.cfl_partial, a.flag));
   }
-  if (cflp && (np > kInlineCfl2d || stage_2d_tiles(a.g, a.precision, a.emf) > 2 * kInlineCfl2d)) {
+  if (cflp && (np > kInlineCfl2d || stage_2d_tiles(a.g, a.limiter, a.emf, a.precision, a.glm) > 2 * kInlineCfl2d)) {
     MHD_TIMED(a, K_CFL_FINAL,
               hipLaunchKernelGGL(k_cfl_final, dim3(1), dim3(1024), 0, a.stream, cflp, np, a.cfl,
                                  a.dt_out));
@@ -1360,7 +1365,7 @@ hipError_t stage_plm2d(const StageArgs& a) {
 
 hipError_t launch_stage(const StageArgs& a) {
   if (a.dim == 3 && a.glm && a.limiter != 2) return stage_glm3d(a);
-  if (a.dim == 2 && !a.glm && a.limiter != 2 && !a.records) return stage_plm2d(a);
+  if (a.dim == 2 && !a.records) return stage2d(a);
   if (a.glm) return (a.dim == 3) ? glm_stage_lim<3>(a) : glm_stage_lim<2>(a);
   if (a.emf == 1) return (a.dim == 3) ? stage_lim<3, 1>(a) : stage_lim<2, 1>(a);
   return (a.dim == 3) ? stage_lim<3, 0>(a) : stage_lim<2, 0>(a);

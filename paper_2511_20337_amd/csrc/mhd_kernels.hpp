@@ -49,10 +49,10 @@ struct StageArgs {
   // 3D PLM only: L(U) of the five cell-averaged fields is left in FW (n
   // doubles each from its start, space no edge input uses) besides
   bool keep_rhs;
-  // 2D PLM only: the stage's face records and E_z in FW and EW (the adjoint
+  // 2D only: the stage's face records and E_z in FW and EW (the adjoint
   // reads them)
   bool records;
-  // 2D PLM only, optional: the stage also leaves the CFL partials of the state
+  // 2D only, optional: the stage also leaves the CFL partials of the state
   // it writes (stage_2d_tiles doubles; out must differ from U and U0), and a
   // first stage takes its dt from ncfl such partials in cfl_prev instead of
   // from a pass over U
@@ -100,9 +100,9 @@ hipError_t launch_cfl(const CflArgs& a);
 MarchGrid march_grid(const Geom& g);
 void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out);
 void launch_update_b(const StageArgs& a, const double* Lc);
-// 2D PLM stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).
+// 2D stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart);
-int stage_2d_tiles(const Geom& g, int precision, int emf);
+int stage_2d_tiles(const Geom& g, int limiter, int emf, int precision, bool glm);
 // Grids of at most this many 32 x 8 tiles take 8 x 8 ones.
 constexpr int64_t kSmallTiles2d = 256;
 // 2D: most CFL partials that every workgroup of the stage reduces itself.

@@ -1,21 +1,25 @@
-// 2D PLM stage in one kernel: a workgroup recovers the primitives of its tile
-// of W x H cells and two cells around it, solves every face that the tile's
-// flux differences and corner EMFs read, forms E_z at the tile's corners and
-// updates its cells, all through LDS.
+// 2D stage in one kernel (PLM, WENO-Z; CT, GLM cleaning): a workgroup recovers
+// the primitives of its tile of W x H cells and the two (WENO-Z: three) cells
+// around it, solves every face that the tile's flux differences and corner EMFs
+// read, forms E_z at the tile's corners and updates its cells, all through LDS.
 //
 // What bounds it: on small grids the latency of this chain (the launches it
 // replaces cost more), on large ones the instruction count. Measured against
 // the two kernels per stage it replaces (tiled faces with 9 stored values each,
 // EMF and update): 128^2 30.5 -> 15.2 us a step, KH 512^2 72.8 -> 60 us, 1500 x
-// 1001 mixed with UCT-HLLD 341 -> 193 us. Choices:
+// 1001 mixed with UCT-HLLD 341 -> 193 us. Against the three of WENO-Z and of GLM
+// (primitives, faces, update): WENO-Z and RK2 29 x 21 43.3 -> 17.3 us a step,
+// L(U) at 323 x 312 27.0 -> 24.2 us; WENO-Z, GLM and RK3 56 x 1230 90.6 -> 64.5
+// us a step; GLM and RK2 82 x 831 49.7 -> 33.2 us. Choices:
 //  - The faces are one list, x-faces then y-faces, dealt to the threads in
 //    turn, so that the two extra rows and columns do not leave waves idle; a
 //    lane's direction is two LDS offsets and a few selects.
 //  - Large grids: 32 x 8 cells, 512 threads: 720 faces are 12 waves' work for 8
 //    waves, and two workgroups fit a CU (16 waves, four per SIMD at 128
 //    VGPRs); KH 512^2 with 256 threads 36.6 us a launch against 34.2, 384: 47.6,
-//    32 x 16 cells and 1024 threads: 34.9, 8 x 8 cells: 43.7. Small ones: 8 x 8 cells, 216 faces for 256 threads, one each: the
-//    shortest chain, and four times the workgroups.
+//    32 x 16 cells and 1024 threads: 34.9, 8 x 8 cells: 43.7. Small ones: 8 x 8
+//    cells, 216 faces for 256 threads, one each: the shortest chain, and four
+//    times the workgroups.
 //  - The time step of the CFL bound is reduced from its partials by every
 //    workgroup itself (a minimum is exact in any order), and between the steps
 //    of one run the stage that writes a state leaves its partials, which saves
@@ -29,26 +33,31 @@ namespace mhd {
 
 namespace {
 
-template <int W_, int H_, int NT_>
+// S: cells around the tile that a reconstruction reaches; E: faces around it
+// that the corner EMFs read (GLM has none).
+template <int W_, int H_, int NT_, int S_, int E_>
 struct Tile2 {
-  static constexpr int W = W_, H = H_, NT = NT_;
-  static constexpr int PW = W + 4, NP = PW * (H + 4);         // cells recovered
-  static constexpr int NX = (W + 1) * (H + 4);                // x-faces solved
-  static constexpr int NF = NX + (W + 4) * (H + 1);           // and y-faces
+  static constexpr int W = W_, H = H_, NT = NT_, S = S_, E = E_;
+  static constexpr int PW = W + 2 * S, NP = PW * (H + 2 * S);    // cells recovered
+  static constexpr int NX = (W + 1) * (H + 2 * E);               // x-faces solved
+  static constexpr int NF = NX + (W + 2 * E) * (H + 1);          // and y-faces
   static constexpr int FX = (W + 1) * H, FN = FX + W * (H + 1);  // those with fluxes
-  static constexpr int NC = (W + 1) * (H + 1);                // corners
+  static constexpr int NC = (W + 1) * (H + 1);                   // corners
 };
 
+// EM 0, 1: CT with the HLL or the UCT-HLLD average; 2: GLM.
 template <class R, class T, int EM>
 struct Lds2 {
-  R v[10][T::NP];          // the eight primitives, then b_x and b_y
-  R fl[6][T::FN];          // fluxes of rho, m_x, m_y, m_z, E, B_z
-  R ed[EM == 1 ? 4 : 3][T::NF];  // alpha+-, (or om, d^L, d^R,) the EMF's velocity
-  R ez[T::NC];
+  static constexpr int NV = EM == 2 ? 9 : 10, NFL = EM == 2 ? 9 : 6;
+  R v[NV][T::NP];   // the eight primitives, then b_x and b_y (GLM: psi)
+  R fl[NFL][T::FN];  // fluxes of rho, m_x, m_y, m_z, E, B_z (GLM: all nine fields)
+  R ed[EM == 2 ? 1 : (EM == 1 ? 4 : 3)][EM == 2 ? 1 : T::NF];  // alpha+- (or om, d^L,
+                                                              // d^R), the EMF's velocity
+  R ez[EM == 2 ? 1 : T::NC];
   double red[T::NT / 64];
 };
 
-// i in [-2, n + W + 1] to its periodic image (n may be smaller than a tile)
+// i in [-3, n + W + 2] to its periodic image (n may be smaller than a tile)
 __device__ __forceinline__ int wrap_near(int i, int n) {
   if (i < 0) return i + n;
   if (i < n) return i;
@@ -67,22 +76,40 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
                 int stage, double dt, const double* __restrict__ dtp,
                 const double* __restrict__ cflp, int npart, double cfl,
                 double* __restrict__ dt_out, double* __restrict__ cfl_next,
-                int* __restrict__ flag) {
+                int* __restrict__ flag, double dmin, double decay) {
   constexpr int W = T::W, H = T::H, NT = T::NT, PW = T::PW, NP = T::NP, NX = T::NX, NF = T::NF;
+  constexpr int S = T::S, E = T::E;
+  constexpr bool GLM = EM == 2;
+  constexpr int NU = GLM ? 9 : 8, NW = GLM ? 9 : 7;  // fields, reconstructed quantities
   __shared__ Lds2<R, T, EM> L;
   const int t = (int)threadIdx.x;
   const int i0 = (int)(blockIdx.x % (unsigned)ntx) * W, j0 = (int)(blockIdx.x / (unsigned)ntx) * H;
   const int64_t n = g.n;
   bool bad = false;
   for (int e = t; e < NP; e += NT) {
-    const int i = wrap_near(i0 + e % PW - 2, g.nx), j = wrap_near(j0 + e / PW - 2, g.ny);
-    const RawCell raw = load_raw<2>(U, g, i, j, 0);
-    double V[8];
+    const int i = wrap_near(i0 + e % PW - S, g.nx), j = wrap_near(j0 + e / PW - S, g.ny);
+    double V[9];
+    RawCell raw;
+    if constexpr (GLM) {
+      const int64_t cc = (int64_t)j * g.nx + i;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) raw.u[q] = U[q * n + cc];
+      raw.bxp = raw.u[5];  // (the mean of two equal faces is the cell's field, exactly)
+      raw.byp = raw.u[6];
+      raw.bzp = 0.0;
+      V[8] = U[8 * n + cc];
+    } else {
+      raw = load_raw<2>(U, g, i, j, 0);
+    }
     bad |= !prim_from_raw<2>(raw, g.gamma, V);
 #pragma unroll
     for (int q = 0; q < 8; ++q) L.v[q][e] = (R)V[q];
-    L.v[8][e] = (R)raw.u[5];
-    L.v[9][e] = (R)raw.u[6];
+    if constexpr (GLM) {
+      L.v[8][e] = (R)V[8];
+    } else {
+      L.v[8][e] = (R)raw.u[5];
+      L.v[9][e] = (R)raw.u[6];
+    }
   }
   if (cflp) {
     double m = __builtin_inf();
@@ -96,43 +123,71 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
   }
   if (bad) atomicOr(flag, 1);
   __syncthreads();
+  double h = 0.0;
+  if (cflp) {
+    double m = L.red[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
+    h = cfl * m;
+    if (blockIdx.x == 0 && t == 0) *dt_out = h;
+  } else if (stage != 0) {
+    h = dtp ? *dtp : dt;
+  }
+  const R ch = GLM ? (R)(cfl * dmin / h) : R(0);  // the largest speed dt allows
   const R* v = &L.v[0][0];
   for (int f = t; f < NF; f += NT) {
     const bool yf = f >= NX;
     // the face's place: column and row of its cell in the list's rectangle
-    const int q0 = yf ? f - NX : f, w0 = yf ? W + 4 : W + 1;
+    const int q0 = yf ? f - NX : f, w0 = yf ? W + 2 * E : W + 1;
     const int fr = q0 / w0, fc = q0 - fr * w0;
-    const int o = fr * PW + fc, st = yf ? PW : 1;  // first stencil cell, step
-    // slots of the x frame, plus 1 at (v_n, v_t1, B_t1) and minus 2 at
+    // first stencil cell, step
+    const int o = yf ? fr * PW + fc + S - E : (fr + S - E) * PW + fc, st = yf ? PW : 1;
+    // slots of the x frame, plus 1 at (v_n, v_t1, B_t1, B_n) and minus 2 at
     // (v_t2, B_t2) for a y-face
-    constexpr int slot[7] = {0, 1, 2, 3, 6, 7, 4}, kind[7] = {0, 1, 1, 2, 1, 2, 0};
+    constexpr int slot[9] = {0, 1, 2, 3, 6, 7, 4, 5, 8}, kind[9] = {0, 1, 1, 2, 1, 2, 0, 1, 0};
     const int ok[3] = {o, o + (yf ? NP : 0), o - (yf ? 2 * NP : 0)};
-    R wl[7], wr[7];
+    R wl[NW], wr[NW];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
+    for (int q = 0; q < NW; ++q) {
       const R* p = v + ok[kind[q]] + slot[q] * NP;
-      plm_pair<LIM, R>(p[0], p[st], p[2 * st], p[3 * st], wl[q], wr[q]);
+      if constexpr (LIM == 2) {
+        const R a[6] = {p[0], p[st], p[2 * st], p[3 * st], p[4 * st], p[5 * st]};
+        wl[q] = wenoz_upper(a[0], a[1], a[2], a[3], a[4]);
+        wr[q] = wenoz_upper(a[5], a[4], a[3], a[2], a[1]);
+      } else {
+        plm_pair<LIM, R>(p[0], p[st], p[2 * st], p[3 * st], wl[q], wr[q]);
+      }
     }
-    const R bn = v[o + 2 * st + (yf ? 9 : 8) * NP];
     RiemannOut<R> r;
-    riemann<RS, R, EM>((R)g.gamma, wl, wr, bn, r);
-    if (EM == 1) {
-      L.ed[0][f] = r.om;
-      L.ed[1][f] = r.dl;
-      L.ed[2][f] = r.dr;
-    } else {
-      L.ed[0][f] = r.ap;
-      L.ed[1][f] = r.am;
+    R psi, fpsi;
+    face_solve<RS, R, EM>((R)g.gamma, wl, wr, GLM ? R(0) : v[o + S * st + (yf ? 9 : 8) * NP], ch, r,
+                          psi, fpsi);
+    if constexpr (!GLM) {
+      if (EM == 1) {
+        L.ed[0][f] = r.om;
+        L.ed[1][f] = r.dl;
+        L.ed[2][f] = r.dr;
+      } else {
+        L.ed[0][f] = r.ap;
+        L.ed[1][f] = r.am;
+      }
+      L.ed[EM == 1 ? 3 : 2][f] = yf ? r.v2 : r.v1;  // v_x on y-faces, v_y on x-faces
     }
-    L.ed[EM == 1 ? 3 : 2][f] = yf ? r.v2 : r.v1;  // v_x on y-faces, v_y on x-faces
-    const int fi = yf ? T::FX + fr * W + fc - 2 : (fr - 2) * (W + 1) + fc;
-    if (yf ? (fc >= 2 && fc < W + 2) : (fr >= 2 && fr < H + 2)) {
+    const int fi = yf ? T::FX + fr * W + fc - E : (fr - E) * (W + 1) + fc;
+    if (yf ? (fc >= E && fc < W + E) : (fr >= E && fr < H + E)) {
       L.fl[0][fi] = r.f[0];
       L.fl[1][fi] = yf ? r.f[3] : r.f[1];
       L.fl[2][fi] = yf ? r.f[1] : r.f[2];
       L.fl[3][fi] = yf ? r.f[2] : r.f[3];
       L.fl[4][fi] = r.f[6];
-      L.fl[5][fi] = yf ? r.f[4] : r.f[5];
+      if constexpr (GLM) {
+        L.fl[5][fi] = yf ? r.f[5] : psi;
+        L.fl[6][fi] = yf ? psi : r.f[4];
+        L.fl[7][fi] = yf ? r.f[4] : r.f[5];
+        L.fl[8][fi] = fpsi;
+      } else {
+        L.fl[5][fi] = yf ? r.f[4] : r.f[5];
+      }
     }
   }
   __syncthreads();
@@ -144,16 +199,16 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
   const bool used = own || (cell && cfl_next);
   const int64_t c =
       used ? (int64_t)wrap_near(j0 + y, g.ny) * g.nx + wrap_near(i0 + x, g.nx) : 0;
-  double u[8], u0[8];
+  double u[NU], u0[NU];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
+  for (int q = 0; q < NU; ++q) {
     u[q] = used ? U[q * n + c] : 0.0;
     u0[q] = used ? U0[q * n + c] : 0.0;
   }
   // cfl_next: the faces above the tile, one each for the next H + W threads
   static_assert(T::NT >= W * H + W + H, "a thread for each face above the tile");
   const int ab = t - W * H;  // 0 .. H - 1: b_x at column W; H .. H + W - 1: b_y at row H
-  const bool above = cfl_next && ab >= 0 && ab < H + W;
+  const bool above = !GLM && cfl_next && ab >= 0 && ab < H + W;
   double ua = 0.0, ua0 = 0.0;
   if (above) {
     const int64_t ca = (ab < H) ? (int64_t)wrap_near(j0 + ab, g.ny) * g.nx + wrap_near(i0 + W, g.nx)
@@ -162,58 +217,54 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
     ua = U[fo];
     ua0 = U0[fo];
   }
+  if constexpr (!GLM) {
+  constexpr int EL = LIM == 2 ? 1 : LIM;  // WENO-Z: van Leer PLM at the corners
   for (int e = t; e < T::NC; e += NT) {
     const int cj = e / (W + 1), ci = e - cj * (W + 1);
-    const int xf = (cj + 2) * (W + 1) + ci;         // the x-face above the corner
-    const int yf = NX + cj * (W + 4) + ci + 2;      // the y-face to its right
+    const int xf = (cj + E) * (W + 1) + ci;         // the x-face above the corner
+    const int yf = NX + cj * (W + 2 * E) + ci + E;      // the y-face to its right
     constexpr int VS = EM == 1 ? 3 : 2;
     R wv[4], wb[4], sv[4], sb[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       wv[s] = L.ed[VS][yf - 2 + s];
-      wb[s] = L.v[9][(cj + 2) * PW + ci + s];
+      wb[s] = L.v[9][(cj + S) * PW + ci + S - 2 + s];
       sv[s] = L.ed[VS][xf + (s - 2) * (W + 1)];
-      sb[s] = L.v[8][(cj + s) * PW + ci + 2];
+      sb[s] = L.v[8][(cj + S - 2 + s) * PW + ci + S];
     }
     const int xm = xf - (W + 1), ym = yf - 1;
     if constexpr (EM == 1)
-      L.ez[e] = emf_core_hlld<LIM, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf],
+      L.ez[e] = emf_core_hlld<EL, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf],
                                       L.ed[2][xm], L.ed[2][xf], L.ed[0][ym], L.ed[0][yf],
                                       L.ed[1][ym], L.ed[1][yf], L.ed[2][ym], L.ed[2][yf], wv, wb,
                                       sv, sb);
     else
-      L.ez[e] = emf_core<LIM, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf], L.ed[0][ym],
+      L.ez[e] = emf_core<EL, R>(L.ed[0][xm], L.ed[0][xf], L.ed[1][xm], L.ed[1][xf], L.ed[0][ym],
                                  L.ed[0][yf], L.ed[1][ym], L.ed[1][yf], wv, wb, sv, sb);
   }
   __syncthreads();
-  double h = 0.0;
-  if (cflp) {
-    double m = L.red[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
-    h = cfl * m;
-    if (blockIdx.x == 0 && t == 0) *dt_out = h;
-  } else if (stage != 0) {
-    h = dtp ? *dtp : dt;
   }
   const RkCoef rk = rk_coef(stage, h);
   const double idx = 1.0 / g.dx, idy = 1.0 / g.dy;
-  double v1[8];
+  double v1[NU];
   if (used) {
     const int fx = y * (W + 1) + x, fy = T::FX + y * W + x, ec = y * (W + 1) + x;
-    double Lq[8];
+    double Lq[NU];
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
-      Lq[q == 5 ? 7 : q] = -(((double)L.fl[q][fx + 1] - (double)L.fl[q][fx]) * idx +
-                             ((double)L.fl[q][fy + W] - (double)L.fl[q][fy]) * idy);
-    const double e0 = (double)L.ez[ec];
-    Lq[5] = -(((double)L.ez[ec + W + 1] - e0) * idy);
-    Lq[6] = ((double)L.ez[ec + 1] - e0) * idx;
+    for (int q = 0; q < (GLM ? 9 : 6); ++q)
+      Lq[!GLM && q == 5 ? 7 : q] = -(((double)L.fl[q][fx + 1] - (double)L.fl[q][fx]) * idx +
+                                     ((double)L.fl[q][fy + W] - (double)L.fl[q][fy]) * idy);
+    if constexpr (!GLM) {
+      const double e0 = (double)L.ez[ec];
+      Lq[5] = -(((double)L.ez[ec + W + 1] - e0) * idy);
+      Lq[6] = ((double)L.ez[ec + 1] - e0) * idx;
+    }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v1[q] = rk_apply(rk, u[q], u0[q], Lq[q]);
+    for (int q = 0; q < NU; ++q) v1[q] = rk_apply(rk, u[q], u0[q], Lq[q]);
+    if (GLM) v1[NU - 1] *= decay;
     if (own) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) out[q * n + c] = v1[q];
+      for (int q = 0; q < NU; ++q) out[q * n + c] = v1[q];
     }
   }
   if (!cfl_next) return;
@@ -226,7 +277,8 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
     nby[y * W + x] = v1[6];
   }
   if (above) {
-    if (ab < H) {
+    if constexpr (GLM) {
+    } else if (ab < H) {
       const int ec = ab * (W + 1) + W;
       nbx[ec] = rk_apply(rk, ua, ua0, -(((double)L.ez[ec + W + 1] - (double)L.ez[ec]) * idy));
     } else {
@@ -241,8 +293,8 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
     RawCell raw;
 #pragma unroll
     for (int q = 0; q < 8; ++q) raw.u[q] = v1[q];
-    raw.bxp = nbx[y * (W + 1) + x + 1];
-    raw.byp = nby[(y + 1) * W + x];
+    raw.bxp = GLM ? v1[5] : nbx[y * (W + 1) + x + 1];
+    raw.byp = GLM ? v1[6] : nby[(y + 1) * W + x];
     raw.bzp = 0.0;
     double V[8];
     prim_from_raw<2>(raw, g.gamma, V);  // (an unphysical cell is the next stage's to report)
@@ -267,51 +319,59 @@ void stage_2d(const StageArgs& a, const double* cflp, int npart) {
   const int ntx = (a.g.nx + T::W - 1) / T::W, nty = (a.g.ny + T::H - 1) / T::H;
   hipLaunchKernelGGL((k_stage_2d<T, LIM, RS, R, EM>), dim3((unsigned)ntx * (unsigned)nty),
                      dim3(T::NT), 0, a.stream, a.U, a.U0 ? a.U0 : a.U, a.out, a.g, ntx, a.stage,
-                     a.dt, a.dtp, cflp, npart, a.cfl, a.dt_out, a.cfl_next, a.flag);
+                     a.dt, a.dtp, cflp, npart, a.cfl, a.dt_out, a.cfl_next, a.flag, a.glm_dmin,
+                     (a.stage == 2 || a.stage == 5) ? a.glm_decay : 1.0);
 }
-// FP64 with the UCT-HLLD average keeps four values a face: 28 x 8 cells are
-// what two workgroups of a CU have LDS for.
-using Small2 = Tile2<8, 8, 256>;
-template <class R, int EM>
-using Large2 = Tile2<(EM == 1 && sizeof(R) == 8) ? 28 : 32, 8, 512>;
 
+// Widths of the large tiles: what two workgroups of a CU have LDS for (in FP64
+// the UCT-HLLD average keeps four values a face, and WENO-Z recovers three
+// cells around).
+constexpr int large_w(int limiter, int emf, int precision) {
+  return emf == 2 ? 32 : limiter == 2 ? 24 : (emf == 1 && precision == 0) ? 28 : 32;
+}
+constexpr int kSmallW = 8, kTileH = 8;
 bool small_tiles(const Geom& g) {
   return (int64_t)((g.nx + 31) / 32) * ((g.ny + 7) / 8) <= kSmallTiles2d;
 }
 
 template <int LIM, int RS, class R, int EM>
 void stage_2d_tile(const StageArgs& a, const double* cflp, int npart) {
-  if (small_tiles(a.g)) stage_2d<Small2, LIM, RS, R, EM>(a, cflp, npart);
-  else stage_2d<Large2<R, EM>, LIM, RS, R, EM>(a, cflp, npart);
+  constexpr int S = LIM == 2 ? 3 : 2, E = EM == 2 ? 0 : 2;
+  using Small = Tile2<kSmallW, kTileH, 256, S, E>;
+  using Large = Tile2<large_w(LIM, EM, sizeof(R) == 4), kTileH, 512, S, E>;
+  if (small_tiles(a.g)) stage_2d<Small, LIM, RS, R, EM>(a, cflp, npart);
+  else stage_2d<Large, LIM, RS, R, EM>(a, cflp, npart);
 }
-template <int LIM, int RS>
-void stage_2d_prec(const StageArgs& a, const double* cflp, int npart) {
-  if (a.precision == 1) {
-    if (a.emf == 1) stage_2d_tile<LIM, RS, float, 1>(a, cflp, npart);
-    else stage_2d_tile<LIM, RS, float, 0>(a, cflp, npart);
+template <int LIM, int RS, class R>
+void stage_2d_emf(const StageArgs& a, const double* cflp, int npart) {
+  if (a.glm) stage_2d_tile<LIM, RS, R, 2>(a, cflp, npart);
+  else if (a.emf == 1) stage_2d_tile<LIM, RS, R, 1>(a, cflp, npart);
+  else stage_2d_tile<LIM, RS, R, 0>(a, cflp, npart);
+}
+template <int RS>
+void stage_2d_lim(const StageArgs& a, const double* cflp, int npart) {
+  const bool mixed = a.precision == 1;
+  if (a.limiter == 2) {
+    stage_2d_emf<2, RS, double>(a, cflp, npart);
+  } else if (a.limiter == 1) {
+    if (mixed) stage_2d_emf<1, RS, float>(a, cflp, npart);
+    else stage_2d_emf<1, RS, double>(a, cflp, npart);
   } else {
-    if (a.emf == 1) stage_2d_tile<LIM, RS, double, 1>(a, cflp, npart);
-    else stage_2d_tile<LIM, RS, double, 0>(a, cflp, npart);
+    if (mixed) stage_2d_emf<0, RS, float>(a, cflp, npart);
+    else stage_2d_emf<0, RS, double>(a, cflp, npart);
   }
 }
 
 }  // namespace
 
-int stage_2d_tiles(const Geom& g, int precision, int emf) {
-  const int W = small_tiles(g) ? Small2::W : (emf == 1 && precision == 0)
-                                                 ? Large2<double, 1>::W : Large2<double, 0>::W;
-  static_assert(Small2::H == 8 && Large2<double, 1>::H == 8 && Large2<double, 0>::H == 8, "");
-  return ((g.nx + W - 1) / W) * ((g.ny + 7) / 8);
+int stage_2d_tiles(const Geom& g, int limiter, int emf, int precision, bool glm) {
+  const int W = small_tiles(g) ? kSmallW : large_w(limiter, glm ? 2 : emf, precision);
+  return ((g.nx + W - 1) / W) * ((g.ny + kTileH - 1) / kTileH);
 }
 
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart) {
-  if (a.limiter == 0) {
-    if (a.riemann == 0) stage_2d_prec<0, 0>(a, cflp, npart);
-    else stage_2d_prec<0, 1>(a, cflp, npart);
-  } else {
-    if (a.riemann == 0) stage_2d_prec<1, 0>(a, cflp, npart);
-    else stage_2d_prec<1, 1>(a, cflp, npart);
-  }
+  if (a.riemann == 0) stage_2d_lim<0>(a, cflp, npart);
+  else stage_2d_lim<1>(a, cflp, npart);
 }
 
 }  // namespace mhd

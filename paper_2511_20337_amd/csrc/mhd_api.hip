@@ -277,6 +277,7 @@ mhd_status run_2d(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void*
 mhd_status cfl_to(mhd_ctx* ctx, const double* U, void* ws, double* dt_dev, hipStream_t s) {
   mhd::CflArgs a{};
   a.dim = ctx->cfg.dim;
+  a.glm = ctx->cfg.divb == MHD_DIVB_GLM;
   a.g = ctx->g;
   a.U = U;
   a.partial = reinterpret_cast<double*>(base(ws) + ctx->off_partial);
@@ -286,7 +287,7 @@ mhd_status cfl_to(mhd_ctx* ctx, const double* U, void* ws, double* dt_dev, hipSt
   a.flag = ws_flag(ws);
   a.stream = s;
   a.timer = ctx->timer;
-  hipError_t e = ctx->cfg.divb == MHD_DIVB_GLM ? mhd::launch_glm_cfl(a) : mhd::launch_cfl(a);
+  hipError_t e = mhd::launch_cfl(a);
   if (e != hipSuccess) return device_fail(ctx, e, "cfl");
   return MHD_OK;
 }

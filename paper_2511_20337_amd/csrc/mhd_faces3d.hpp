@@ -11,7 +11,8 @@
 // (or L) directly. A face solved twice gives the same bits both times.
 //
 // With GLM cleaning (nine cell-centred fields, no edge EMFs) this kernel is the
-// whole stage.
+// whole stage. WENO-Z reads the primitives k_prim left: its stencil is three
+// cells either way, and recovering them again at each plane's halo cost more.
 //
 // What bounds it: the instruction count (2250 per cell at 256^3 in FP64, the
 // vector units 71 % busy). Measured against the split it replaces (a face
@@ -19,14 +20,17 @@
 // them back): faces 1.52 -> 1.60 ms, update 0.96 -> 0.43 ms per launch at 256^3
 // in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms; with GLM (before:
 // primitives 0.44, faces 1.97 and update 1.32 ms per stage through memory) 1.62
-// ms per stage, the step 7.50 -> 3.40 ms. Choices:
+// ms per stage, the step 7.50 -> 3.40 ms. WENO-Z (before: a face kernel without
+// LDS and an update that read all its fluxes back): 352^3 with RK3 and UCT-HLLD
+// faces 6.5 -> 6.4, update 2.7 -> 0.68 ms a stage, the step 35.8 -> 30.2 ms;
+// 150 x 131 x 97 with GLM 1112 -> 900 us. Choices:
 //  - 32 x 8 columns: the extra faces fit one wave (40 lanes; 64 x 4 needs 68),
 //    the halo is 160 cells a plane (64 x 4: 272), and a ragged nx wastes less.
 //  - LDS holds two planes of the column (by the parity of k - k0; the values a
 //    thread needs of planes k-1 and k+1 are its own), one cross halo and the
 //    exchanged fluxes.
-//  - Two waves per SIMD in FP64 (218 VGPRs), three in mixed precision: one more
-//    spills (FP64 2.17 ms against 1.60, mixed 384^3 4.03 against 3.51).
+//  - Two waves per SIMD in FP64 (200 VGPRs, GLM 246), three in mixed precision:
+//    one more spills (FP64 1.95 ms against 1.52, mixed 384^3 3.73 against 3.39).
 //  - Two barriers a plane: before the first one everybody reads plane k; then
 //    the halo of plane k+1 and the exchanged fluxes are written; the second
 //    publishes them.
@@ -46,48 +50,50 @@ namespace {
 
 struct March {
   static constexpr int TX = 32, TY = 8, NCORE = TX * TY;
-  static constexpr int NHX = 4 * TY;           // x halo: columns -2, -1, TX, TX + 1
-  static constexpr int NHALO = NHX + 4 * TX;   // then the y halo rows
 };
 static_assert(March::NCORE == kBlock, "one column cell per thread");
-static_assert(March::NHALO <= March::NCORE, "at most one halo cell per thread");
 static_assert(March::TX + March::TY <= 64, "the faces above the column fit one wave");
 static_assert(March::TX == 32, "a wave holds two rows");
 
-// One stride for every quantity, core or halo, so that a stencil cell is one
-// offset and its quantities lie at constant distances from it.
-template <class R, int NQ, int NF>
+// The cross halo of S cells below and S above (PLM 2, WENO-Z 3) and the LDS
+// offsets. One stride for every quantity, core or halo, so that a stencil cell
+// is one offset and its quantities lie at constant distances from it.
+template <int S>
+struct Halo {
+  static constexpr int NX = 2 * S * March::TY;         // columns -S .. -1, TX .. TX + S - 1
+  static constexpr int N = NX + 2 * S * March::TX;     // then the rows
+  static constexpr int OFF = 2 * March::NCORE;         // offset, after the core of two planes
+  static constexpr int Q = 2 * March::NCORE + N;       // quantity stride
+  static_assert(N <= March::NCORE, "at most one halo cell per thread");
+  // Position of halo entry h relative to the column origin.
+  static __device__ __forceinline__ void pos(int h, int& x, int& y) {
+    if (h < NX) {
+      const int s = h / March::TY;
+      y = h % March::TY;
+      x = (s < S) ? s - S : March::TX + s - S;
+    } else {
+      h -= NX;
+      const int s = h / March::TX;
+      x = h % March::TX;
+      y = (s < S) ? s - S : March::TY + s - S;
+    }
+  }
+  // Offset of cell (xx, yy) of the plane whose core starts at cp (at most one
+  // coordinate outside the column).
+  static __device__ __forceinline__ int at(int cp, int xx, int yy) {
+    const int hx = OFF + ((xx < 0) ? xx + S : xx - March::TX + S) * March::TY + yy;
+    const int hy = OFF + NX + ((yy < 0) ? yy + S : yy - March::TY + S) * March::TX + xx;
+    const int in = cp + yy * March::TX + xx;
+    return (xx < 0 || xx >= March::TX) ? hx : (yy < 0 || yy >= March::TY) ? hy : in;
+  }
+};
+
+template <class R, int S, int NQ, int NF>
 struct MarchLds {
-  R v[NQ][2 * March::NCORE + March::NHALO];  // core of two planes, halo
+  R v[NQ][Halo<S>::Q];     // core of two planes, halo
   R fy[NF][March::NCORE];  // y-fluxes of rows 1 .. TY (row r at (r - 1) * TX)
   R fx[NF][March::TY];     // x-fluxes at column TX
 };
-constexpr int kMarchQ = 2 * March::NCORE + March::NHALO;  // quantity stride
-constexpr int kHaloOff = 2 * March::NCORE;
-
-// Position of halo entry h relative to the column origin.
-__device__ __forceinline__ void march_halo_pos(int h, int& x, int& y) {
-  if (h < March::NHX) {
-    const int s = h / March::TY;
-    y = h % March::TY;
-    x = (s < 2) ? s - 2 : March::TX + s - 2;
-  } else {
-    h -= March::NHX;
-    const int s = h / March::TX;
-    x = h % March::TX;
-    y = (s < 2) ? s - 2 : March::TY + s - 2;
-  }
-}
-
-// Offset of cell (xx, yy) of the plane whose core starts at cp (at most one
-// coordinate outside the column).
-__device__ __forceinline__ int march_xy(int cp, int xx, int yy) {
-  if (xx < 0 || xx >= March::TX)
-    return kHaloOff + ((xx < 0) ? xx + 2 : xx - March::TX + 2) * March::TY + yy;
-  if (yy < 0 || yy >= March::TY)
-    return kHaloOff + March::NHX + ((yy < 0) ? yy + 2 : yy - March::TY + 2) * March::TX + xx;
-  return cp + yy * March::TX + xx;
-}
 
 // A value that every lane holds alike, in scalar registers.
 __device__ __forceinline__ double uni(double v) {
@@ -117,8 +123,8 @@ __device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j) {
 }
 // Raw values of the cell at offsets p in plane kw; the staggered B_z above
 // from plane kw1 (both wrapped into 0..nz-1). GLM (EM 2): the nine
-// cell-centred values, psi in bzp.
-template <int EM>
+// cell-centred values, psi in bzp. WENO-Z (LIM 2): the primitives, from U = PW.
+template <int LIM, int EM>
 __device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, const Geom& g,
                                                   int64_t nxy, int kw, int kw1,
                                                   const PlaneOffs& p) {
@@ -127,9 +133,9 @@ __device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, 
   RawCell r;
 #pragma unroll
   for (int q = 0; q < 8; ++q) r.u[q] = ld_at(pl + q * g.n, c);
-  if constexpr (EM == 2) {
+  if constexpr (EM == 2 || LIM == 2) {
     r.bxp = r.byp = 0.0;
-    r.bzp = ld_at(pl + 8 * g.n, c);
+    r.bzp = (EM == 2) ? ld_at(pl + 8 * g.n, c) : 0.0;
     return r;
   }
   r.bxp = ld_at(pl + 5 * g.n, xp);
@@ -139,9 +145,14 @@ __device__ __forceinline__ RawCell load_raw_plane(const double* __restrict__ U, 
 }
 
 // The primitives of a raw cell (GLM: with psi as the ninth).
-template <int EM>
+template <int LIM, int EM>
 __device__ __forceinline__ bool march_prim(const RawCell& r, double gamma, double* W) {
-  if constexpr (EM == 2) {
+  if constexpr (LIM == 2) {  // recovered (and checked) already
+#pragma unroll
+    for (int q = 0; q < 8; ++q) W[q] = r.u[q];
+    W[8] = r.bzp;
+    return true;
+  } else if constexpr (EM == 2) {
     RawCell c = r;  // a mean of two equal faces is the cell's field, exactly
     c.bxp = r.u[5];
     c.byp = r.u[6];
@@ -193,17 +204,18 @@ __device__ __forceinline__ void cell_fluxes(const RiemannOut<R>& o, R psi, R fps
   }
 }
 
-// Reconstructed states of a face from its four stencil cells (offsets o);
-// slot: the quantities of the face frame.
-template <int LIM, int NW, class R>
-__device__ __forceinline__ void march_recon(const R* lds, const int* o, const int* slot, R* wl,
-                                            R* wr) {
+// Left and right value of quantity q at a face from its stencil cells (offsets
+// o), S of them on either side.
+template <int LIM, int S, class R>
+__device__ __forceinline__ void march_pair(const R* lds, const int* o, int q, R& l, R& r) {
+  R v[2 * S];
 #pragma unroll
-  for (int q = 0; q < NW; ++q) {
-    R v[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = lds[o[s] + slot[q] * kMarchQ];
-    plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
+  for (int s = 0; s < 2 * S; ++s) v[s] = lds[o[s] + q * Halo<S>::Q];
+  if constexpr (LIM == 2) {
+    l = wenoz_upper(v[0], v[1], v[2], v[3], v[4]);
+    r = wenoz_upper(v[5], v[4], v[3], v[2], v[1]);
+  } else {
+    plm_pair<LIM, R>(v[0], v[1], v[2], v[3], l, r);
   }
 }
 
@@ -215,17 +227,21 @@ __device__ __forceinline__ void march_recon(const R* lds, const int* o, const in
 // times decay in a step's last stage; no CFL bound (c_h needs the dt).
 template <int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 3)))
-void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
+void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
+                   const double* U0, double* out,
                    double* __restrict__ FW, Geom g, MarchGrid mg, int stage, double dt,
                    const double* __restrict__ dtp, int* __restrict__ flag,
                    double* __restrict__ cflp, double ch0, double decay) {
   using M = March;
-  constexpr bool GLM = EM == 2;
+  constexpr bool GLM = EM == 2, WZ = LIM == 2;
+  constexpr int S = WZ ? 3 : 2;
+  using HL = Halo<S>;
+  const double* __restrict__ const src = WZ ? PW : U;
   constexpr int NQ = GLM ? 9 : 8, NF = GLM ? 9 : 5, NW = GLM ? 9 : 7;
   // face frames (rho, v_n, v_t1, v_t2, B_t1, B_t2, p), GLM: and (B_n, psi)
   constexpr int xslot[9] = {0, 1, 2, 3, 6, 7, 4, 5, 8}, yslot[9] = {0, 2, 3, 1, 7, 5, 4, 6, 8};
   constexpr int zslot[9] = {0, 3, 1, 2, 5, 6, 4, 7, 8};
-  __shared__ MarchLds<R, NQ, NF> L;
+  __shared__ MarchLds<R, S, NQ, NF> L;
   R* lds = &L.v[0][0];
   const unsigned b = blockIdx.x;
   const int tx = (int)(b % (unsigned)mg.ntx);
@@ -244,9 +260,9 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
   const PlaneOffs po = plane_offs(g, i0 + x, j0 + y);
   const uint32_t boff = po.c / 8u * (uint32_t)sizeof(R);
   // halo cell (threads past the halo load a valid cell and drop it)
-  const bool haloer = t < M::NHALO;
+  const bool haloer = t < HL::N;
   int hx, hy;
-  march_halo_pos(haloer ? t : M::NHALO - 1, hx, hy);
+  HL::pos(haloer ? t : HL::N - 1, hx, hy);
   const PlaneOffs ph = plane_offs(g, i0 + hx, j0 + hy);
   // face above the column of this lane: y-faces of lanes 0 .. 31, x-faces of
   // lanes 32 .. 39 (further lanes repeat the last); the offset of its cell
@@ -266,37 +282,57 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
   // core plane, the left state of the first z-face, the raw cell of k0 + 1.
   R zl[NW];
   double bn[3];  // normal fields of the own cell's lower faces, plane k
+  // WENO-Z: the own column's z-face quantities of planes k - 2 and k + 2, the
+  // normal fields of plane k + 1
+  double zm2[NW], zp2[NW], nb[3] = {0.0, 0.0, 0.0};
   {
     const int km2 = wrap_any(k0 - 2, g.nz), km1 = wrap_any(k0 - 1, g.nz);
     const int kp1 = wrap_any(k0 + 1, g.nz);
-    const RawCell rm2 = load_raw_plane<EM>(U, g, nxy, km2, km1, po);
-    const RawCell rm1 = load_raw_plane<EM>(U, g, nxy, km1, k0, po);
-    const RawCell rc = load_raw_plane<EM>(U, g, nxy, k0, kp1, po);
-    const RawCell rh = load_raw_plane<EM>(U, g, nxy, k0, kp1, ph);
+    const RawCell rm2 = load_raw_plane<LIM, EM>(src, g, nxy, km2, km1, po);
+    const RawCell rm1 = load_raw_plane<LIM, EM>(src, g, nxy, km1, k0, po);
+    const RawCell rc = load_raw_plane<LIM, EM>(src, g, nxy, k0, kp1, po);
+    const RawCell rh = load_raw_plane<LIM, EM>(src, g, nxy, k0, kp1, ph);
     double Wm2[9], Wm1[9], W[9];
-    bad |= !march_prim<EM>(rm2, g.gamma, Wm2);
-    bad |= !march_prim<EM>(rm1, g.gamma, Wm1);
-    bad |= !march_prim<EM>(rc, g.gamma, W);
+    bad |= !march_prim<LIM, EM>(rm2, g.gamma, Wm2);
+    bad |= !march_prim<LIM, EM>(rm1, g.gamma, Wm1);
+    bad |= !march_prim<LIM, EM>(rc, g.gamma, W);
     if (cflp) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      lds[q * kMarchQ + M::NCORE + t] = (R)Wm1[q];
-      lds[q * kMarchQ + t] = (R)W[q];
+      lds[q * HL::Q + M::NCORE + t] = (R)Wm1[q];
+      lds[q * HL::Q + t] = (R)W[q];
+    }
+    if constexpr (WZ) {  // the upper value of cell k0 - 1, from planes k0 - 3 .. k0 + 1
+      const double* const pm3 = PW + wrap_any(k0 - 3, g.nz) * nxy;
+      const double* const pp1 = PW + kp1 * nxy;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const int sq = zslot[q];
+        zl[q] = wenoz_upper(ld_at(pm3 + sq * n, po.c), Wm2[sq], Wm1[sq], W[sq],
+                            ld_at(pp1 + sq * n, po.c));
+        zm2[q] = Wm2[sq];
+        zp2[q] = ld_at(PW + sq * n + wrap_any(k0 + 2, g.nz) * nxy, po.c);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const R a = (R)Wm2[zslot[q]], bb = (R)Wm1[zslot[q]], c = (R)W[zslot[q]];
+        zl[q] = plm_up<LIM, R>(plm_slope<LIM, R>(bb - a, c - bb), bb);
+      }
     }
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      const R a = (R)Wm2[zslot[q]], bb = (R)Wm1[zslot[q]], c = (R)W[zslot[q]];
-      zl[q] = plm_up<LIM, R>(plm_slope<LIM, R>(bb - a, c - bb), bb);
+    for (int d = 0; d < 3; ++d) {
+      bn[d] = WZ ? (GLM ? 0.0 : ld_at(U + (F_BX + d) * n + k0 * nxy, po.c)) : rc.u[5 + d];
+      if (WZ && !GLM) nb[d] = ld_at(U + (F_BX + d) * n + kp1 * nxy, po.c);
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) bn[d] = rc.u[5 + d];
     if (haloer) {
-      bad |= !march_prim<EM>(rh, g.gamma, W);
+      bad |= !march_prim<LIM, EM>(rh, g.gamma, W);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[q * HL::Q + HL::OFF + t] = (R)W[q];
     }
   }
-  RawCell nxt = load_raw_plane<EM>(U, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
+  RawCell nxt =
+      load_raw_plane<LIM, EM>(src, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
   __syncthreads();
   int cp = 0;  // core offset of plane k
   double acc[NF];  // minus L of the cell below, but for its upper z-flux
@@ -306,29 +342,37 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     R* const fwp = fw0 + kw * nxy;
     R wl[NW], wr[NW], psi = R(0), fpsi = R(0);
     RiemannOut<R> o;
-    // z-face: the own cell of plane k + 1, then the slope of cell k, which
-    // gives the right state and the next plane's left state
+    // z-face: the own cell of plane k + 1, then the reconstruction of cell k,
+    // which gives the right state and the next plane's left state
     double bnn[3];
     {
       double W[9];
-      bad |= !march_prim<EM>(nxt, g.gamma, W);
+      bad |= !march_prim<LIM, EM>(nxt, g.gamma, W);
       if (cflp && k + 1 < k1) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) bnn[d] = nxt.u[5 + d];
+      for (int d = 0; d < 3; ++d) bnn[d] = WZ ? nb[d] : nxt.u[5 + d];
       const int cn = M::NCORE - cp + t;  // own cell in the other core plane: k - 1, then k + 1
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
         const int sq = zslot[q];
-        const R a = lds[cn + sq * kMarchQ];
-        const R bb = lds[cp + t + sq * kMarchQ];
+        const R a = lds[cn + sq * HL::Q];
+        const R bb = lds[cp + t + sq * HL::Q];
         const R c = (R)W[sq];
-        const R dlt = plm_slope<LIM, R>(bb - a, c - bb);
         wl[q] = zl[q];
-        wr[q] = plm_lo<LIM, R>(dlt, bb);
-        zl[q] = plm_up<LIM, R>(dlt, bb);
+        if constexpr (WZ) {
+          wenoz_both(zm2[q], a, bb, c, zp2[q], wr[q], zl[q]);
+        } else {
+          const R dlt = plm_slope<LIM, R>(bb - a, c - bb);
+          wr[q] = plm_lo<LIM, R>(dlt, bb);
+          zl[q] = plm_up<LIM, R>(dlt, bb);
+        }
+        // formed here: the compiler otherwise moves the arithmetic of the next
+        // plane's left state behind the faces and keeps its inputs until then
+        // (WENO-Z spilled 200 B a lane and took 9.5 ms instead of 6.4 at 352^3)
+        zl[q] = here(zl[q]);
       }
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) lds[cn + q * kMarchQ] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[cn + q * HL::Q] = (R)W[q];
     }
     face_solve<RS, R, EM>(gam, wl, wr, (R)bn[2], ch, o, psi, fpsi);
     {
@@ -360,10 +404,11 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     // x-face
     {
       const int tt = here(t), xx = tt & (M::TX - 1), yy = tt / M::TX;
-      int os[4];
+      int os[2 * S];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx - 2 + s, yy);
-      march_recon<LIM, NW>(lds, os, xslot, wl, wr);
+      for (int s = 0; s < 2 * S; ++s) os[s] = HL::at(cp, xx - S + s, yy);
+#pragma unroll
+      for (int q = 0; q < NW; ++q) march_pair<LIM, S, R>(lds, os, xslot[q], wl[q], wr[q]);
     }
     face_solve<RS, R, EM>(gam, wl, wr, (R)bn[0], ch, o, psi, fpsi);
     if constexpr (!GLM) put_edge<0, EM>(fwp, n, boff, o);
@@ -379,10 +424,11 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     // y-face
     {
       const int tt = here(t), xx = tt & (M::TX - 1), yy = tt / M::TX;
-      int os[4];
+      int os[2 * S];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) os[s] = march_xy(cp, xx, yy - 2 + s);
-      march_recon<LIM, NW>(lds, os, yslot, wl, wr);
+      for (int s = 0; s < 2 * S; ++s) os[s] = HL::at(cp, xx, yy - S + s);
+#pragma unroll
+      for (int q = 0; q < NW; ++q) march_pair<LIM, S, R>(lds, os, yslot[q], wl[q], wr[q]);
     }
     face_solve<RS, R, EM>(gam, wl, wr, (R)bn[1], ch, o, psi, fpsi);
     if constexpr (!GLM) put_edge<1, EM>(fwp, n, boff, o);
@@ -401,22 +447,18 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
           GLM ? 0.0 : ld_at(U + (ey ? F_BY : F_BX) * n + kw * nxy, here(eoff));
       // slots: the x frame's, plus 1 at (v_n, v_t1, B_t1, B_n) and minus 2 at
       // (v_t2, B_t2) for a y-face
-      const int up = ey ? kMarchQ : 0, dn = ey ? -2 * kMarchQ : 0;
-      int os[3][4];
+      const int up = ey ? HL::Q : 0, dn = ey ? -2 * HL::Q : 0;
+      int os[3][2 * S];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        os[0][s] = march_xy(cp, ey ? e : M::TX - 2 + s, ey ? M::TY - 2 + s : e);
+      for (int s = 0; s < 2 * S; ++s) {
+        os[0][s] = HL::at(cp, ey ? e : M::TX - S + s, ey ? M::TY - S + s : e);
         os[1][s] = os[0][s] + up;
         os[2][s] = os[0][s] + dn;
       }
       constexpr int kind[9] = {0, 1, 1, 2, 1, 2, 0, 1, 0};
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        R v[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) v[s] = lds[os[kind[q]][s] + xslot[q] * kMarchQ];
-        plm_pair<LIM, R>(v[0], v[1], v[2], v[3], wl[q], wr[q]);
-      }
+      for (int q = 0; q < NW; ++q)
+        march_pair<LIM, S, R>(lds, os[kind[q]], xslot[q], wl[q], wr[q]);
       face_solve<RS, R, EM>(gam, wl, wr, (R)ebn, ch, o, psi, fpsi);
       fe[0] = o.f[0];
       fe[1] = ey ? o.f[3] : o.f[1];
@@ -432,8 +474,21 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     }
     // the raw halo cell of plane k + 1 and own cell of plane k + 2 (their
     // latency passes at the barriers)
-    const RawCell hr = load_raw_plane<EM>(U, g, nxy, ka, kb, ph);
-    nxt = load_raw_plane<EM>(U, g, nxy, kb, kc, po);
+    const RawCell hr = load_raw_plane<LIM, EM>(src, g, nxy, ka, kb, ph);
+    nxt = load_raw_plane<LIM, EM>(src, g, nxy, kb, kc, po);
+    if constexpr (WZ) {
+      const uint32_t c = here(po.c);
+      const int km1 = wrap_any(k - 1, g.nz);
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        zm2[q] = ld_at(PW + zslot[q] * n + km1 * nxy, c);
+        zp2[q] = ld_at(PW + zslot[q] * n + kc * nxy, c);
+      }
+      if constexpr (!GLM) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) nb[d] = ld_at(U + (F_BX + d) * n + kb * nxy, c);
+      }
+    }
     __syncthreads();
     if (y > 0) {
 #pragma unroll
@@ -448,9 +503,9 @@ void k_faces_march(const double* __restrict__ U, const double* U0, double* out,
     }
     if (haloer) {
       double W[9];
-      bad |= !march_prim<EM>(hr, g.gamma, W);
+      bad |= !march_prim<LIM, EM>(hr, g.gamma, W);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) lds[q * kMarchQ + kHaloOff + t] = (R)W[q];
+      for (int q = 0; q < NQ; ++q) lds[q * HL::Q + HL::OFF + t] = (R)W[q];
     }
     __syncthreads();
 #pragma unroll
@@ -476,7 +531,7 @@ __global__ __launch_bounds__(kBlock) void k_update_b(const double* __restrict__ 
                                                     double* out, const double* __restrict__ EW,
                                                     Geom g, MarchGrid tg, double dt,
                                                     const double* __restrict__ dtp) {
-  // mixed mode (FP32 EMFs): the XCD-grouped order, as in k_update2
+  // mixed mode (FP32 EMFs): the XCD-grouped order
   const unsigned b = (sizeof(R) == 4) ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
   const int tx = (int)(b % (unsigned)tg.ntx);
   const unsigned r = b / (unsigned)tg.ntx;
@@ -527,8 +582,8 @@ __global__ __launch_bounds__(kBlock) void k_update_b(const double* __restrict__ 
 template <int LIM, int RS, class R, int EM>
 void faces_impl(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
   hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM>), dim3(mg.nblocks), dim3(kBlock), 0, a.stream,
-                     a.U, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag, a.cfl_partial, a.cfl * a.glm_dmin,
-                     (stage == 2 || stage == 5) ? a.glm_decay : 1.0);
+                     a.U, a.PW, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag,
+                     a.cfl_partial, a.cfl * a.glm_dmin, (stage == 2 || stage == 5) ? a.glm_decay : 1.0);
 }
 template <int LIM, int RS, class R>
 void faces_em(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
@@ -538,7 +593,8 @@ void faces_em(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
 }
 template <int LIM, int RS>
 void faces_prec(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
-  if (a.precision == 1) faces_em<LIM, RS, float>(a, mg, stage, out);
+  if constexpr (LIM == 2) faces_em<LIM, RS, double>(a, mg, stage, out);
+  else if (a.precision == 1) faces_em<LIM, RS, float>(a, mg, stage, out);
   else faces_em<LIM, RS, double>(a, mg, stage, out);
 }
 
@@ -595,7 +651,10 @@ MarchGrid march_grid(const Geom& g) {
 }
 
 void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
-  if (a.limiter == 0) {
+  if (a.limiter == 2) {
+    if (a.riemann == 0) faces_prec<2, 0>(a, mg, stage, out);
+    else faces_prec<2, 1>(a, mg, stage, out);
+  } else if (a.limiter == 0) {
     if (a.riemann == 0) faces_prec<0, 0>(a, mg, stage, out);
     else faces_prec<0, 1>(a, mg, stage, out);
   } else {

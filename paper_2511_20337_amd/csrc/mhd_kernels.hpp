@@ -33,7 +33,7 @@ struct StageArgs {
   double* out;
   double* FW;             // face records: dim * NSLOT * n doubles
   double* EW;             // edge EMFs: 3 * n doubles
-  double* PW;             // WENO-Z only: primitives of every cell, 8 * n doubles
+  double* PW;             // 3D WENO-Z only: primitives of every cell, 8 (GLM: 9) * n doubles
   double dt;
   const double* dtp;      // device dt (nullptr: use dt)
   int* flag;              // sticky unphysical flag
@@ -70,6 +70,7 @@ struct MarchGrid {
 
 struct CflArgs {
   int dim;
+  bool glm;               // GLM: nine cell-centred fields
   Geom g;
   const double* U;
   double* partial;        // nblocks doubles
@@ -92,10 +93,9 @@ hipError_t launch_stage(const StageArgs& a);
 // number of CFL partials the 3D face kernel (WENO-Z, GLM: primitive kernel)
 // writes (one per workgroup)
 size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm);
-// GLM: the CFL time step of U
-hipError_t launch_glm_cfl(const CflArgs& a);
+// the CFL time step of U
 hipError_t launch_cfl(const CflArgs& a);
-// 3D PLM face kernel (stage 3: edge inputs only) and the update that follows
+// 3D face kernel (stage 3: edge inputs only) and the update that follows
 // the EMFs (Lc: the cell fields' L where they are not finished yet, or null).
 MarchGrid march_grid(const Geom& g);
 void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out);

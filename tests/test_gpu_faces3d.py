@@ -1,4 +1,4 @@
-"""The 3D PLM face kernel at the sizes where its columns (32 x 8 cells), the
+"""The 3D face kernel at the sizes where its columns (32 x 8 cells), the
 faces solved above them and its runs along z can go wrong, against the oracle:
 FP64 to the repository's 1e-12 per field, mixed precision to the mixed path's
 stated 2e-5."""
@@ -18,12 +18,14 @@ GRIDS = [(32, 8, 4), (33, 9, 5), (31, 7, 6), (4, 4, 4), (64, 16, 9), (5, 40, 4),
 
 
 @pytest.mark.parametrize("grid", GRIDS)
-@pytest.mark.parametrize("scheme", ["hlld", "hll_uct_hlld", "hlld_uct_hlld_rk3", "mixed_rk3"])
+@pytest.mark.parametrize("scheme", ["hlld", "hll_uct_hlld", "hlld_uct_hlld_rk3", "mixed_rk3",
+                                    "hll_wenoz_uct_hlld_rk3", "hlld_wenoz"])
 def test_columns_and_runs(grid, scheme):
     from paper_2511_20337_amd import mhd
     nx, ny, nz = grid
-    s, U0 = W.generic_state(3, nx, ny, nz, "minmod" if scheme == "hlld" else "vanleer",
-                            "hll" if scheme.startswith("hll_") else "hlld", seed=nx + nz)
+    lim = "wenoz" if "wenoz" in scheme else ("minmod" if scheme == "hlld" else "vanleer")
+    s, U0 = W.generic_state(3, nx, ny, nz, lim, "hll" if scheme.startswith("hll_") else "hlld",
+                            seed=nx + nz)
     s = dict(s, emf="uct_hlld" if "uct_hlld" in scheme else "uct_hll",
              integrator="rk3" if "rk3" in scheme else "rk2",
              precision="mixed" if "mixed" in scheme else "fp64")
@@ -53,14 +55,15 @@ def test_columns_and_runs(grid, scheme):
 
 
 @pytest.mark.parametrize("grid", GRIDS)
-@pytest.mark.parametrize("scheme", ["hlld", "hll_rk3", "mixed"])
+@pytest.mark.parametrize("scheme", ["hlld", "hll_rk3", "mixed", "wenoz"])
 def test_columns_and_runs_glm(grid, scheme):
     """The same kernel on the nine cell-centred fields of GLM cleaning."""
     from paper_2511_20337_amd import mhd
     from tests.test_gpu_glm import rel_err9
     nx, ny, nz = grid
-    s, U = W.generic_state(3, nx, ny, nz, "minmod" if scheme == "mixed" else "vanleer",
-                           "hll" if scheme == "hll_rk3" else "hlld", seed=nx + nz)
+    lim = {"mixed": "minmod", "wenoz": "wenoz"}.get(scheme, "vanleer")
+    s, U = W.generic_state(3, nx, ny, nz, lim, "hll" if scheme == "hll_rk3" else "hlld",
+                           seed=nx + nz)
     s, U0 = W.glm_from_ct(s, U)
     U0[8] = 0.02 * np.random.default_rng(17).normal(size=U0[8].shape)
     s = dict(s, integrator="rk3" if scheme == "hll_rk3" else "rk2",

@@ -929,8 +929,7 @@ __device__ __forceinline__ void stage_rhs(const double* __restrict__ FW,
   const int64_t n = g.n;
   const int64_t xp = lin(g, wrap(i + 1, g.nx), j, k);
   const int64_t yp = lin(g, i, wrap(j + 1, g.ny), k);
-  const int64_t zp = (DIM == 3) ? lin(g, i, j, wrap(k + 1, g.nz)) : c;
-  const double idx = 1.0 / g.dx, idy = 1.0 / g.dy, idz = 1.0 / g.dz;
+  const double idx = 1.0 / g.dx, idy = 1.0 / g.dy;
   if constexpr (DIM == 3) {  // the cell fields' L as the face kernel left it
 #pragma unroll
     for (int q = 0; q < 5; ++q) L[q] = FW[q * n + c];
@@ -942,13 +941,9 @@ __device__ __forceinline__ void stage_rhs(const double* __restrict__ FW,
       L[q == 5 ? 7 : q] = -((fx[q * n + xp] - fx[q * n + c]) * idx +
                             (fy[q * n + yp] - fy[q * n + c]) * idy);
   }
-  if (DIM == 3) {
-    const double* ex = EW;
-    const double* ey = EW + n;
-    const double* ez = EW + 2 * n;
-    L[5] = -((ez[yp] - ez[c]) * idy - (ey[zp] - ey[c]) * idz);
-    L[6] = -((ex[zp] - ex[c]) * idz - (ez[xp] - ez[c]) * idx);
-    L[7] = -((ey[xp] - ey[c]) * idx - (ex[yp] - ex[c]) * idy);
+  if (DIM == 3) {  // and the field's as the CT kernel left it
+#pragma unroll
+    for (int d = 0; d < 3; ++d) L[5 + d] = EW[d * n + c];
   } else {
     const double* ez = EW + 2 * n;
     L[5] = -((ez[yp] - ez[c]) * idy);

@@ -333,7 +333,7 @@ mhd_status mhd_init(const mhd_config* cfg, mhd_ctx** out) {
   // of the fused step; GLM: one per primitive workgroup in 2D and 3D
   size_t npart = kCflBlocks;
   if (cfg->dim == 3 || glm)
-    npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter, glm));
+    npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter));
   size_t off = kCtl;
   c->off_partial = off;
   off = align_up(off + sizeof(double) * npart);

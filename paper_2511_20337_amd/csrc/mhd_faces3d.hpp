@@ -1,5 +1,5 @@
-// 3D PLM stage kernels: the z-marching face kernel, which also differences the
-// fluxes of the cell-averaged fields, and the update of the staggered field.
+// 3D stage: the z-marching face kernel, which also differences the fluxes of the
+// cell-averaged fields.
 //
 // A workgroup owns a 32 x 8 column of cells and walks a run of planes
 // k0 <= k < k1, one cell of each plane per thread. Per plane each thread
@@ -29,7 +29,7 @@
 //  - LDS holds two planes of the column (by the parity of k - k0; the values a
 //    thread needs of planes k-1 and k+1 are its own), one cross halo and the
 //    exchanged fluxes.
-//  - Two waves per SIMD in FP64 (200 VGPRs, GLM 246), three in mixed precision:
+//  - Two waves per SIMD in FP64 (204 VGPRs, GLM 252), three in mixed precision:
 //    one more spills (FP64 1.95 ms against 1.52, mixed 384^3 3.73 against 3.39).
 //  - Two barriers a plane: before the first one everybody reads plane k; then
 //    the halo of plane k+1 and the exchanged fluxes are written; the second
@@ -93,18 +93,9 @@ struct MarchLds {
   R v[NQ][Halo<S>::Q];     // core of two planes, halo
   R fy[NF][March::NCORE];  // y-fluxes of rows 1 .. TY (row r at (r - 1) * TX)
   R fx[NF][March::TY];     // x-fluxes at column TX
+  double red[March::NCORE / 64];
 };
 
-// A value that every lane holds alike, in scalar registers.
-__device__ __forceinline__ double uni(double v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ float uni(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-}
 // Byte offsets within a plane of one field (FP64) of the values the primitive
 // recovery of cell (i, j) reads (indices wrapped): the cell, and its upper x
 // and y neighbours (staggered B_x, B_y). The staggered B_z above is the
@@ -113,8 +104,9 @@ __device__ __forceinline__ float uni(float v) {
 struct PlaneOffs {
   uint32_t c, xp, yp;
 };
-__device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j) {
-  const int iw = wrap_any(i, g.nx), jw = wrap_any(j, g.ny);
+__device__ __forceinline__ PlaneOffs plane_offs(const Geom& g, int i, int j, bool wide) {
+  const int iw = wide ? wrap(i, g.nx) : wrap_any(i, g.nx);
+  const int jw = wide ? wrap(j, g.ny) : wrap_any(j, g.ny);
   PlaneOffs p;
   p.c = (uint32_t)(jw * g.nx + iw) * 8u;
   p.xp = (uint32_t)(jw * g.nx + wrap(iw + 1, g.nx)) * 8u;
@@ -219,19 +211,19 @@ __device__ __forceinline__ void march_pair(const R* lds, const int* o, int q, R&
   }
 }
 
-// stage: as rk_combine, for the five cell-averaged fields (U0 not null: U
-// where the stage does not use it); 3: edge inputs only. cflp != nullptr: also
-// the CFL bound of the state over the column and run into cflp[blockIdx.x] (a
-// lane past the grid repeats a cell, which a minimum does not mind). EM 2: GLM
-// cleaning, nine cell-centred fields and no edge inputs, c_h = ch0 / dt, psi
-// times decay in a step's last stage; no CFL bound (c_h needs the dt).
+// stage: as rk_coef, for the five cell-averaged fields (U0 not null: U
+// where the stage does not use it); 3: no state. Lc != nullptr: their L too, into
+// Lc[5][n]. EM 2: GLM cleaning, nine cell-centred fields and no edge inputs, c_h =
+// ch0 / dt, psi times decay in a step's last stage. cflp != nullptr:
+// dt = cfl times the minimum of the npart CFL partials of U, also to *dt_out.
 template <int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 3)))
 void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
                    const double* U0, double* out,
                    double* __restrict__ FW, Geom g, MarchGrid mg, int stage, double dt,
                    const double* __restrict__ dtp, int* __restrict__ flag,
-                   double* __restrict__ cflp, double ch0, double decay) {
+                   double* __restrict__ Lc, double ch0, double decay,
+                   const double* __restrict__ cflp, int npart, double cfl, double* dt_out) {
   using M = March;
   constexpr bool GLM = EM == 2, WZ = LIM == 2;
   constexpr int S = WZ ? 3 : 2;
@@ -257,27 +249,35 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
   const bool inside = (i0 + x < g.nx) && (j0 + y < g.ny);
   const int64_t n = g.n, nxy = (int64_t)g.nx * g.ny;
   const R gam = (R)g.gamma;
-  const PlaneOffs po = plane_offs(g, i0 + x, j0 + y);
+  // (a remainder only where the grid is smaller than what its last column reaches)
+  const bool wide = mg.ntx * M::TX + S <= 2 * g.nx && mg.nty * M::TY + S <= 2 * g.ny;
+  const PlaneOffs po = plane_offs(g, i0 + x, j0 + y, wide);
   const uint32_t boff = po.c / 8u * (uint32_t)sizeof(R);
   // halo cell (threads past the halo load a valid cell and drop it)
   const bool haloer = t < HL::N;
   int hx, hy;
   HL::pos(haloer ? t : HL::N - 1, hx, hy);
-  const PlaneOffs ph = plane_offs(g, i0 + hx, j0 + hy);
+  const PlaneOffs ph = plane_offs(g, i0 + hx, j0 + hy, wide);
   // face above the column of this lane: y-faces of lanes 0 .. 31, x-faces of
   // lanes 32 .. 39 (further lanes repeat the last); the offset of its cell
   uint32_t eoff;
   {
     const bool ey = lane < M::TX;
     const int e = ey ? lane : min(lane - M::TX, M::TY - 1);
-    eoff = plane_offs(g, i0 + (ey ? e : M::TX), j0 + (ey ? M::TY : e)).c;
+    eoff = plane_offs(g, i0 + (ey ? e : M::TX), j0 + (ey ? M::TY : e), wide).c;
   }
-  const double h = (stage == 0 || stage == 3) ? 0.0 : uni(dtp ? *dtp : dt);
-  const RkCoef rk = rk_coef(stage, h);
-  const R ch = GLM ? uni((R)(ch0 / h)) : R(0);
   const double idx = uni(1.0 / g.dx), idy = uni(1.0 / g.dy), idz = uni(1.0 / g.dz);
   bool bad = false;
-  double cmin = __builtin_inf();
+  if (cflp) {
+    double m = __builtin_inf();
+    for (int e = t; e < npart; e += M::NCORE) m = (cflp[e] < m) ? cflp[e] : m;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const double o = __shfl_xor(m, off, 64);
+      m = (o < m) ? o : m;
+    }
+    if (lane == 0) L.red[wave] = m;
+  }
   // Prologue: plane k0 (core and halo), V_{k0-1} of the own cell in the other
   // core plane, the left state of the first z-face, the raw cell of k0 + 1.
   R zl[NW];
@@ -286,8 +286,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
   // normal fields of plane k + 1
   double zm2[NW], zp2[NW], nb[3] = {0.0, 0.0, 0.0};
   {
-    const int km2 = wrap_any(k0 - 2, g.nz), km1 = wrap_any(k0 - 1, g.nz);
-    const int kp1 = wrap_any(k0 + 1, g.nz);
+    const int km2 = wrap(k0 - 2, g.nz), km1 = wrap(k0 - 1, g.nz);
+    const int kp1 = wrap(k0 + 1, g.nz);
     const RawCell rm2 = load_raw_plane<LIM, EM>(src, g, nxy, km2, km1, po);
     const RawCell rm1 = load_raw_plane<LIM, EM>(src, g, nxy, km1, k0, po);
     const RawCell rc = load_raw_plane<LIM, EM>(src, g, nxy, k0, kp1, po);
@@ -296,14 +296,13 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     bad |= !march_prim<LIM, EM>(rm2, g.gamma, Wm2);
     bad |= !march_prim<LIM, EM>(rm1, g.gamma, Wm1);
     bad |= !march_prim<LIM, EM>(rc, g.gamma, W);
-    if (cflp) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       lds[q * HL::Q + M::NCORE + t] = (R)Wm1[q];
       lds[q * HL::Q + t] = (R)W[q];
     }
     if constexpr (WZ) {  // the upper value of cell k0 - 1, from planes k0 - 3 .. k0 + 1
-      const double* const pm3 = PW + wrap_any(k0 - 3, g.nz) * nxy;
+      const double* const pm3 = PW + wrap(k0 - 3, g.nz) * nxy;
       const double* const pp1 = PW + kp1 * nxy;
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
@@ -311,7 +310,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
         zl[q] = wenoz_upper(ld_at(pm3 + sq * n, po.c), Wm2[sq], Wm1[sq], W[sq],
                             ld_at(pp1 + sq * n, po.c));
         zm2[q] = Wm2[sq];
-        zp2[q] = ld_at(PW + sq * n + wrap_any(k0 + 2, g.nz) * nxy, po.c);
+        zp2[q] = ld_at(PW + sq * n + wrap(k0 + 2, g.nz) * nxy, po.c);
       }
     } else {
 #pragma unroll
@@ -332,13 +331,25 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     }
   }
   RawCell nxt =
-      load_raw_plane<LIM, EM>(src, g, nxy, wrap_any(k0 + 1, g.nz), wrap_any(k0 + 2, g.nz), po);
+      load_raw_plane<LIM, EM>(src, g, nxy, wrap(k0 + 1, g.nz), wrap(k0 + 2, g.nz), po);
   __syncthreads();
+  double h = 0.0;
+  if (cflp) {
+    double m = L.red[0];
+#pragma unroll
+    for (int w = 1; w < M::NCORE / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
+    h = uni(cfl * m);
+    if (b == 0 && t == 0) *dt_out = h;
+  } else if (stage != 0 && stage != 3) {
+    h = uni(dtp ? *dtp : dt);
+  }
+  const RkCoef rk = rk_coef(stage, h);
+  const R ch = GLM ? uni((R)(ch0 / h)) : R(0);
   int cp = 0;  // core offset of plane k
   double acc[NF];  // minus L of the cell below, but for its upper z-flux
   R* const fw0 = reinterpret_cast<R*>(FW);
   for (int k = k0;; ++k) {
-    const int kw = wrap_any(k, g.nz);
+    const int kw = wrap(k, g.nz);
     R* const fwp = fw0 + kw * nxy;
     R wl[NW], wr[NW], psi = R(0), fpsi = R(0);
     RiemannOut<R> o;
@@ -348,7 +359,6 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     {
       double W[9];
       bad |= !march_prim<LIM, EM>(nxt, g.gamma, W);
-      if (cflp && k + 1 < k1) cmin = cfl_bound<3>(g, W, cmin);
 #pragma unroll
       for (int d = 0; d < 3; ++d) bnn[d] = WZ ? nb[d] : nxt.u[5 + d];
       const int cn = M::NCORE - cp + t;  // own cell in the other core plane: k - 1, then k + 1
@@ -380,19 +390,30 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       cell_fluxes<2, EM>(o, psi, fpsi, F);
       // the cell below is finished
       const int64_t cb = (int64_t)(k - 1) * nxy;
-      if (k > k0 && inside && stage != 3) {
+      if (k > k0 && inside) {
         const uint32_t c = here(po.c);
-        double u[NF], u0[NF];
+        auto put = [&](double* p, double v) {
+          *reinterpret_cast<double*>(reinterpret_cast<char*>(p + cb) + c) = v;
+        };
 #pragma unroll
-        for (int q = 0; q < NF; ++q) {
-          u[q] = ld_at(U + q * n + cb, c);
-          u0[q] = ld_at(U0 + q * n + cb, c);
+        for (int q = 0; q < NF; ++q) acc[q] = -(acc[q] + (double)F[q] * idz);
+        if (stage != 3) {
+          double u[NF], u0[NF];
+#pragma unroll
+          for (int q = 0; q < NF; ++q) {
+            u[q] = ld_at(U + q * n + cb, c);
+            u0[q] = ld_at(U0 + q * n + cb, c);
+          }
+#pragma unroll
+          for (int q = 0; q < NF; ++q) {
+            double v = rk_apply(rk, u[q], u0[q], acc[q]);
+            if (GLM && q == 8) v *= decay;
+            put(out + q * n, v);
+          }
         }
+        if (Lc) {
 #pragma unroll
-        for (int q = 0; q < NF; ++q) {
-          double v = rk_apply(rk, u[q], u0[q], -(acc[q] + (double)F[q] * idz));
-          if (GLM && q == 8) v *= decay;
-          *reinterpret_cast<double*>(reinterpret_cast<char*>(out + q * n + cb) + c) = v;
+          for (int q = 0; q < NF; ++q) put(Lc + q * n, acc[q]);
         }
       }
       if (k == k1) break;
@@ -400,7 +421,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       for (int q = 0; q < NF; ++q) acc[q] = -(double)F[q] * idz;
     }
     if constexpr (!GLM) put_edge<2, EM>(fwp, n, boff, o);
-    const int ka = wrap_any(k + 1, g.nz), kb = wrap_any(k + 2, g.nz), kc = wrap_any(k + 3, g.nz);
+    const int ka = wrap(k + 1, g.nz), kb = wrap(k + 2, g.nz), kc = wrap(k + 3, g.nz);
     // x-face
     {
       const int tt = here(t), xx = tt & (M::TX - 1), yy = tt / M::TX;
@@ -478,7 +499,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     nxt = load_raw_plane<LIM, EM>(src, g, nxy, kb, kc, po);
     if constexpr (WZ) {
       const uint32_t c = here(po.c);
-      const int km1 = wrap_any(k - 1, g.nz);
+      const int km1 = wrap(k - 1, g.nz);
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
         zm2[q] = ld_at(PW + zslot[q] * n + km1 * nxy, c);
@@ -517,109 +538,29 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     for (int d = 0; d < 3; ++d) bn[d] = bnn[d];
     cp = M::NCORE - cp;
   }
-  if (cflp) workgroup_min_store(cmin, cflp + blockIdx.x);
   if (bad) atomicOr(flag, 1);
 }
 
-// Update of the staggered field by -curl E (and, HYDRO, of the cell fields by
-// the L the face kernel left in Lc, whose time step was not known yet), V
-// cells along x per thread (V = 2 for an even nx: two-wide loads and stores).
-// What bounds it: HBM.
-template <int STAGE, class R, bool HYDRO, int V>
-__global__ __launch_bounds__(kBlock) void k_update_b(const double* __restrict__ U,
-                                                    const double* U0, const double* Lc,
-                                                    double* out, const double* __restrict__ EW,
-                                                    Geom g, MarchGrid tg, double dt,
-                                                    const double* __restrict__ dtp) {
-  // mixed mode (FP32 EMFs): the XCD-grouped order
-  const unsigned b = (sizeof(R) == 4) ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
-  const int tx = (int)(b % (unsigned)tg.ntx);
-  const unsigned r = b / (unsigned)tg.ntx;
-  const int ty = (int)(r % (unsigned)tg.nty);
-  const int k = (int)(r / (unsigned)tg.nty);
-  const int i = (tx * 64 + (int)threadIdx.x % 64) * V;
-  const int j = ty * 4 + (int)threadIdx.x / 64;
-  if (i >= g.nx || j >= g.ny) return;
-  typedef R RV __attribute__((ext_vector_type(V)));
-  typedef double DV __attribute__((ext_vector_type(V)));
-  const int64_t n = g.n, c = lin(g, i, j, k);
-  const double h = (STAGE == 0) ? 0.0 : (dtp ? *dtp : dt);
-  const int64_t xq = lin(g, wrap(i + V, g.nx), j, k);
-  const int64_t yp = lin(g, i, wrap(j + 1, g.ny), k), zp = lin(g, i, j, wrap(k + 1, g.nz));
-  const double idx = 1.0 / g.dx, idy = 1.0 / g.dy, idz = 1.0 / g.dz;
-  const R* ex = reinterpret_cast<const R*>(EW);
-  const R* ey = ex + n;
-  const R* ez = ex + 2 * n;
-  auto ldr = [](const R* p, int64_t q) { return *reinterpret_cast<const RV*>(p + q); };
-  auto ldd = [](const double* p, int64_t q) { return *reinterpret_cast<const DV*>(p + q); };
-  const RV xc = ldr(ex, c), xy = ldr(ex, yp), xz = ldr(ex, zp);
-  const RV yc = ldr(ey, c), yz = ldr(ey, zp);
-  const RV zc = ldr(ez, c), zy = ldr(ez, yp);
-  const R yq = ey[xq], zq = ez[xq];
-  double Lb[V][3];
-#pragma unroll
-  for (int e = 0; e < V; ++e) {
-    const double ezx = (e + 1 < V) ? (double)zc[(e + 1) % V] : (double)zq;
-    const double eyx = (e + 1 < V) ? (double)yc[(e + 1) % V] : (double)yq;
-    const double x0 = (double)xc[e], y0 = (double)yc[e], z0 = (double)zc[e];
-    Lb[e][0] = -(((double)zy[e] - z0) * idy - ((double)yz[e] - y0) * idz);
-    Lb[e][1] = -(((double)xz[e] - x0) * idz - (ezx - z0) * idx);
-    Lb[e][2] = -((eyx - y0) * idx - ((double)xy[e] - x0) * idy);
-  }
-#pragma unroll
-  for (int q = HYDRO ? 0 : 5; q < 8; ++q) {
-    DV u = {}, u0 = {}, v, lc = {};
-    if (STAGE != 0) u = ldd(U + q * n, c);
-    if (STAGE >= 2) u0 = ldd(U0 + q * n, c);
-    if (q < 5) lc = ldd(Lc + q * n, c);
-#pragma unroll
-    for (int e = 0; e < V; ++e)
-      v[e] = rk_combine(STAGE, u[e], u0[e], h, q < 5 ? lc[e] : Lb[e][q < 5 ? 0 : q - 5]);
-    *reinterpret_cast<DV*>(out + q * n + c) = v;
-  }
-}
-
 template <int LIM, int RS, class R, int EM>
-void faces_impl(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+void faces_impl(const StageArgs& a, const double* cflp, int npart) {
+  const MarchGrid mg = march_grid(a.g);
   hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM>), dim3(mg.nblocks), dim3(kBlock), 0, a.stream,
-                     a.U, a.PW, a.U0 ? a.U0 : a.U, out, a.FW, a.g, mg, stage, a.dt, a.dtp, a.flag,
-                     a.cfl_partial, a.cfl * a.glm_dmin, (stage == 2 || stage == 5) ? a.glm_decay : 1.0);
+                     a.U, a.PW, a.U0 ? a.U0 : a.U, a.out, a.FW, a.g, mg, a.stage, a.dt, a.dtp,
+                     a.flag, a.keep_rhs ? a.FW : nullptr, a.cfl * a.glm_dmin,
+                     (a.stage == 2 || a.stage == 5) ? a.glm_decay : 1.0, cflp, npart, a.cfl,
+                     a.dt_out);
 }
 template <int LIM, int RS, class R>
-void faces_em(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
-  if (a.glm) faces_impl<LIM, RS, R, 2>(a, mg, stage, out);
-  else if (a.emf == 1) faces_impl<LIM, RS, R, 1>(a, mg, stage, out);
-  else faces_impl<LIM, RS, R, 0>(a, mg, stage, out);
+void faces_em(const StageArgs& a, const double* cflp, int npart) {
+  if (a.glm) faces_impl<LIM, RS, R, 2>(a, cflp, npart);
+  else if (a.emf == 1) faces_impl<LIM, RS, R, 1>(a, cflp, npart);
+  else faces_impl<LIM, RS, R, 0>(a, cflp, npart);
 }
 template <int LIM, int RS>
-void faces_prec(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
-  if constexpr (LIM == 2) faces_em<LIM, RS, double>(a, mg, stage, out);
-  else if (a.precision == 1) faces_em<LIM, RS, float>(a, mg, stage, out);
-  else faces_em<LIM, RS, double>(a, mg, stage, out);
-}
-
-template <class R, bool HYDRO, int V>
-void update_impl(const StageArgs& a, const double* Lc) {
-  MarchGrid tg;
-  tg.ntx = (a.g.nx + 64 * V - 1) / (64 * V);
-  tg.nty = (a.g.ny + 3) / 4;
-  tg.nblocks = (unsigned)tg.ntx * (unsigned)tg.nty * (unsigned)a.g.nz;
-#define MHD_UPD(ST)                                                                           \
-  hipLaunchKernelGGL((k_update_b<ST, R, HYDRO, V>), dim3(tg.nblocks), dim3(kBlock), 0, a.stream, \
-                     a.U, a.U0, Lc, a.out, a.EW, a.g, tg, a.dt, a.dtp)
-  switch (a.stage) {
-    case 0: MHD_UPD(0); break;
-    case 1: MHD_UPD(1); break;
-    case 4: MHD_UPD(4); break;
-    case 5: MHD_UPD(5); break;
-    default: MHD_UPD(2); break;
-  }
-#undef MHD_UPD
-}
-template <class R, bool HYDRO>
-void update_v(const StageArgs& a, const double* Lc) {
-  if (a.g.nx % 2 == 0) update_impl<R, HYDRO, 2>(a, Lc);
-  else update_impl<R, HYDRO, 1>(a, Lc);
+void faces_prec(const StageArgs& a, const double* cflp, int npart) {
+  if constexpr (LIM == 2) faces_em<LIM, RS, double>(a, cflp, npart);
+  else if (a.precision == 1) faces_em<LIM, RS, float>(a, cflp, npart);
+  else faces_em<LIM, RS, double>(a, cflp, npart);
 }
 
 }  // namespace
@@ -632,7 +573,6 @@ void update_v(const StageArgs& a, const double* Lc) {
 // 233 mixed (16) and 256^3 (16: 1608, 32: 1601, 8: 1654, 4: 1742 us).
 MarchGrid march_grid(const Geom& g) {
   MarchGrid mg;
-  mg.lx = 5;
   mg.ntx = (g.nx + March::TX - 1) / March::TX;
   mg.nty = (g.ny + March::TY - 1) / March::TY;
   double best = 0.0;
@@ -650,26 +590,16 @@ MarchGrid march_grid(const Geom& g) {
   return mg;
 }
 
-void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out) {
+void launch_faces_march(const StageArgs& a, const double* cflp, int npart) {
   if (a.limiter == 2) {
-    if (a.riemann == 0) faces_prec<2, 0>(a, mg, stage, out);
-    else faces_prec<2, 1>(a, mg, stage, out);
+    if (a.riemann == 0) faces_prec<2, 0>(a, cflp, npart);
+    else faces_prec<2, 1>(a, cflp, npart);
   } else if (a.limiter == 0) {
-    if (a.riemann == 0) faces_prec<0, 0>(a, mg, stage, out);
-    else faces_prec<0, 1>(a, mg, stage, out);
+    if (a.riemann == 0) faces_prec<0, 0>(a, cflp, npart);
+    else faces_prec<0, 1>(a, cflp, npart);
   } else {
-    if (a.riemann == 0) faces_prec<1, 0>(a, mg, stage, out);
-    else faces_prec<1, 1>(a, mg, stage, out);
-  }
-}
-
-void launch_update_b(const StageArgs& a, const double* Lc) {
-  if (a.precision == 1) {
-    if (Lc) update_v<float, true>(a, Lc);
-    else update_v<float, false>(a, Lc);
-  } else {
-    if (Lc) update_v<double, true>(a, Lc);
-    else update_v<double, false>(a, Lc);
+    if (a.riemann == 0) faces_prec<1, 0>(a, cflp, npart);
+    else faces_prec<1, 1>(a, cflp, npart);
   }
 }
 

@@ -39,6 +39,16 @@ __device__ __forceinline__ T here(T v) {
   return v;
 }
 
+// A value that every lane holds alike, in scalar registers.
+__device__ __forceinline__ double uni(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float uni(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
 // The value at byte offset off of the uniform base b.
 __device__ __forceinline__ double ld_at(const double* __restrict__ b, uint32_t off) {
   return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(b) + off);
@@ -178,19 +188,11 @@ __device__ __forceinline__ void workgroup_min_store(double v, double* __restrict
   }
 }
 
-// The stages' combinations of k_update with u the state L was formed at and
-// u0 the state at the start of the step.
-__device__ __forceinline__ double rk_combine(int stage, double u, double u0, double h, double L) {
-  if (stage == 0) return L;
-  if (stage == 1) return u + h * L;
-  if (stage == 4) return (3.0 * u0 + (u + h * L)) / 4.0;
-  if (stage == 5) return (u0 + 2.0 * (u + h * L)) / 3.0;
-  return 0.5 * (u0 + (u + h * L));
-}
-
-// The same combinations by coefficients, for a stage known at run time without
-// a branch per value: (ca u0 + cb (cu u + h L)) / cd, the quotient by the
-// divisors 1, 2, 4 exact and by 3 corrected to the rounded one.
+// The stages' combinations of u, the state L was formed at, and u0, the state at
+// the start of the step: 0: L; 1: u + h L; 2: (u0 + (u + h L)) / 2; 4: (3 u0 + (u +
+// h L)) / 4; 5: (u0 + 2 (u + h L)) / 3. By coefficients, for a stage known at run
+// time without a branch per value: (ca u0 + cb (cu u + h L)) / cd, the quotient by
+// the divisors 1, 2, 4 exact and by 3 corrected to the rounded one.
 struct RkCoef {
   double cu, h, ca, cb, cc, cd;
 };

@@ -1,19 +1,21 @@
 // HIP kernels of the ideal-MHD step for gfx950, and their launchers.
 //
-// One stage in 3D with CT is three launches: the z-marching face kernel of
-// mhd_faces3d.hpp, which finishes the cell-averaged fields; k_emf_march, per cell
-// the upwind CT EMF on its lower edges; the update of the staggered field. GLM
+// One stage in 3D with CT is two launches: the z-marching face kernel of
+// mhd_faces3d.hpp, which finishes the cell-averaged fields, and that of mhd_ct3d.hpp,
+// the upwind CT EMFs on the cells' edges and the update of the staggered field. GLM
 // stages are the face kernel alone; WENO-Z ones recover every cell's primitives
 // first (k_prim). In 2D a stage is one kernel (mhd_stage2d.hpp), except for the
 // adjoint's, which keep their records. The CFL time step is a per-cell minimum
 // reduced with wave64 shuffles and a block LDS step into per-block partials (by
-// a kernel of the step itself where it recovers every cell's primitives anyway),
-// then one finishing block.
+// a kernel of the step itself where it recovers every cell's primitives anyway);
+// on small grids every workgroup of the first stage reduces these, else one block
+// does.
 //
 // Layout: state and workspace arrays are field-major SoA, x fastest, so a
 // wavefront of 64 consecutive cells reads 512 contiguous bytes per field.
 #include <mutex>
 
+#include "mhd_ct3d.hpp"
 #include "mhd_device.hpp"
 #include "mhd_faces3d.hpp"
 #include "mhd_grid.hpp"
@@ -23,175 +25,6 @@
 namespace mhd {
 
 namespace {
-
-// 3D EMF kernel marching along z over 64 x 4 columns: the inputs of E_x and
-// E_y that are offset along z (alpha+- of the y- and x-faces one plane down,
-// v and b on those faces two planes down to one up) ride in registers from
-// plane to plane, so each is loaded once per run instead of up to four times.
-struct EmfCol {
-  static constexpr int NT = 256;  // workgroup size: 64 x 4 or 32 x 8 columns
-};
-constexpr int kEmfRun = 16;  // planes per run (8 and 32 measured no faster at 256^3)
-
-// The coefficients of one face the edge average takes: alpha+ and alpha-
-// (EM 0), or the UCT-HLLD weight and diffusion coefficients (EM 1).
-template <int EM, class R>
-struct FaceCoef {
-  R c[EM == 1 ? 3 : 2];
-};
-template <int EM, class R>
-__device__ __forceinline__ FaceCoef<EM, R> face_coef(const R* f, int64_t n, int64_t c) {
-  FaceCoef<EM, R> o;
-  o.c[0] = f[S_AP * n + c];
-  o.c[1] = f[S_AM * n + c];
-  if constexpr (EM == 1) o.c[2] = f[S_DR * n + c];
-  return o;
-}
-// Edge EMF from the coefficients of the a-faces (below the edge along B,
-// then the cell's own) and b-faces, and the reconstructed values.
-template <int LIM, int EM, class R>
-__device__ __forceinline__ R emf_from(const FaceCoef<EM, R>& am, const FaceCoef<EM, R>& ac,
-                                      const FaceCoef<EM, R>& bm, const FaceCoef<EM, R>& bc,
-                                      const R* vbA, const R* bB, const R* vaB, const R* bA) {
-  if constexpr (EM == 1)
-    return emf_core_hlld<LIM, R>(am.c[0], ac.c[0], am.c[1], ac.c[1], am.c[2], ac.c[2], bm.c[0],
-                                 bc.c[0], bm.c[1], bc.c[1], bm.c[2], bc.c[2], vbA, bB, vaB, bA);
-  else
-    return emf_core<LIM, R>(am.c[0], ac.c[0], am.c[1], ac.c[1], bm.c[0], bc.c[0], bm.c[1],
-                            bc.c[1], vbA, bB, vaB, bA);
-}
-
-template <int LIM, class R, int EM>
-__device__ __forceinline__ void emf_march(const double* __restrict__ U,
-                                          const double* __restrict__ FW, double* __restrict__ EW,
-                                          Geom g, MarchGrid mg) {
-  // mixed mode: the XCD-grouped order (0.523 -> 0.513 ms at 256^3; FP64 unchanged)
-  const unsigned b = (sizeof(R) == 4) ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
-  const int tx = (int)(b % (unsigned)mg.ntx);
-  const unsigned r = b / (unsigned)mg.ntx;
-  const int ty = (int)(r % (unsigned)mg.nty);
-  const int zc = (int)(r / (unsigned)mg.nty);
-  const int i = (tx << mg.lx) + ((int)threadIdx.x & ((1 << mg.lx) - 1));
-  const int j = ty * (EmfCol::NT >> mg.lx) + ((int)threadIdx.x >> mg.lx);
-  if (i >= g.nx || j >= g.ny) return;
-  const int k0 = zc * mg.lz;
-  const int k1 = min(k0 + mg.lz, g.nz);
-  const int64_t n = g.n;
-  const R* fx = stored<R>(FW);
-  const R* fy = fx + (int64_t)NSLOT * n;
-  const R* fz = fx + (int64_t)2 * NSLOT * n;
-  R* ew = stored<R>(EW);
-  const double* bx = U + F_BX * n;
-  const double* by = U + F_BY * n;
-  const double* bz = U + F_BZ * n;
-  // planes k-2 .. k+1 of this column: v_z on y-faces and b_y (E_x), v_z on
-  // x-faces and b_x (E_y); the coefficients of y- and x-faces on planes k-1, k
-  R yv[4], yb[4], xv[4], xb[4];
-  FaceCoef<EM, R> yc[2], xc[2];
-#pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int64_t cs = lin(g, i, j, wrap_any(k0 - 2 + s, g.nz));
-    yv[s] = fy[S_V1 * n + cs];
-    yb[s] = (R)by[cs];
-    xv[s] = fx[S_V2 * n + cs];
-    xb[s] = (R)bx[cs];
-  }
-  {
-    const int64_t cm = lin(g, i, j, wrap_any(k0 - 1, g.nz));
-    yc[0] = face_coef<EM, R>(fy, n, cm);
-    xc[0] = face_coef<EM, R>(fx, n, cm);
-  }
-  const int im2 = wrap(i - 2, g.nx), im1 = wrap(i - 1, g.nx), ip1 = wrap(i + 1, g.nx);
-  const int jm2 = wrap(j - 2, g.ny), jm1 = wrap(j - 1, g.ny), jp1 = wrap(j + 1, g.ny);
-  for (int k = k0; k < k1; ++k) {
-    const int64_t c = lin(g, i, j, k);
-    const int64_t cp = lin(g, i, j, wrap(k + 1, g.nz));
-    const int64_t cjm2 = lin(g, i, jm2, k), cjm1 = lin(g, i, jm1, k), cjp1 = lin(g, i, jp1, k);
-    const int64_t cim2 = lin(g, im2, j, k), cim1 = lin(g, im1, j, k), cip1 = lin(g, ip1, j, k);
-    // all loads of this plane first (face records in R, staggered fields in
-    // FP64), then the conversions to R: the loads stay in flight together
-    const R* vz2 = fz + S_V2 * n;
-    const R* vz1 = fz + S_V1 * n;
-    R r[14];
-    double d[9];
-    r[0] = fy[S_V1 * n + cp]; r[1] = fx[S_V2 * n + cp];
-    yc[1] = face_coef<EM, R>(fy, n, c);
-    xc[1] = face_coef<EM, R>(fx, n, c);
-    r[6] = vz2[cjm2]; r[7] = vz2[cjm1]; r[8] = vz2[c]; r[9] = vz2[cjp1];
-    r[10] = vz1[cim2]; r[11] = vz1[cim1]; r[12] = vz1[c]; r[13] = vz1[cip1];
-    const FaceCoef<EM, R> zjm = face_coef<EM, R>(fz, n, cjm1);
-    const FaceCoef<EM, R> zc0 = face_coef<EM, R>(fz, n, c);
-    const FaceCoef<EM, R> zim = face_coef<EM, R>(fz, n, cim1);
-    d[0] = by[cp]; d[1] = bx[cp];
-    d[2] = bz[cjm2]; d[3] = bz[cjm1]; d[4] = bz[c]; d[5] = bz[cjp1];
-    d[6] = bz[cim2]; d[7] = bz[cim1]; d[8] = bz[cip1];
-    // E_z: (A, B) = (x, y); its inputs are loaded here too, so that no load
-    // of the plane is issued after one of its EMF stores (the wait for it
-    // would then wait for the store as well)
-    const FaceCoef<EM, R> xjm = face_coef<EM, R>(fx, n, cjm1);
-    const FaceCoef<EM, R> yim = face_coef<EM, R>(fy, n, cim1);
-    const R* vyx = fy + S_V2 * n;  // v_x on y-faces
-    const R* vxy = fx + S_V1 * n;  // v_y on x-faces
-    const R zwv[4] = {vyx[cim2], vyx[cim1], vyx[c], vyx[cip1]};
-    const R zsv[4] = {vxy[cjm2], vxy[cjm1], vxy[c], vxy[cjp1]};
-    const double zwd[4] = {by[cim2], by[cim1], by[c], by[cip1]};
-    const double zsd[4] = {bx[cjm2], bx[cjm1], bx[c], bx[cjp1]};
-    // keep the scheduler from sinking loads into the arithmetic (the minmod
-    // FP64 instantiation otherwise waited for its loads one or two at a time)
-    __builtin_amdgcn_sched_barrier(0);
-    yv[3] = r[0];
-    yb[3] = (R)d[0];
-    xv[3] = r[1];
-    xb[3] = (R)d[1];
-    // E_x: (A, B) = (y, z); a-faces are y-faces, b-faces z-faces
-    R ex, ey, ez;
-    {
-      const R wv[4] = {r[6], r[7], r[8], r[9]};
-      const R wb[4] = {(R)d[2], (R)d[3], (R)d[4], (R)d[5]};
-      ex = emf_from<LIM, EM, R>(yc[0], yc[1], zjm, zc0, wv, wb, yv, yb);
-    }
-    // E_y: (A, B) = (z, x); a-faces are z-faces, b-faces x-faces
-    {
-      const R sv[4] = {r[10], r[11], r[12], r[13]};
-      const R sb[4] = {(R)d[6], (R)d[7], (R)d[4], (R)d[8]};
-      ey = emf_from<LIM, EM, R>(zim, zc0, xc[0], xc[1], xv, xb, sv, sb);
-    }
-    // E_z: a-faces are x-faces, b-faces y-faces
-    {
-      const R wb[4] = {(R)zwd[0], (R)zwd[1], (R)zwd[2], (R)zwd[3]};
-      const R sb[4] = {(R)zsd[0], (R)zsd[1], (R)zsd[2], (R)zsd[3]};
-      ez = emf_from<LIM, EM, R>(xjm, xc[1], yim, yc[1], zwv, wb, zsv, sb);
-    }
-    ew[c] = ex;
-    ew[n + c] = ey;
-    ew[2 * n + c] = ez;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      yv[s] = yv[s + 1];
-      yb[s] = yb[s + 1];
-      xv[s] = xv[s + 1];
-      xb[s] = xb[s + 1];
-    }
-    yc[0] = yc[1];
-    xc[0] = xc[1];
-  }
-}
-
-// The upwind (EM 0) kernel is held to two waves per SIMD, where it keeps all
-// its loads of a plane in flight without spilling; the UCT-HLLD kernel (EM 1)
-// needs more registers and runs at one.
-template <int LIM, class R>
-__global__ __launch_bounds__(EmfCol::NT) __attribute__((amdgpu_waves_per_eu(2)))
-void k_emf_march(const double* __restrict__ U, const double* __restrict__ FW,
-                 double* __restrict__ EW, Geom g, MarchGrid mg) {
-  emf_march<LIM, R, 0>(U, FW, EW, g, mg);
-}
-template <int LIM, class R>
-__global__ __launch_bounds__(EmfCol::NT)
-void k_emf_march_hlld(const double* __restrict__ U, const double* __restrict__ FW,
-                      double* __restrict__ EW, Geom g, MarchGrid mg) {
-  emf_march<LIM, R, 1>(U, FW, EW, g, mg);
-}
 
 // ---------------------------------------------------------------------------
 // The adjoint's 2D stages, which keep their records (FP64, the HLL average; the
@@ -519,42 +352,6 @@ __global__ __launch_bounds__(1024) void k_cfl_final(const double* __restrict__ p
   }
 }
 
-// Columns and runs of the EMF march: 32 x 8 columns where 64 x 4 ones would
-// leave more lanes past the grid; runs of 16 planes, shorter where those
-// would not give every CU its two workgroups.
-MarchGrid emf_grid(const Geom& g) {
-  MarchGrid mg;
-  const int w64 = (g.nx + 63) / 64 * 64, w32 = (g.nx + 31) / 32 * 32;
-  mg.lx = (w32 < w64) ? 5 : 6;
-  const int TX = 1 << mg.lx, TY = EmfCol::NT / TX;
-  mg.ntx = (g.nx + TX - 1) / TX;
-  mg.nty = (g.ny + TY - 1) / TY;
-  mg.lz = g.nz < kEmfRun ? g.nz : kEmfRun;
-  while (mg.lz > 1 && (int64_t)mg.ntx * mg.nty * ((g.nz + mg.lz - 1) / mg.lz) < 512) mg.lz /= 2;
-  mg.nzc = (g.nz + mg.lz - 1) / mg.lz;
-  mg.nblocks = (unsigned)mg.ntx * (unsigned)mg.nty * (unsigned)mg.nzc;
-  return mg;
-}
-
-template <int LIM, class R, int EM>
-void launch_emf_march(const StageArgs& a) {
-  const MarchGrid eg = emf_grid(a.g);
-  if constexpr (EM == 1)
-    MHD_TIMED(a, K_EMF,
-              hipLaunchKernelGGL((k_emf_march_hlld<LIM, R>), dim3(eg.nblocks), dim3(EmfCol::NT), 0,
-                                 a.stream, a.U, a.FW, a.EW, a.g, eg));
-  else
-    MHD_TIMED(a, K_EMF,
-              hipLaunchKernelGGL((k_emf_march<LIM, R>), dim3(eg.nblocks), dim3(EmfCol::NT), 0,
-                                 a.stream, a.U, a.FW, a.EW, a.g, eg));
-}
-
-template <int LIM, class R>
-void launch_emf(const StageArgs& a) {
-  if (a.emf == 1) launch_emf_march<LIM, R, 1>(a);
-  else launch_emf_march<LIM, R, 0>(a);
-}
-
 // The adjoint's 2D stages (stage 1 and 4, or 3: records only), FP64 with the HLL
 // average: face records in FW, E_z in EW.
 template <int LIM, int RS>
@@ -582,9 +379,9 @@ hipError_t records_2d(const StageArgs& a) {
 
 }  // namespace
 
-size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm) {
-  if (glm || limiter == 2) return (size_t)((g.n + kBlock - 1) / kBlock);
-  return march_grid(g).nblocks;
+size_t stage_cfl_blocks(const Geom& g, int limiter) {
+  const size_t nl = (size_t)((g.n + kBlock - 1) / kBlock);
+  return limiter == 2 || nl < kCfl3d ? nl : kCfl3d;
 }
 
 namespace {
@@ -605,45 +402,40 @@ void cfl_final(const A& a, const double* partial, int np) {
                                a.dt_out));
 }
 
-// 3D stage. WENO-Z: the primitives of every cell first. Then the face kernel,
-// which finishes the cell-averaged fields itself; with CT the EMFs and the
-// update of the staggered field. A time step that is the CFL bound of U is known
-// before the faces with WENO-Z (from the primitive kernel) and GLM (whose c_h
-// needs it: from a pass over U), and only after them with PLM and CT, where they
-// reduce it: there, or where L(U) is wanted beside the state, the face kernel
-// leaves L and the update finishes all eight fields.
+// Partials of the grid-stride CFL pass: at most most, as many as blocks of cells.
+int cfl_parts(const Geom& g, int most) {
+  const int64_t need = (g.n + kBlock - 1) / kBlock;
+  return (int)(need < most ? need : most);
+}
+
+// 3D stage. WENO-Z: the primitives of every cell first. A time step that is the
+// CFL bound of U: from those, or from a pass over U. Then the face kernel, which
+// finishes the cell-averaged fields itself, and with CT the EMFs and the update of
+// the staggered field.
+//
+// (With PLM and CT the face kernel once reduced the CFL bound itself, and as its
+// state then had to wait for the next kernel, L was written and read back instead
+// of U read once more: 256^3 5.18 -> 4.95 ms a step without, 384^3 mixed 12.0 ->
+// 10.9.)
 hipError_t stage3d(const StageArgs& a) {
-  const MarchGrid mg = march_grid(a.g);
-  StageArgs f = a;
+  const double* cflp = a.cfl_partial;
+  int np = 0;
   if (a.limiter == 2) {
     if (!a.PW || a.precision == 1) return hipErrorInvalidValue;
-    const unsigned nl = (unsigned)((a.g.n + kBlock - 1) / kBlock);
+    np = (int)((a.g.n + kBlock - 1) / kBlock);
     MHD_TIMED(a, K_PRIM,
-              hipLaunchKernelGGL(a.glm ? k_prim<true> : k_prim<false>, dim3(nl), dim3(kBlock), 0,
+              hipLaunchKernelGGL(a.glm ? k_prim<true> : k_prim<false>, dim3(np), dim3(kBlock), 0,
                                  a.stream, a.U, a.PW, a.g, a.flag, a.cfl_partial));
-    if (a.cfl_partial) cfl_final(a, a.cfl_partial, (int)nl);
-    f.cfl_partial = nullptr;
-  } else if (a.glm && a.cfl_partial) {
-    const int64_t need = (a.g.n + kBlock - 1) / kBlock;
-    const int np = (int)(need < 2048 ? need : 2048);
+  } else if (cflp) {
+    np = cfl_parts(a.g, kCfl3d);
     cfl_pass(a, a.cfl_partial, np, a.flag);
-    cfl_final(a, a.cfl_partial, np);
-    f.cfl_partial = nullptr;
   }
-  const bool late = f.cfl_partial || a.keep_rhs;
-  double* Lc = f.cfl_partial ? a.out : a.FW;  // FW: slots S_RHO .. S_EN of direction 0
-  MHD_TIMED(a, K_FACES, launch_faces_march(f, mg, late ? 0 : a.stage, late ? Lc : a.out));
-  if (f.cfl_partial) cfl_final(a, a.cfl_partial, (int)mg.nblocks);
-  if (a.glm) return hipGetLastError();
-  // (WENO-Z takes van Leer PLM for the CT edge values)
-  if (a.precision == 1) {
-    if (a.limiter == 0) launch_emf<0, float>(a);
-    else launch_emf<1, float>(a);
-  } else {
-    if (a.limiter == 0) launch_emf<0, double>(a);
-    else launch_emf<1, double>(a);
+  if (cflp && (np > (int)kCfl3d || march_grid(a.g).nblocks > kInlineCfl3d)) {
+    cfl_final(a, cflp, np);
+    cflp = nullptr;
   }
-  if (a.stage != 3) MHD_TIMED(a, K_UPDATE, launch_update_b(a, late ? Lc : nullptr));
+  MHD_TIMED(a, K_FACES, launch_faces_march(a, cflp, np));
+  if (!a.glm && (a.stage != 3 || a.keep_rhs)) MHD_TIMED(a, K_EMF, launch_ct(a));
   return hipGetLastError();
 }
 
@@ -655,8 +447,7 @@ hipError_t stage2d(const StageArgs& a) {
   const double* cflp = a.cfl_prev;
   int np = a.ncfl;
   if (a.cfl_partial && !cflp) {
-    const int64_t need = (a.g.n + kBlock - 1) / kBlock;
-    np = (int)(need < kInlineCfl2d ? need : kInlineCfl2d);
+    np = cfl_parts(a.g, kInlineCfl2d);
     cflp = a.cfl_partial;
     cfl_pass(a, a.cfl_partial, np, a.flag);
   }

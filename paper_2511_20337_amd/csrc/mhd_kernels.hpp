@@ -39,15 +39,15 @@ struct StageArgs {
   int* flag;              // sticky unphysical flag
   hipStream_t stream;
   Timer* timer;           // nullable
-  // 3D stage 1 only, optional: the face kernel (with WENO-Z, the primitive
-  // kernel) also reduces the CFL bound of U
-  // into cfl_partial (stage_cfl_blocks(g, limiter) doubles), and *dt_out = cfl * min
-  // is written before the update reads dtp (which then must be dt_out)
+  // stage 1 only, optional: dt is the CFL bound of U, whose partials go to
+  // cfl_partial (stage_cfl_blocks doubles in 3D, kInlineCfl2d in 2D); *dt_out =
+  // cfl * min is written before anything reads dtp (which then must be dt_out)
   double* cfl_partial;
   double cfl;
   double* dt_out;
-  // 3D PLM only: L(U) of the five cell-averaged fields is left in FW (n
-  // doubles each from its start, space no edge input uses) besides
+  // 3D with CT only: L(U) is left besides, of the five cell-averaged fields in FW
+  // (n doubles each from its start, space no edge input uses), of the staggered
+  // ones in EW
   bool keep_rhs;
   // 2D only: the stage's face records and E_z in FW and EW (the adjoint
   // reads them)
@@ -61,10 +61,9 @@ struct StageArgs {
   int ncfl;
 };
 
-// Column tiles in x, y (of 1 << lx cells along x, where that varies) and runs
-// of lz planes along z.
+// Column tiles in x, y and runs of lz planes along z.
 struct MarchGrid {
-  int ntx, nty, nzc, lz, lx;
+  int ntx, nty, nzc, lz;
   unsigned nblocks;
 };
 
@@ -90,16 +89,20 @@ struct CflArgs {
   } while (0)
 
 hipError_t launch_stage(const StageArgs& a);
-// number of CFL partials the 3D face kernel (WENO-Z, GLM: primitive kernel)
-// writes (one per workgroup)
-size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm);
+// number of CFL partials of a 3D stage (WENO-Z: one per block of the primitive
+// kernel, else of a grid-stride pass)
+size_t stage_cfl_blocks(const Geom& g, int limiter);
+constexpr size_t kCfl3d = 2048;
+// 3D: on grids of at most this many workgroups of the face kernel each reduces the
+// partials itself, if there are at most kCfl3d.
+constexpr unsigned kInlineCfl3d = 1024;
 // the CFL time step of U
 hipError_t launch_cfl(const CflArgs& a);
-// 3D face kernel (stage 3: edge inputs only) and the update that follows
-// the EMFs (Lc: the cell fields' L where they are not finished yet, or null).
+// 3D face kernel (stage 3: edge inputs only; cflp: npart CFL partials, or null:
+// a.dtp or a.dt), and with CT the EMFs and the update of the staggered field.
 MarchGrid march_grid(const Geom& g);
-void launch_faces_march(const StageArgs& a, const MarchGrid& mg, int stage, double* out);
-void launch_update_b(const StageArgs& a, const double* Lc);
+void launch_faces_march(const StageArgs& a, const double* cflp, int npart);
+void launch_ct(const StageArgs& a);
 // 2D stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart);
 int stage_2d_tiles(const Geom& g, int limiter, int emf, int precision, bool glm);

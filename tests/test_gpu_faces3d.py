@@ -1,5 +1,5 @@
-"""The 3D face kernel at the sizes where its columns (32 x 8 cells), the
-faces solved above them and its runs along z can go wrong, against the oracle:
+"""The 3D face and CT kernels at the sizes where their columns (32 x 8 and 31 x 7
+cells), the faces solved above them and their runs along z can go wrong, against the oracle:
 FP64 to the repository's 1e-12 per field, mixed precision to the mixed path's
 stated 2e-5."""
 import numpy as np
@@ -36,8 +36,7 @@ def test_columns_and_runs(grid, scheme):
     c = O.cfg_from(s)
     err = rel_err(ctx.rhs(U).cpu().numpy(), O.rhs(c, U0))
     assert (err <= tol).all(), err
-    # dt inside the step (its update finishes the cell fields) and beforehand
-    # (the face kernel does): the same bits
+    # dt inside the step and beforehand: the same bits
     Ub, dts = U.clone(), []
     for _ in range(2):
         ctx.step_cfl(U)

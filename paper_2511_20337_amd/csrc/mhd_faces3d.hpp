@@ -543,7 +543,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
 
 template <int LIM, int RS, class R, int EM>
 void faces_impl(const StageArgs& a, const double* cflp, int npart) {
-  const MarchGrid mg = march_grid(a.g);
+  const MarchGrid mg = march_grid(a.g, a.limiter);
   hipLaunchKernelGGL((k_faces_march<LIM, RS, R, EM>), dim3(mg.nblocks), dim3(kBlock), 0, a.stream,
                      a.U, a.PW, a.U0 ? a.U0 : a.U, a.out, a.FW, a.g, mg, a.stage, a.dt, a.dtp,
                      a.flag, a.keep_rhs ? a.FW : nullptr, a.cfl * a.glm_dmin,
@@ -565,22 +565,25 @@ void faces_prec(const StageArgs& a, const double* cflp, int npart) {
 
 }  // namespace
 
-// Planes per run: a run costs about two planes more (its prologue and the
-// z-faces above it), a longer one leaves fewer workgroups, of which two fit on
-// each of the 256 CUs. The power of two up to 16 that minimises (runs per slot
-// + 1/2) (planes + 2) is within 2 % of the best measured of 1 .. 64 at 32^3
-// (1: 19.5 us a launch, 16: 137), 150 x 131 x 97 (8: 196, 4: 213), 301 x 200 x
-// 233 mixed (16) and 256^3 (16: 1608, 32: 1601, 8: 1654, 4: 1742 us).
-MarchGrid march_grid(const Geom& g) {
+// Planes per run: a run costs about a plane more (its prologue and the z-faces above
+// it; less of one with WENO-Z, whose primitives are there), a longer one leaves fewer
+// workgroups, of which two fit on each of the 256 CUs. The power of two up to 16 that
+// minimises (runs per slot + 0.4) (planes + extra), the longer of two that differ by
+// less than 2 %. Measured, us a launch: 32^3 1: 17, 2: 23, 4: 38; 64^3 1: 46, 2: 40, 4:
+// 45; 150 x 131 x 97 1: 243, 2: 214, 4: 193, 8: 185; 60 x 50 x 40 WENO-Z 1: 51, 2: 56,
+// 4: 59; 60 x 64 x 27 WENO-Z with GLM 1: 41, 2: 44, 4: 69; 256^3 4: 1742, 8: 1654, 16:
+// 1608, 32: 1601.
+MarchGrid march_grid(const Geom& g, int limiter) {
   MarchGrid mg;
   mg.ntx = (g.nx + March::TX - 1) / March::TX;
   mg.nty = (g.ny + March::TY - 1) / March::TY;
+  const double extra = limiter == 2 ? 0.6 : 1.0;
   double best = 0.0;
   mg.lz = 0;
   for (int lz = 16; lz >= 1; lz /= 2) {
     const int64_t nb = (int64_t)mg.ntx * mg.nty * ((g.nz + lz - 1) / lz);
-    const double t = ((double)nb / 512.0 + 0.5) * (lz + 2.0);
-    if (mg.lz == 0 || t < 0.97 * best) {
+    const double t = ((double)nb / 512.0 + 0.4) * (lz + extra);
+    if (mg.lz == 0 || t < 0.98 * best) {
       best = t;
       mg.lz = lz;
     }

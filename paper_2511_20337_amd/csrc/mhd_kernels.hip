@@ -430,7 +430,7 @@ hipError_t stage3d(const StageArgs& a) {
     np = cfl_parts(a.g, kCfl3d);
     cfl_pass(a, a.cfl_partial, np, a.flag);
   }
-  if (cflp && (np > (int)kCfl3d || march_grid(a.g).nblocks > kInlineCfl3d)) {
+  if (cflp && (np > (int)kCfl3d || march_grid(a.g, a.limiter).nblocks > kInlineCfl3d)) {
     cfl_final(a, cflp, np);
     cflp = nullptr;
   }

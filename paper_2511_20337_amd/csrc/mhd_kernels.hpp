@@ -100,7 +100,7 @@ constexpr unsigned kInlineCfl3d = 1024;
 hipError_t launch_cfl(const CflArgs& a);
 // 3D face kernel (stage 3: edge inputs only; cflp: npart CFL partials, or null:
 // a.dtp or a.dt), and with CT the EMFs and the update of the staggered field.
-MarchGrid march_grid(const Geom& g);
+MarchGrid march_grid(const Geom& g, int limiter);
 void launch_faces_march(const StageArgs& a, const double* cflp, int npart);
 void launch_ct(const StageArgs& a);
 // 2D stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).

@@ -45,7 +45,7 @@ def log(*a):
 #  flops: operations of the method's definition in those phases (add/sub, mul,
 #         div, sqrt one each), counted by oracle/count_flops.py on the initial
 #         state of this workload at 256^3 (3D turbulence, van Leer, HLLD);
-#  bytes: the state it must read once, 64 B; the face records it writes are an
+#  bytes: the state it must read once, 64 B; the edge inputs it writes are an
 #         artefact of splitting the stage into kernels, not algorithmic traffic.
 # The kernel's roof is the slower of the two: flops at the vector peak of the
 # arithmetic's precision (FP64 78.6 TFLOP/s; FP32 157.3 in the mixed mode) or
@@ -55,17 +55,17 @@ FACE_BYTES = 64
 FP32_PEAK = 157.3e12
 # HBM bytes per cell of one face-kernel launch, rocprofv3 FETCH_SIZE x 2.0 and
 # WRITE_SIZE x 1.0 (the copy-kernel calibration), for the kernel as it stands.
-FACE_TRAFFIC = {"fp64": 189.0 + 216.0, "mixed": 190.0 + 108.0}
+FACE_TRAFFIC = {"fp64": 250.4 + 136.0, "mixed": 262.0 + 88.0}
 # HBM bytes per cell of one whole step, the same counters summed over its
-# launches (two of faces and EMF, the updates of both stages): what the
-# three-kernel stage moves beside the 320 algorithmic bytes.
-STEP_TRAFFIC = {"fp64": 1984.7, "mixed": 1320.4}
+# launches (the CFL pass, two of faces and CT): what the two-kernel stage
+# moves beside the 320 algorithmic bytes.
+STEP_TRAFFIC = {"fp64": 1271.5, "mixed": 1120.9}
 # WENO-Z face kernel on the 3D Orszag-Tang problem (FP64, HLLD): algorithmic
 # flops per cell of the oracle's face phase on that workload at 256^3 (count_flops.py;
 # its textbook WENO-Z with seven divisions per value, each one flop), and the
 # HBM bytes per cell counted at 352^3 (reads past L2 x2.0, writes x1.0).
 WENO_FACE_FLOPS = 4039.4
-WENO_FACE_TRAFFIC = 339.8 + 240.0
+WENO_FACE_TRAFFIC = 412.6 + 160.0
 
 
 def face_roofline(kt, ncell, precision="fp64"):

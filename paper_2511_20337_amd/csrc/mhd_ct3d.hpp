@@ -11,8 +11,8 @@
 // and the coefficients one plane down, ride in registers. The next plane's loads
 // are on the way while this one's EMFs are formed.
 //
-// What bounds it: HBM (256^3 FP64: 3.1 GB in 0.69 ms with U0, 4.5 TB/s of the
-// 4.76 a large copy reaches). Measured against the two kernels it replaces (EMFs to
+// What bounds it: HBM (256^3 FP64 with U0: 227 B per cell counted, 168 of them
+// needed, 4.6 TB/s; a large copy reaches 4.76). Measured against the two kernels it replaces (EMFs to
 // memory, 0.65 ms; the update that read them back, 0.31 ms, 0.56 where it also
 // finished the cell fields): 256^3 0.79 ms a stage, 384^3 mixed 2.68 -> 1.73, 352^3
 // UCT-HLLD 2.65 -> 2.25. Choices:

@@ -8,14 +8,14 @@
 // every flux the column's cells need is at hand: only the inputs of the edge
 // EMFs (alpha+- or the UCT-HLLD coefficients, two velocities: 12 or 15 values
 // per cell) go to memory, and the five flux divergences end in the new state
-// (or L) directly. A face solved twice gives the same bits both times.
+// directly. A face solved twice gives the same bits both times.
 //
 // With GLM cleaning (nine cell-centred fields, no edge EMFs) this kernel is the
 // whole stage. WENO-Z reads the primitives k_prim left: its stencil is three
 // cells either way, and recovering them again at each plane's halo cost more.
 //
-// What bounds it: the instruction count (2250 per cell at 256^3 in FP64, the
-// vector units 71 % busy). Measured against the split it replaces (a face
+// What bounds it: the instruction count (1860 per cell at 256^3 in FP64, the
+// vector units 67 % busy; WENO-Z 3470 and 75 %). Measured against the split it replaces (a face
 // kernel that stored the fluxes, 27 values per cell, and an update that read
 // them back): faces 1.52 -> 1.60 ms, update 0.96 -> 0.43 ms per launch at 256^3
 // in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms; with GLM (before:

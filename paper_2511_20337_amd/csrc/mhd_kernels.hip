@@ -242,22 +242,6 @@ __global__ __launch_bounds__(RowTile::NT) void k_emf_update_2d(const double* __r
   }
 }
 
-// Cell of this thread when each workgroup of kBlock threads takes kBlock
-// consecutive cells in storage order (x fastest; workgroups in the
-// XCD-grouped order of xcd_grouped), so that no lane idles
-// whatever nx is (row tiles of 64 leave 8% of the lanes idle at nx = 352).
-// The configuration check keeps n below 2^32.
-__device__ __forceinline__ bool linear_cell(const Geom& g, int& i, int& j, int& k, int64_t& c) {
-  const uint32_t t = xcd_grouped(blockIdx.x, gridDim.x) * (uint32_t)kBlock + threadIdx.x;
-  if ((int64_t)t >= g.n) return false;
-  const uint32_t r = t / (uint32_t)g.nx;
-  i = (int)(t - r * (uint32_t)g.nx);
-  k = (int)(r / (uint32_t)g.ny);
-  j = (int)(r - (uint32_t)k * (uint32_t)g.ny);
-  c = t;
-  return true;
-}
-
 // Primitives (rho, v_x, v_y, v_z, p, B_x, B_y, B_z, psi) of cell c of a GLM
 // state; false for an unphysical one.
 __device__ __forceinline__ bool glm_prim(const double* __restrict__ U, int64_t n, int64_t c,
@@ -430,11 +414,14 @@ hipError_t stage3d(const StageArgs& a) {
     np = cfl_parts(a.g, kCfl3d);
     cfl_pass(a, a.cfl_partial, np, a.flag);
   }
-  if (cflp && (np > (int)kCfl3d || march_grid(a.g, a.limiter).nblocks > kInlineCfl3d)) {
+  const bool cells = a.limiter == 2 && a.g.n < kCellsWeno;
+  if (cflp && (cells || np > (int)kCfl3d ||
+               march_grid(a.g, a.limiter).nblocks > kInlineCfl3d)) {
     cfl_final(a, cflp, np);
     cflp = nullptr;
   }
-  MHD_TIMED(a, K_FACES, launch_faces_march(a, cflp, np));
+  if (cells) launch_faces_cells(a);
+  else MHD_TIMED(a, K_FACES, launch_faces_march(a, cflp, np));
   if (!a.glm && (a.stage != 3 || a.keep_rhs)) MHD_TIMED(a, K_EMF, launch_ct(a));
   return hipGetLastError();
 }

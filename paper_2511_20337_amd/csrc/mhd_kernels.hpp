@@ -102,6 +102,9 @@ hipError_t launch_cfl(const CflArgs& a);
 // a.dtp or a.dt), and with CT the EMFs and the update of the staggered field.
 MarchGrid march_grid(const Geom& g, int limiter);
 void launch_faces_march(const StageArgs& a, const double* cflp, int npart);
+// The same for WENO-Z on grids of fewer cells than this (dt: a.dtp or a.dt).
+void launch_faces_cells(const StageArgs& a);
+constexpr int64_t kCellsWeno = 1500000;
 void launch_ct(const StageArgs& a);
 // 2D stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart);

@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 
 # one column; a column and one cell, or one row, more; a cell and a row less;
 # the smallest grid; more than one plane per run, the last run shorter
+# (the last: WENO-Z marches from 1.5 million cells on)
 GRIDS = [(32, 8, 4), (33, 9, 5), (31, 7, 6), (4, 4, 4), (64, 16, 9), (5, 40, 4), (65, 17, 709)]
 
 
-@pytest.mark.parametrize("grid", GRIDS)
+@pytest.mark.parametrize("grid", GRIDS + [(65, 33, 707)])
 @pytest.mark.parametrize("scheme", ["hlld", "hll_uct_hlld", "hlld_uct_hlld_rk3", "mixed_rk3",
                                     "hll_wenoz_uct_hlld_rk3", "hlld_wenoz"])
 def test_columns_and_runs(grid, scheme):
@@ -53,7 +54,7 @@ def test_columns_and_runs(grid, scheme):
         assert abs(got[q].sum() - U0[q].sum()) <= 1e-12 * mag, q
 
 
-@pytest.mark.parametrize("grid", GRIDS)
+@pytest.mark.parametrize("grid", GRIDS + [(65, 33, 707)])
 @pytest.mark.parametrize("scheme", ["hlld", "hll_rk3", "mixed", "wenoz"])
 def test_columns_and_runs_glm(grid, scheme):
     """The same kernel on the nine cell-centred fields of GLM cleaning."""

@@ -29,8 +29,15 @@
 //  - LDS holds two planes of the column (by the parity of k - k0; the values a
 //    thread needs of planes k-1 and k+1 are its own), one cross halo and the
 //    exchanged fluxes.
-//  - Two waves per SIMD in FP64 (204 VGPRs, GLM 252), three in mixed precision:
-//    one more spills (FP64 1.95 ms against 1.52, mixed 384^3 3.73 against 3.39).
+//  - Two waves per SIMD in FP64 (204 VGPRs, GLM 236, WENO-Z with GLM 254), three in
+//    mixed precision: one more spills (FP64 1.95 ms against 1.52, mixed 384^3 3.73
+//    against 3.39).
+//  - Fluxes are differenced before they are added up, so a uniform flow has L = 0 and
+//    a cell's result does not depend on its place in the column (a running sum over
+//    the faces has neither; it took 0.2 to 0.9 % less time a step). The lower z-flux
+//    waits in the thread's own slot of fy, which is free between the exchanges: in
+//    registers, HLL in FP64 needs 176 (with 168 or fewer three workgroups fit a CU),
+//    and WENO-Z with GLM spills.
 //  - Two barriers a plane: before the first one everybody reads plane k; then
 //    the halo of plane k+1 and the exchanged fluxes are written; the second
 //    publishes them.
@@ -346,7 +353,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
   const RkCoef rk = rk_coef(stage, h);
   const R ch = GLM ? uni((R)(ch0 / h)) : R(0);
   int cp = 0;  // core offset of plane k
-  double acc[NF];  // minus L of the cell below, but for its upper z-flux
+  double acc[NF];  // flux differences along x and y of the own cell
+  R fz[NF];        // its lower z-flux, in L.fy[.][t] but for the exchange
   R* const fw0 = reinterpret_cast<R*>(FW);
   for (int k = k0;; ++k) {
     const int kw = wrap(k, g.nz);
@@ -396,7 +404,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
           *reinterpret_cast<double*>(reinterpret_cast<char*>(p + cb) + c) = v;
         };
 #pragma unroll
-        for (int q = 0; q < NF; ++q) acc[q] = -(acc[q] + (double)F[q] * idz);
+        for (int q = 0; q < NF; ++q)
+          acc[q] = -(acc[q] + ((double)F[q] - (double)L.fy[q][t]) * idz);
         if (stage != 3) {
           double u[NF], u0[NF];
 #pragma unroll
@@ -418,7 +427,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       }
       if (k == k1) break;
 #pragma unroll
-      for (int q = 0; q < NF; ++q) acc[q] = -(double)F[q] * idz;
+      for (int q = 0; q < NF; ++q) L.fy[q][t] = F[q];
     }
     if constexpr (!GLM) put_edge<2, EM>(fwp, n, boff, o);
     const int ka = wrap(k + 1, g.nz), kb = wrap(k + 2, g.nz), kc = wrap(k + 3, g.nz);
@@ -438,8 +447,9 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       cell_fluxes<0, EM>(o, psi, fpsi, F);
 #pragma unroll
       for (int q = 0; q < NF; ++q) {
-        const R up = __shfl_down(F[q], 1, 64);  // the upper face, but for the last column
-        acc[q] += (x == M::TX - 1) ? -(double)F[q] * idx : ((double)up - (double)F[q]) * idx;
+        // the upper face; the last column keeps the lower one until it is exchanged
+        const R up = __shfl_down(F[q], 1, 64);
+        acc[q] = (x == M::TX - 1) ? (double)F[q] : ((double)up - (double)F[q]) * idx;
       }
     }
     // y-face
@@ -455,8 +465,6 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     if constexpr (!GLM) put_edge<1, EM>(fwp, n, boff, o);
     R fy[NF];
     cell_fluxes<1, EM>(o, psi, fpsi, fy);
-#pragma unroll
-    for (int q = 0; q < NF; ++q) acc[q] -= (double)fy[q] * idy;
     // the faces above the column: one wave, in turn
     const bool helper = wave == ((k - k0) & 3);
     R fe[NF];
@@ -510,6 +518,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
         for (int d = 0; d < 3; ++d) nb[d] = ld_at(U + (F_BX + d) * n + kb * nxy, c);
       }
     }
+#pragma unroll
+    for (int q = 0; q < NF; ++q) fz[q] = L.fy[q][t];
     __syncthreads();
     if (y > 0) {
 #pragma unroll
@@ -531,8 +541,9 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
-      acc[q] += (double)L.fy[q][t] * idy;
-      if (x == M::TX - 1) acc[q] += (double)L.fx[q][y] * idx;
+      if (x == M::TX - 1) acc[q] = ((double)L.fx[q][y] - acc[q]) * idx;
+      acc[q] += ((double)L.fy[q][t] - (double)fy[q]) * idy;
+      L.fy[q][t] = fz[q];
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) bn[d] = bnn[d];

@@ -1,0 +1,95 @@
+"""What the 3D stages owe to the last bit, with no oracle beside them: equal fluxes
+cancel exactly, and a cell's update depends on the values about it alone, not on its
+place in the grid (32 x 8 columns for the faces, 31 x 7 for CT, runs along z). Every
+comparison is of the bits, so there is no tolerance."""
+import numpy as np
+import pytest
+
+from paper_2511_20337_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SCHEMES = ["minmod", "hll", "hlld", "hll_uct_hlld", "uct_hlld_rk3", "mixed", "mixed_hll_uct_hlld",
+           "glm", "glm_hll_minmod", "glm_mixed", "wenoz_uct_hlld_rk3", "hll_wenoz", "glm_wenoz",
+           "glm_hll_wenoz"]
+
+
+def setup(scheme, nx, ny, nz, box=(0, 1, 0, 1, 0, 1)):
+    lim = "wenoz" if "wenoz" in scheme else ("minmod" if "minmod" in scheme else "vanleer")
+    s = W.make_setup("exact3d", 3, nx, ny, nz, box, 5.0 / 3.0, 0.3, lim,
+                     "hll" if "hll" in scheme.split("_") else "hlld")
+    return dict(s, emf="uct_hlld" if "uct_hlld" in scheme else "uct_hll",
+                integrator="rk3" if "rk3" in scheme else "rk2",
+                precision="mixed" if "mixed" in scheme else "fp64",
+                divb="glm" if "glm" in scheme else "ct")
+
+
+def state(s, seed=3):
+    """Random and physical; cells differ by some 20 %, so that every limiter branch
+    and region of the solvers occurs."""
+    rng = np.random.default_rng(seed)
+    sh = (s["nz"], s["ny"], s["nx"])
+    w = [b + 0.2 * rng.uniform(-1, 1, sh) for b in (1.0, 0.3, -0.2, 0.1, 0.8, 0.4, 0.25, -0.15)]
+    U = W.assemble(s, *w)
+    if s["divb"] == "glm":
+        s9, U = W.glm_from_ct(s, U)
+        U[8] = 0.02 * rng.uniform(-1, 1, sh)
+    return U
+
+
+def advance(s, U0):
+    """One step of U0 (with CT also L(U0)), on the device."""
+    from paper_2511_20337_amd import mhd
+    ctx = mhd.Context(s, "cuda:0")
+    U = torch.from_numpy(np.ascontiguousarray(U0)).cuda()
+    out = [ctx.rhs(U)] if s["divb"] == "ct" else []
+    dt = ctx.dt(U)
+    ctx.step(U, dt)
+    ctx.check()
+    return out + [U, torch.tensor(dt)]
+
+
+def assert_same(got, want):
+    for a, b in zip(got, want):
+        assert torch.equal(a, b), int((a != b).sum())
+
+
+# more than one column and run each way, ragged; spacings no powers of two
+@pytest.mark.parametrize("grid", [(65, 17, 12), (48, 24, 20), (5, 9, 70)])
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_uniform_flow_stays(grid, scheme):
+    """L of a moving, magnetised uniform state is zero, and a step leaves it as it is."""
+    s = setup(scheme, *grid)
+    sh = (s["nz"], s["ny"], s["nx"])
+    U0 = W.assemble(s, *[np.full(sh, v) for v in (1.3, 0.3, -0.2, 0.1, 0.7, 0.4, -0.25, 0.6)])
+    if s["divb"] == "glm":
+        _, U0 = W.glm_from_ct(s, U0)
+    print("uniform flow", grid, scheme, flush=True)
+    got = advance(s, U0)
+    if s["divb"] == "ct":
+        assert float(got[0].abs().max()) == 0.0
+    if s["integrator"] == "rk2":  # (3 u + u) / 4 may round
+        assert torch.equal(got[-2], torch.from_numpy(U0).cuda())
+
+
+@pytest.mark.parametrize("axis", [1, 2, 3])
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_what_is_uniform_along_an_axis_stays_so(scheme, axis):
+    s = setup(scheme, 65, 17, 21)
+    U0 = state(s)
+    U0 = np.repeat(U0.take([0], axis=axis), U0.shape[axis], axis=axis)
+    print("uniform along", axis, scheme, flush=True)
+    for a in advance(s, U0)[:-1]:
+        assert torch.equal(a, a.narrow(axis, 0, 1).expand_as(a))
+
+
+@pytest.mark.parametrize("grid", [(65, 17, 37), (31, 40, 16), (4, 5, 50)])
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_a_shifted_state_gives_the_shifted_result(grid, scheme):
+    s = setup(scheme, *grid)
+    U0 = state(s)
+    shift = (3, 5, 13)
+    print("shifted state", grid, scheme, flush=True)
+    want = [torch.roll(a, shift, (1, 2, 3)) if a.dim() else a for a in advance(s, U0)]
+    assert_same(advance(s, np.roll(U0, shift, (1, 2, 3))), want)

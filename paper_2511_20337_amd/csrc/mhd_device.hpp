@@ -189,7 +189,8 @@ __device__ __forceinline__ double wenoz_upper(double v0, double v1, double v2, d
 
 // The values at the lower and the upper interface of the middle cell: the two
 // share the smoothness indicators (in reverse order), their products and the
-// middle weight.
+// middle weight. Equal to two wenoz_upper up to rounding, not bit for bit: a value
+// that is formed at two places takes the same function at both.
 __device__ __forceinline__ void wenoz_both(double v0, double v1, double v2, double v3, double v4,
                                            double& lo, double& up) {
   const double c1 = 13.0 / 12.0, c2 = 1.0 / 4.0, eps = 1e-40;
@@ -203,18 +204,17 @@ __device__ __forceinline__ void wenoz_both(double v0, double v1, double v2, doub
   const double tau5 = __builtin_fabs(e0 - e2);
   const double w0 = (e0 + tau5) * (e1 * e2), w2 = (e2 + tau5) * (e0 * e1);
   const double al1 = 0.6 * (e1 + tau5) * (e0 * e2);
-  const double m = 5.0 * v2;
   {
     const double al0 = 0.1 * w0, al2 = 0.3 * w2;
     const double q0 = __builtin_fma(2.0, v0, __builtin_fma(-7.0, v1, 11.0 * v2));
-    const double q1 = __builtin_fma(2.0, v3, m - v1);
+    const double q1 = __builtin_fma(5.0, v2, __builtin_fma(2.0, v3, -v1));
     const double q2 = __builtin_fma(2.0, v2, __builtin_fma(5.0, v3, -v4));
     up = div_r(__builtin_fma(al0, q0, __builtin_fma(al1, q1, al2 * q2)), 6.0 * (al0 + al1 + al2));
   }
   {
     const double al0 = 0.1 * w2, al2 = 0.3 * w0;
     const double q0 = __builtin_fma(2.0, v4, __builtin_fma(-7.0, v3, 11.0 * v2));
-    const double q1 = __builtin_fma(2.0, v1, m - v3);
+    const double q1 = __builtin_fma(5.0, v2, __builtin_fma(2.0, v1, -v3));
     const double q2 = __builtin_fma(2.0, v2, __builtin_fma(5.0, v1, -v0));
     lo = div_r(__builtin_fma(al0, q0, __builtin_fma(al1, q1, al2 * q2)), 6.0 * (al0 + al1 + al2));
   }

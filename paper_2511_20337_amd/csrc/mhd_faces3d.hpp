@@ -308,14 +308,18 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       lds[q * HL::Q + M::NCORE + t] = (R)Wm1[q];
       lds[q * HL::Q + t] = (R)W[q];
     }
-    if constexpr (WZ) {  // the upper value of cell k0 - 1, from planes k0 - 3 .. k0 + 1
+    if constexpr (WZ) {
+      // the upper value of cell k0 - 1, from planes k0 - 3 .. k0 + 1, as the run below
+      // forms it (wenoz_both, its lower value unused): the face between two runs is
+      // solved by either, to the same bits
       const double* const pm3 = PW + wrap(k0 - 3, g.nz) * nxy;
       const double* const pp1 = PW + kp1 * nxy;
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
         const int sq = zslot[q];
-        zl[q] = wenoz_upper(ld_at(pm3 + sq * n, po.c), Wm2[sq], Wm1[sq], W[sq],
-                            ld_at(pp1 + sq * n, po.c));
+        double lo;
+        wenoz_both(ld_at(pm3 + sq * n, po.c), Wm2[sq], Wm1[sq], W[sq], ld_at(pp1 + sq * n, po.c),
+                   lo, zl[q]);
         zm2[q] = Wm2[sq];
         zp2[q] = ld_at(PW + sq * n + wrap(k0 + 2, g.nz) * nxy, po.c);
       }

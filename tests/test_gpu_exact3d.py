@@ -93,3 +93,10 @@ def test_a_shifted_state_gives_the_shifted_result(grid, scheme):
     print("shifted state", grid, scheme, flush=True)
     want = [torch.roll(a, shift, (1, 2, 3)) if a.dim() else a for a in advance(s, U0)]
     assert_same(advance(s, np.roll(U0, shift, (1, 2, 3))), want)
+
+
+# 1.5 million cells: from here on WENO-Z marches, and solves the faces between two
+# runs along z once in either
+@pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
+def test_shifted_state_where_wenoz_marches(scheme):
+    test_a_shifted_state_gives_the_shifted_result((65, 33, 707), scheme)

@@ -100,3 +100,28 @@ def test_a_shifted_state_gives_the_shifted_result(grid, scheme):
 @pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
 def test_shifted_state_where_wenoz_marches(scheme):
     test_a_shifted_state_gives_the_shifted_result((65, 33, 707), scheme)
+
+
+# columns narrower than the face kernel's (32 x 8), where an index takes one
+# remainder more and where it does not (18 x 6 and 17 x 5), and just wider
+@pytest.mark.parametrize("grid", [(4, 4, 47000), (17, 5, 9000), (18, 6, 7000), (5, 9, 17000),
+                                  (31, 7, 3500), (33, 9, 2600)])
+@pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
+def test_marching_wenoz_on_narrow_grids(scheme, grid):
+    """A periodic state twice along z has 1.5 million cells, which WENO-Z marches; once,
+    it has fewer, which it takes cell by cell (checked against the oracle elsewhere).
+    The two form a z-face's values with other roundings: the repository's 1e-12 of each
+    field's maximum."""
+    nx, ny, nz = grid
+    assert nx * ny * nz < 1500000 <= 2 * nx * ny * nz
+    s1 = setup(scheme, nx, ny, nz, (0, 1, 0, 1, 0, nz / 16))
+    s2 = setup(scheme, nx, ny, 2 * nz, (0, 1, 0, 1, 0, nz / 8))
+    U0 = state(s1)
+    print("narrow grid", grid, scheme, flush=True)
+    once = advance(s1, U0)
+    twice = advance(s2, np.concatenate([U0, U0], axis=1))
+    assert twice[-1] == once[-1]  # the time step
+    for a, b in zip(twice[:-1], once[:-1]):
+        tol = 1e-12 * b.abs().amax(dim=(1, 2, 3), keepdim=True)
+        for half in (a[:, :nz], a[:, nz:]):
+            assert bool(((half - b).abs() <= tol).all())

@@ -85,3 +85,24 @@ def test_columns_and_runs_glm(grid, scheme):
     for q in range(8):  # the same flux on both sides of a column's edge
         mag = np.abs(U0[q]).sum() + np.abs(U0[1:4]).sum() * (1 <= q <= 3)
         assert abs(got[q].sum() - U0[q].sum()) <= 1e-12 * mag, q
+
+
+@pytest.mark.parametrize("grid", GRIDS[:-1] + [(40, 20, 12)])
+def test_glm_wenoz_with_hll(grid):
+    """The cell-by-cell WENO-Z kernel with GLM cleaning and the HLL solver."""
+    from paper_2511_20337_amd import mhd
+    from tests.test_gpu_glm import rel_err9
+    nx, ny, nz = grid
+    s, U = W.generic_state(3, nx, ny, nz, "wenoz", "hll", seed=nx + nz)
+    s, U0 = W.glm_from_ct(s, U)
+    U0[8] = 0.02 * np.random.default_rng(17).normal(size=U0[8].shape)
+    print("GLM, WENO-Z, HLL", grid, flush=True)
+    ctx = mhd.Context(s, "cuda:0")
+    Ua = torch.from_numpy(U0).cuda()
+    dts = []
+    for _ in range(2):
+        dts.append(ctx.dt(Ua))
+        ctx.step(Ua, dts[-1])
+    ctx.check()
+    err = rel_err9(Ua.cpu().numpy(), O.glm_run_dts(O.cfg_from(s), U0, np.array(dts)))
+    assert (err <= 1e-12).all(), err

@@ -11,6 +11,7 @@ missing every call raises — there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -194,7 +195,7 @@ def mhd_step_cfl(ctx, U, dt_dev, ws) -> None:
 
 
 def mhd_run(ctx, U, nsteps: int, dt_dev, ws) -> None:
-    rc = lib().mhd_run(ctx, U.data_ptr(), int(nsteps), dt_dev.data_ptr(), ws.data_ptr(),
+    rc = lib().mhd_run(ctx, U.data_ptr(), operator.index(nsteps), dt_dev.data_ptr(), ws.data_ptr(),
                        ws.numel(), _stream(U.device))
     _raise(ctx, rc, "mhd_run")
 
@@ -338,6 +339,7 @@ class Context:
 
     def run(self, U, nsteps: int):
         """nsteps CFL-limited steps, dt computed on the device each step."""
+        nsteps = operator.index(nsteps)  # whole steps only: 2.5 is refused
         if nsteps > 0:
             mhd_run(self.ctx, self._state(U), nsteps, self.dt_dev, self.ws)
         return U

@@ -96,3 +96,18 @@ def test_c_abi_program_rejects_bad_input_without_a_gpu(tmp_path):
     r = subprocess.run([exe, str(fin), str(tmp_path / "out.bin"), "1"] + bad,
                        capture_output=True, text=True, timeout=60)
     assert r.returncode == 1 and "mhd_init" in r.stderr, r.stderr
+
+
+def test_run_takes_whole_steps_only():
+    """A number of steps that is no integer is refused, also where it would round
+    down to nothing to do."""
+    import types
+
+    import torch
+    U = torch.zeros(8)
+    stub = types.SimpleNamespace(ctx=None, ws=U, dt_dev=U, _state=lambda u: u)
+    for nsteps in (2.5, 2.0, 0.0, -1.0, "2", None):
+        with pytest.raises(TypeError):
+            mhd.Context.run(stub, U, nsteps)
+    assert mhd.Context.run(stub, U, 0) is U
+    assert mhd.Context.run(stub, U, -3) is U

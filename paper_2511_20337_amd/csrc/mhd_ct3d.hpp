@@ -362,9 +362,9 @@ MarchGrid ct_grid(const Geom& g, int precision) {
   const int64_t cols = (int64_t)mg.ntx * mg.nty;
   int64_t best = 0;
   mg.lz = 0;
-  for (int r = (g.nz + 19) / 20; r <= g.nz; ++r) {
-    const int lz = (g.nz + r - 1) / r;
-    const int64_t t = (cols * ((g.nz + lz - 1) / lz) + slots - 1) / slots * (lz + 2);
+  for (int most = min(g.nz, 20); most >= 1; --most) {
+    const int runs = (g.nz + most - 1) / most, lz = (g.nz + runs - 1) / runs;
+    const int64_t t = (cols * runs + slots - 1) / slots * (lz + 2);
     if (mg.lz == 0 || t < best) {
       best = t;
       mg.lz = lz;

@@ -125,3 +125,29 @@ def test_marching_wenoz_on_narrow_grids(scheme, grid):
         tol = 1e-12 * b.abs().amax(dim=(1, 2, 3), keepdim=True)
         for half in (a[:, :nz], a[:, nz:]):
             assert bool(((half - b).abs() <= tol).all())
+
+
+def test_a_long_grid_costs_the_host_nothing():
+    """The launches of a grid of a million planes are chosen in a bounded number of
+    steps: the call returns within a millisecond (a search over all numbers of
+    runs took the host several)."""
+    import time
+    from paper_2511_20337_amd import mhd
+    s = setup("hll", 4, 4, 1000000, (0, 1, 0, 1, 0, 250000))
+    ctx = mhd.Context(s, "cuda:0")
+    w = [1.0, 0.3, -0.2, 0.1, 2.0, 0.4, 0.25, -0.15]
+    U = torch.empty(ctx.shape, dtype=torch.float64, device="cuda:0")
+    for q, v in enumerate(w):
+        U[q] = v
+    out = torch.empty_like(U)
+    best = 1.0
+    for _ in range(4):
+        ctx.rhs(U, out)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        ctx.rhs(U, out)
+        best = min(best, time.perf_counter() - t)
+        torch.cuda.synchronize()
+    ctx.check()
+    assert float(out.abs().max()) == 0.0
+    assert best < 1e-3, best

@@ -157,9 +157,8 @@ mhd::StageArgs stage_args(mhd_ctx* ctx, void* ws, hipStream_t s) {
   a.emf = ctx->cfg.emf;
   a.g = ctx->g;
   a.FW = reinterpret_cast<double*>(base(ws) + ctx->off_fw);
-  a.EW = reinterpret_cast<double*>(base(ws) + ctx->off_ew);
   a.glm = ctx->cfg.divb == MHD_DIVB_GLM;
-  a.PW = (ctx->cfg.limiter == MHD_LIM_WENOZ || a.glm)
+  a.PW = (a.dim == 3 && a.limiter == MHD_LIM_WENOZ)
              ? reinterpret_cast<double*>(base(ws) + ctx->off_pw) : nullptr;
   if (a.glm) {
     // c_h = C Delta_min / dt; the damping per step exp(-alpha c_h dt / Delta_min)
@@ -222,8 +221,8 @@ mhd_status run_step(mhd_ctx* ctx, double* U, double dt, const double* dtp, void*
 // nsteps steps with the 2D stages, dt of each step in *dt_dev. The last
 // stage of a step leaves the CFL partials of the state it writes to the next
 // step, which needs the state it reads left alone: the steps alternate between
-// U and a second state, and the last one ends in U. The second state and the
-// partials take the space of the face records, which these stages do not use.
+// U and a second state, and the last one ends in U. The second state and two sets
+// of partials take the space in which the adjoint's stages keep their records.
 mhd_status run_2d(mhd_ctx* ctx, double* U, int64_t nsteps, double* dt_dev, void* ws,
                   hipStream_t s) {
   double* alt = reinterpret_cast<double*>(base(ws) + ctx->off_fw);
@@ -329,25 +328,36 @@ mhd_status mhd_init(const mhd_config* cfg, mhd_ctx** out) {
   const bool glm = cfg->divb == MHD_DIVB_GLM;
   const size_t nf = glm ? 9 : 8;  // stored fields
   c->cfl_blocks = kCflBlocks;
-  // CFL partials: of k_cfl, or (3D) one per face (WENO-Z: primitive) workgroup
-  // of the fused step; GLM: one per primitive workgroup in 2D and 3D
+  // CFL partials: of k_cfl, or one per workgroup of the 3D WENO-Z primitive kernel
   size_t npart = kCflBlocks;
-  if (cfg->dim == 3 || glm)
-    npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter));
+  if (cfg->dim == 3) npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter));
+  // 3D: the face kernel's edge inputs (CT), or the nine fluxes per direction of
+  // the kernel that takes WENO-Z cell by cell (GLM; CT has both, in one record);
+  // 2D: the second state of mhd_run and its two sets of CFL partials
+  size_t nrec = 0;
+  if (cfg->dim == 2)
+    nrec = nf * n + 2 * (size_t)mhd::stage_2d_tiles(c->g, cfg->limiter, cfg->emf, cfg->precision,
+                                                    glm);
+  else if (!glm)
+    nrec = 3 * (size_t)mhd::NSLOT * n;
+  else if (cfg->limiter == MHD_LIM_WENOZ && c->g.n < mhd::kCellsWeno)
+    nrec = 3 * 9 * n;
   size_t off = kCtl;
   c->off_partial = off;
   off = align_up(off + sizeof(double) * npart);
   c->off_u1 = off;
   off = align_up(off + sizeof(double) * nf * n);
-  c->off_fw = off;  // face records (CT) or the nine face fluxes per direction (GLM)
-  off = align_up(off + sizeof(double) * (size_t)cfg->dim * (glm ? 9 : mhd::NSLOT) * n);
-  c->off_ew = off;
-  if (!glm) off = align_up(off + sizeof(double) * 3 * n);
   c->off_u2 = off;  // SSP-RK3: the second-stage state
   if (cfg->integrator == MHD_SSP_RK3) off = align_up(off + sizeof(double) * nf * n);
-  c->off_pw = off;  // WENO-Z and GLM: the primitives of every cell
-  if (cfg->limiter == MHD_LIM_WENOZ || glm) off = align_up(off + sizeof(double) * nf * n);
-  c->bytes_fwd = off;
+  c->off_pw = off;  // 3D WENO-Z: the primitives of every cell
+  if (cfg->dim == 3 && cfg->limiter == MHD_LIM_WENOZ) off = align_up(off + sizeof(double) * nf * n);
+  c->off_fw = off;
+  c->bytes_fwd = align_up(off + sizeof(double) * nrec);
+  // The adjoint: whole face records (2D: over mhd_run's space), E_z (3D: L of the
+  // staggered field), then its own arrays
+  off = align_up(off + sizeof(double) * std::max(nrec, (size_t)cfg->dim * mhd::NSLOT * n));
+  c->off_ew = off;
+  off = align_up(off + sizeof(double) * 3 * n);
   c->off_adj = off;
   c->bytes_adj = off + mhd::adjoint_workspace_bytes(cfg->dim, n, cfg->integrator);
   c->err[0] = '\0';

@@ -82,3 +82,42 @@ def test_run_reports_unphysical_cells(scheme):
     ctx.run(torch.from_numpy(U0).cuda(), 2)
     with pytest.raises(mhd.Unphysical):
         ctx.check()
+
+
+# both kinds of tile, the smallest grid; in 3D both kinds of WENO-Z
+@pytest.mark.parametrize("grid", [(4, 4, 1), (33, 9, 1), (300, 257, 1), (4, 4, 4), (33, 9, 6),
+                                  (132, 110, 105)])
+@pytest.mark.parametrize("lim,kind", [("vanleer", k) for k in (
+    "ct", "uct_hlld_rk3", "glm", "glm_rk3", "mixed", "adjoint", "adjoint_rk3")] + [
+    ("wenoz", k) for k in ("ct", "uct_hlld_rk3", "glm", "glm_rk3")])
+def test_no_call_writes_past_the_workspace(grid, lim, kind):
+    """Every call with a workspace of just the bytes asked for, behind which a pattern
+    stays as it is."""
+    from paper_2511_20337_amd import mhd
+    nx, ny, nz = grid
+    adjoint = "adjoint" in kind
+    s, U0 = W.generic_state(2 if nz == 1 else 3, nx, ny, nz, lim, seed=5)
+    s = dict(s, emf="uct_hlld" if "uct" in kind else "uct_hll",
+             integrator="rk3" if "rk3" in kind else "rk2",
+             precision="mixed" if kind == "mixed" else "fp64")
+    if "glm" in kind:
+        s, U0 = W.glm_from_ct(s, U0)
+    print("past the workspace", grid, lim, kind, flush=True)
+    ctx = mhd.Context(s, "cuda:0", with_adjoint=adjoint)
+    nbytes = ctx.ws.numel()
+    buf = torch.full((nbytes + 65536 + 256,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    off = (-buf.data_ptr()) % 256
+    ctx.ws = buf[off:off + nbytes]
+    ctx.ws[:256].zero_()
+    U = torch.from_numpy(U0).cuda()
+    if adjoint:
+        ctx.adjoint_step(U, ctx.dt(U), torch.ones_like(U), want_dtbar=True)
+    else:
+        if "glm" not in kind:
+            ctx.rhs(U)
+        ctx.step(U, ctx.dt(U))
+        ctx.step_cfl(U)
+        ctx.run(U, 3)
+    ctx.check()
+    assert bool((buf[off + nbytes:] == 0xA5).all())
+    assert bool((buf[:off] == 0xA5).all())

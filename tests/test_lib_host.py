@@ -111,3 +111,30 @@ def test_run_takes_whole_steps_only():
             mhd.Context.run(stub, U, nsteps)
     assert mhd.Context.run(stub, U, 0) is U
     assert mhd.Context.run(stub, U, -3) is U
+
+
+# doubles per cell that the forward calls use: stage state(s), then in 3D with CT the
+# face records (33), with WENO-Z the primitives and with GLM under 1.5 million cells its
+# fluxes, in 2D the second state of a run of steps
+@pytest.mark.parametrize("dim,n,per_cell,opts", [
+    (3, 64, 8 + 33, {}),
+    (3, 64, 2 * 8 + 33 + 8, dict(limiter="wenoz", integrator="rk3")),
+    (3, 64, 9, dict(divb="glm")),
+    (3, 64, 2 * 9, dict(divb="glm", integrator="rk3")),
+    (3, 64, 9 + 9 + 27, dict(divb="glm", limiter="wenoz")),
+    (3, 128, 9 + 9, dict(divb="glm", limiter="wenoz")),
+    (2, 512, 8 + 8, {}),
+    (2, 512, 2 * 8 + 8, dict(limiter="wenoz", integrator="rk3")),
+    (2, 512, 9 + 9, dict(divb="glm")),
+    (2, 512, 9 + 9, dict(divb="glm", limiter="wenoz"))])
+def test_workspace_holds_what_the_calls_use(dim, n, per_cell, opts):
+    s, _ = W.uniform(dim=dim, n=8)
+    s = dict(s, nx=n, ny=n, nz=n if dim == 3 else 1, **opts)
+    ctx = mhd.mhd_init(mhd.config_from(s))
+    cells = n ** dim
+    got = mhd.mhd_workspace_bytes(ctx)
+    mhd.mhd_destroy(ctx)
+    # beside them the control block, alignment, and CFL partials: one per 256 cells,
+    # but 2048 at least, and in 2D two for each 64 cells
+    slack = 4096 + 8 * max(2048, cells // 256) + (8 * 2 * cells // 64 if dim == 2 else 0)
+    assert 8 * per_cell * cells <= got <= 8 * per_cell * cells + slack

@@ -25,6 +25,8 @@
 //    of one run the stage that writes a state leaves its partials, which saves
 //    the pass over U (128^2: 17.0 -> 15.2 us a step).
 #pragma once
+#include <algorithm>
+
 #include "mhd_device.hpp"
 #include "mhd_grid.hpp"
 #include "mhd_kernels.hpp"
@@ -69,11 +71,12 @@ __device__ __forceinline__ int wrap_near(int i, int n) {
 // partials, written to *dt_out by workgroup 0; else *dtp or dt. cfl_next !=
 // nullptr (the last stage of a step that another follows; out then is neither
 // U nor U0, whose values above the tile are read): also the CFL bound of the
-// new state over the tile into cfl_next[blockIdx.x].
+// new state over the tile into its place in cfl_next. tile0: the first workgroup's
+// tile.
 template <class T, int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(T::NT) __attribute__((amdgpu_waves_per_eu(T::NT == 512 ? 4 : 2)))
 void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geom g, int ntx,
-                int stage, double dt, const double* __restrict__ dtp,
+                unsigned tile0, int stage, double dt, const double* __restrict__ dtp,
                 const double* __restrict__ cflp, int npart, double cfl,
                 double* __restrict__ dt_out, double* __restrict__ cfl_next,
                 int* __restrict__ flag, double dmin, double decay) {
@@ -83,7 +86,8 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
   constexpr int NU = GLM ? 9 : 8, NW = GLM ? 9 : 7;  // fields, reconstructed quantities
   __shared__ Lds2<R, T, EM> L;
   const int t = (int)threadIdx.x;
-  const int i0 = (int)(blockIdx.x % (unsigned)ntx) * W, j0 = (int)(blockIdx.x / (unsigned)ntx) * H;
+  const unsigned tile = tile0 + blockIdx.x;
+  const int i0 = (int)(tile % (unsigned)ntx) * W, j0 = (int)(tile / (unsigned)ntx) * H;
   const int64_t n = g.n;
   bool bad = false;
   for (int e = t; e < NP; e += NT) {
@@ -129,7 +133,7 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
     h = cfl * m;
-    if (blockIdx.x == 0 && t == 0) *dt_out = h;
+    if (tile == 0 && t == 0) *dt_out = h;
   } else if (stage != 0) {
     h = dtp ? *dtp : dt;
   }
@@ -310,17 +314,23 @@ void k_stage_2d(const double* __restrict__ U, const double* U0, double* out, Geo
   if (t == 0) {
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) m = (L.red[w] < m) ? L.red[w] : m;
-    cfl_next[blockIdx.x] = m;
+    cfl_next[tile] = m;
   }
 }
+
+// A launch has fewer than 2^32 threads; a narrow grid of many rows takes several.
+constexpr unsigned kTilesPerLaunch = 1u << 22;
 
 template <class T, int LIM, int RS, class R, int EM>
 void stage_2d(const StageArgs& a, const double* cflp, int npart) {
   const int ntx = (a.g.nx + T::W - 1) / T::W, nty = (a.g.ny + T::H - 1) / T::H;
-  hipLaunchKernelGGL((k_stage_2d<T, LIM, RS, R, EM>), dim3((unsigned)ntx * (unsigned)nty),
-                     dim3(T::NT), 0, a.stream, a.U, a.U0 ? a.U0 : a.U, a.out, a.g, ntx, a.stage,
-                     a.dt, a.dtp, cflp, npart, a.cfl, a.dt_out, a.cfl_next, a.flag, a.glm_dmin,
-                     (a.stage == 2 || a.stage == 5) ? a.glm_decay : 1.0);
+  const unsigned tiles = (unsigned)ntx * (unsigned)nty;
+  for (unsigned t0 = 0; t0 < tiles; t0 += kTilesPerLaunch)
+    hipLaunchKernelGGL((k_stage_2d<T, LIM, RS, R, EM>),
+                       dim3(std::min(tiles - t0, kTilesPerLaunch)), dim3(T::NT), 0, a.stream, a.U,
+                       a.U0 ? a.U0 : a.U, a.out, a.g, ntx, t0, a.stage, a.dt, a.dtp, cflp, npart,
+                       a.cfl, a.dt_out, a.cfl_next, a.flag, a.glm_dmin,
+                       (a.stage == 2 || a.stage == 5) ? a.glm_decay : 1.0);
 }
 
 // Widths of the large tiles: what two workgroups of a CU have LDS for (in FP64

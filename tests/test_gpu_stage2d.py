@@ -121,3 +121,36 @@ def test_no_call_writes_past_the_workspace(grid, lim, kind):
     ctx.check()
     assert bool((buf[off + nbytes:] == 0xA5).all())
     assert bool((buf[:off] == 0xA5).all())
+
+
+def test_more_tiles_than_one_launch_takes():
+    """Four cells by 67 million rows: 2^32 threads and some more. A uniform state with
+    one disturbed cell in the last tiles (GLM, one step and a run): unchanged far from
+    it, and as on a short grid around it."""
+    from paper_2511_20337_amd import mhd
+    if torch.cuda.mem_get_info()[0] < 100e9:
+        pytest.skip("needs 62 GB")
+    rows = (1 << 26) + 20
+    out = {}
+    for ny in (128, rows):
+        s = dict(W.make_setup("rows", 2, 4, ny, 1, (0, 1, 0, ny / 4, 0, 1), 5.0 / 3.0, 0.4,
+                              "vanleer"), divb="glm")
+        one = W.glm_from_ct(*W.uniform(dim=2, n=8))[1][:, 0, 0, 0]
+        print("rows", ny, flush=True)
+        ctx = mhd.Context(s, "cuda:0")
+        U = torch.empty(ctx.shape, dtype=torch.float64, device="cuda:0")
+        for q in range(9):
+            U[q] = one[q]
+        U[0, 0, ny - 10, 1] *= 1.25
+        ctx.step_cfl(U)
+        ctx.run(U, 2)
+        ctx.check()
+        dt = ctx.dt_dev.item()
+        out[ny] = (U[:, 0, ny - 32:].clone(), dt)
+        for q in range(9):
+            rest = U[q, 0, 32:ny - 32]
+            assert float(rest.min()) == float(rest.max()) == one[q]
+        del U, ctx
+        torch.cuda.empty_cache()
+    assert out[rows][1] == out[128][1]
+    assert torch.equal(out[rows][0], out[128][0])

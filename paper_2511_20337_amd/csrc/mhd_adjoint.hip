@@ -15,8 +15,8 @@
 //                 of alpha+-, the weighted velocities and b gathered from the
 //                 edges that used them (through the adjoint of their
 //                 reconstruction), then the Riemann solver's vector-Jacobian
-//                 product: one hand-written reverse sweep over the values the
-//                 solver itself recorded;
+//                 product: one hand-written reverse sweep (HLL over the values
+//                 the solver recorded, HLLD over values formed again);
 //   k_adj_cells — per cell: adjoint of PLM (gathering the face-state
 //                 cotangents of the faces each cell feeds) and of primitive
 //                 recovery;
@@ -33,8 +33,8 @@ namespace mhd {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Hand-written reverse sweeps of the Riemann solvers. The forward values are
-// formed with the forward solvers' own expressions, so every branch (wave-speed
+// Hand-written reverse sweeps of the Riemann solvers. The forward values that
+// decide a branch come from the forward solvers' own functions, so every branch (wave-speed
 // min/max, HLL/HLLD region, degenerate star state, sign of the normal field)
 // is the one the forward kernels take; the derivative of each branch is then
 // propagated backwards once for all fifteen inputs. At a square root of zero
@@ -260,26 +260,13 @@ __device__ __forceinline__ void hlld_vjp(double g, const double* wl, const doubl
                                          const double* fbar, double apbar, double ambar,
                                          double v1bar, double v2bar, double* wlb, double* wrb,
                                          double& bnb) {
-  // forward, in the expressions of hlld_flux
+  // forward (hlld_fan, hlld_star, hlld_front: as the flux forms them)
   const double igm1 = rcp_r(g - 1.0);
   const double bn2 = bn * bn;
-  const double ptl = fma_r(0.5, fma_r(wl[5], wl[5], fma_r(wl[4], wl[4], bn2)), wl[6]);
-  const double ptr = fma_r(0.5, fma_r(wr[5], wr[5], fma_r(wr[4], wr[4], bn2)), wr[6]);
-  const double c2l = cfast2(g, wl[0], wl[6], bn, wl[4], wl[5]);
-  const double c2r = cfast2(g, wr[0], wr[6], bn, wr[4], wr[5]);
-  const double cm = sqrt_r(max_r(c2l, c2r));
-  const double sl = min_r(wl[1], wr[1]) - cm;
-  const double sr = max_r(wl[1], wr[1]) + cm;
-  double sm, pts, iden;
-  {
-    const double ml = (sl - wl[1]) * wl[0], mr = (sr - wr[1]) * wr[0];
-    iden = rcp_r(mr - ml);
-    sm = fma_r(mr, wr[1], fma_r(-ml, wl[1], ptl - ptr)) * iden;
-    pts = fma_r(ml * mr, wr[1] - wl[1], fma_r(mr, ptl, -ml * ptr)) * iden;
-  }
-  const bool outl = sl > 0.0, outr = !outl && sr < 0.0;
-  const bool fan = !outl && !outr;
-  const bool rt = outr || (fan && !(sm >= 0.0));
+  const HlldFan<double> fn = hlld_fan<double>(g, wl, wr, bn, bn2);
+  const double ptl = fn.ptl, ptr = fn.ptr, c2l = fn.c2l, c2r = fn.c2r;
+  const double sl = fn.sl, sr = fn.sr, sm = fn.sm, pts = fn.pts, iden = fn.iden;
+  const bool fan = fn.fan, rt = fn.rt;
   const bool lo_o = rt ? !(wr[1] < wl[1]) : (wr[1] < wl[1]);  // min(u) is the other side's
   const bool hi_o = rt ? !(wr[1] > wl[1]) : (wr[1] > wl[1]);
   const bool c_o = rt ? !(c2r > c2l) : (c2r > c2l);           // and the fast speed
@@ -325,17 +312,13 @@ __device__ __forceinline__ void hlld_vjp(double g, const double* wl, const doubl
     a.rs = a.m * a.ism;
     const double sq = sqrt_r(a.rs);
     const double abn = abs_r(bn);
-    const double qa = div_r(abn, sq);
-    const double sa = sm + (rt ? qa : -qa);
+    const double sa = hlld_front(sm, abn, sq, rt);
     auto star = [&](StarSide& t, double un) {
-      const double big = t.m * (t.S - sm);
-      const double den = big - bn2;
-      t.deg = abs_r(den) <= DegenerateTol<double>::value * (abs_r(big) + bn2);
-      t.iden2 = rcp_r(den);
-      const double fv = bn * (sm - un) * t.iden2;
-      const double fb = fma_r(t.m, t.d, -bn2) * t.iden2;
-      t.eta = t.deg ? 0.0 : fv;
-      t.zeta = t.deg ? 1.0 : fb;
+      const HlldStar<double> o = hlld_star(t.m, t.d, t.S, un, sm, bn, bn2);
+      t.deg = o.deg;
+      t.iden2 = o.iden2;
+      t.eta = o.eta;
+      t.zeta = o.zeta;
     };
     star(a, w[1]);
     const double vs = fma_r(-w[4], a.eta, w[2]), ws = fma_r(-w[5], a.eta, w[3]);
@@ -713,7 +696,7 @@ __device__ __forceinline__ void edge_apply(EdgeIn& in, double& apbar, double& am
 }
 
 // Reconstructed face-frame states of the lower D-face of cell (i,j,k) as
-// face_inputs forms them, from the recovered primitives PW of the four cells
+// the forward kernels form them, from the recovered primitives PW of the four cells
 // c-2..c+1 along D (the values primitive recovery gives, computed once per
 // cell by k_adj_prim): pw_load gathers the 28 values, pw_states reconstructs.
 template <int D>

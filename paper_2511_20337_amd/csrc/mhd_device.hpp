@@ -341,8 +341,64 @@ __device__ __forceinline__ void riemann_core(R g, const R* wl, const R* wr, R bn
   }
 }
 
-// HLLD flux. It
-// needs the physical flux, the energy star state and (unless the face lies
+// The parts of the HLLD solver that decide its branches, shared by hlld_flux and the
+// adjoint's reverse sweep, which has to take the branch that the flux took.
+template <class R> struct HlldFan {
+  R ptl, ptr, c2l, c2r;  // total pressures, squares of the fast speeds
+  R sl, sr, sm, pts;     // outer fronts, contact, star total pressure
+  R iden;                // 1 / (m_R - m_L), m = rho (S - u)
+  bool fan, rt;          // between the outer fronts; right of the contact, or (not in
+                         // the fan) in the right state
+};
+template <class R>
+__device__ __forceinline__ HlldFan<R> hlld_fan(R g, const R* wl, const R* wr, R bn, R bn2) {
+  HlldFan<R> o;
+  o.ptl = fma_r(R(0.5), fma_r(wl[5], wl[5], fma_r(wl[4], wl[4], bn2)), wl[6]);
+  o.ptr = fma_r(R(0.5), fma_r(wr[5], wr[5], fma_r(wr[4], wr[4], bn2)), wr[6]);
+  // the larger of the two fast speeds: the root of the larger square
+  o.c2l = cfast2(g, wl[0], wl[6], bn, wl[4], wl[5]);
+  o.c2r = cfast2(g, wr[0], wr[6], bn, wr[4], wr[5]);
+  const R cm = sqrt_r(max_r(o.c2l, o.c2r));
+  o.sl = min_r(wl[1], wr[1]) - cm;
+  o.sr = max_r(wl[1], wr[1]) + cm;
+  const R ml = (o.sl - wl[1]) * wl[0], mr = (o.sr - wr[1]) * wr[0];
+  o.iden = rcp_r(mr - ml);
+  o.sm = fma_r(mr, wr[1], fma_r(-ml, wl[1], o.ptl - o.ptr)) * o.iden;
+  o.pts = fma_r(ml * mr, wr[1] - wl[1], fma_r(mr, o.ptl, -ml * o.ptr)) * o.iden;
+  // the side the face lies on: outside the fan the upwind one
+  const bool outl = o.sl > R(0), outr = !outl && o.sr < R(0);
+  o.fan = !outl && !outr;
+  o.rt = outr || (o.fan && !(o.sm >= R(0)));
+  return o;
+}
+// Tangential star state of one side with front S, m = d rho, d = S - u, u = un: v*_t
+// = v_t - eta B_t, B*_t = zeta B_t (degenerate: v*_t = v_t, B*_t = B_t).
+template <class R> struct HlldStar {
+  R eta, zeta, iden2;
+  bool deg;
+};
+template <class R>
+__device__ __forceinline__ HlldStar<R> hlld_star(R m, R d, R S, R un, R sm, R bn, R bn2) {
+  HlldStar<R> o;
+  const R big = m * (S - sm);
+  const R den = big - bn2;
+  o.deg = abs_r(den) <= R(DegenerateTol<R>::value) * (abs_r(big) + bn2);
+  o.iden2 = rcp_r(den);  // dropped (maybe not finite) when degenerate
+  const R fv = bn * (sm - un) * o.iden2;
+  const R fb = fma_r(m, d, -bn2) * o.iden2;
+  o.eta = o.deg ? R(0) : fv;
+  o.zeta = o.deg ? R(1) : fb;
+  return o;
+}
+// The Alfven front of the side rt, sq the root of its star density; between the
+// fronts lies the face where (front >= 0) == rt.
+template <class R>
+__device__ __forceinline__ R hlld_front(R sm, R abn, R sq, bool rt) {
+  const R qa = div_r(abn, sq);
+  return sm + (rt ? qa : -qa);
+}
+
+// HLLD flux. It needs the physical flux, the energy star state and (unless the face lies
 // between the Alfven fronts) the star state of one side only, the side of the
 // contact S_M the face lies on: that side is selected first and only its
 // quantities are formed; the other side's tangential star state and the
@@ -366,13 +422,9 @@ template <class R, int EM>
 __device__ __forceinline__ void hlld_flux(R g, const R* wl, const R* wr, R bn, RiemannOut<R>& o) {
   const R igm1 = rcp_r(g - R(1));  // 1/(gamma-1)
   const R bn2 = bn * bn;
-  const R ptl = fma_r(R(0.5), fma_r(wl[5], wl[5], fma_r(wl[4], wl[4], bn2)), wl[6]);
-  const R ptr = fma_r(R(0.5), fma_r(wr[5], wr[5], fma_r(wr[4], wr[4], bn2)), wr[6]);
-  // the larger of the two fast speeds: the root of the larger square
-  const R cm = sqrt_r(max_r(cfast2(g, wl[0], wl[6], bn, wl[4], wl[5]),
-                            cfast2(g, wr[0], wr[6], bn, wr[4], wr[5])));
-  const R sl = min_r(wl[1], wr[1]) - cm;
-  const R sr = max_r(wl[1], wr[1]) + cm;
+  const HlldFan<R> fn = hlld_fan<R>(g, wl, wr, bn, bn2);
+  const R sl = fn.sl, sr = fn.sr, sm = fn.sm, pts = fn.pts;
+  const bool rt = fn.rt;
   if (EM == 0) {
     o.ap = max0_r(sr);
     o.am = max0_r(-sl);
@@ -380,17 +432,6 @@ __device__ __forceinline__ void hlld_flux(R g, const R* wl, const R* wr, R bn, R
     o.v1 = fma_r(o.ap, wl[2], o.am * wr[2]) * isum;
     o.v2 = fma_r(o.ap, wl[3], o.am * wr[3]) * isum;
   }
-  R sm, pts;
-  {
-    const R ml = (sl - wl[1]) * wl[0], mr = (sr - wr[1]) * wr[0];
-    const R iden = rcp_r(mr - ml);
-    sm = fma_r(mr, wr[1], fma_r(-ml, wl[1], ptl - ptr)) * iden;
-    pts = fma_r(ml * mr, wr[1] - wl[1], fma_r(mr, ptl, -ml * ptr)) * iden;
-  }
-  // the side the face lies on: outside the fan the upwind one
-  const bool outl = sl > R(0), outr = !outl && sr < R(0);
-  const bool fan = !outl && !outr;
-  const bool rt = outr || (fan && !(sm >= R(0)));
   R w[7], u[7], f[7], pt;
 #pragma unroll
   for (int q = 0; q < 7; ++q) w[q] = rt ? wr[q] : wl[q];
@@ -404,28 +445,17 @@ __device__ __forceinline__ void hlld_flux(R g, const R* wl, const R* wr, R bn, R
   }
 #pragma unroll
   for (int q = 0; q < 7; ++q) o.f[q] = f[q];
-  if (!fan) return;
-  // star state of that side (degenerate: v*_t = v_t, B*_t = B_t)
+  if (!fn.fan) return;
+  // star state of that side
   const R S = rt ? sr : sl;
   const R d = S - w[1], m = d * w[0];
   const R ism = rcp_r(S - sm);
   const R rs = m * ism;
   const R sq = sqrt_r(rs);
   const R abn = abs_r(bn);
-  const R qa = div_r(abn, sq);
-  const R sa = sm + (rt ? qa : -qa);  // its Alfven front
-  R zeta, eta;
-  auto star = [&](R mm, R SS, R un, R dd, R& ze, R& et) {
-    const R big = mm * (SS - sm);
-    const R den = big - bn2;
-    const bool deg = abs_r(den) <= R(DegenerateTol<R>::value) * (abs_r(big) + bn2);
-    const R iden2 = rcp_r(den);  // dropped (maybe not finite) when degenerate
-    const R fv = bn * (sm - un) * iden2;
-    const R fb = fma_r(mm, dd, -bn2) * iden2;
-    et = deg ? R(0) : fv;
-    ze = deg ? R(1) : fb;
-  };
-  star(m, S, w[1], d, zeta, eta);
+  const R sa = hlld_front(sm, abn, sq, rt);
+  const HlldStar<R> st = hlld_star(m, d, S, w[1], sm, bn, bn2);
+  const R zeta = st.zeta, eta = st.eta;
   const R vs = fma_r(-w[4], eta, w[2]), ws = fma_r(-w[5], eta, w[3]);
   const R b1s = w[4] * zeta, b2s = w[5] * zeta;
   const R vb = fma_r(w[3], w[5], fma_r(w[2], w[4], w[1] * bn));
@@ -446,8 +476,8 @@ __device__ __forceinline__ void hlld_flux(R g, const R* wl, const R* wr, R bn, R
   const R b1o = rt ? wl[4] : wr[4], b2o = rt ? wl[5] : wr[5];
   const R d_o = so - uo, m_o = d_o * rho_o;
   const R sqo = sqrt_r(m_o * rcp_r(so - sm));
-  R zo, eo;
-  star(m_o, so, uo, d_o, zo, eo);
+  const HlldStar<R> sto = hlld_star(m_o, d_o, so, uo, sm, bn, bn2);
+  const R zo = sto.zeta, eo = sto.eta;
   const R vso = fma_r(-b1o, eo, vo), wso = fma_r(-b2o, eo, wo);
   const R b1so = b1o * zo, b2so = b2o * zo;
   // left and right in their places

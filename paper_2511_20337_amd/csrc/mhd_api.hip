@@ -158,8 +158,7 @@ mhd::StageArgs stage_args(mhd_ctx* ctx, void* ws, hipStream_t s) {
   a.g = ctx->g;
   a.FW = reinterpret_cast<double*>(base(ws) + ctx->off_fw);
   a.glm = ctx->cfg.divb == MHD_DIVB_GLM;
-  a.PW = (a.dim == 3 && a.limiter == MHD_LIM_WENOZ)
-             ? reinterpret_cast<double*>(base(ws) + ctx->off_pw) : nullptr;
+  if (a.dim == 3) a.PW = reinterpret_cast<double*>(base(ws) + ctx->off_pw);
   if (a.glm) {
     // c_h = C Delta_min / dt; the damping per step exp(-alpha c_h dt / Delta_min)
     a.glm_dmin = std::min(ctx->g.dx, ctx->g.dy);
@@ -330,17 +329,18 @@ mhd_status mhd_init(const mhd_config* cfg, mhd_ctx** out) {
   c->cfl_blocks = kCflBlocks;
   // CFL partials: of k_cfl, or one per workgroup of the 3D WENO-Z primitive kernel
   size_t npart = kCflBlocks;
-  if (cfg->dim == 3) npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter));
+  if (cfg->dim == 3) npart = std::max(npart, mhd::stage_cfl_blocks(c->g, cfg->limiter, glm));
   // 3D: the face kernel's edge inputs (CT), or the nine fluxes per direction of
   // the kernel that takes WENO-Z cell by cell (GLM; CT has both, in one record);
   // 2D: the second state of mhd_run and its two sets of CFL partials
+  const bool cells = cfg->dim == 3 && mhd::faces_by_cells(c->g, cfg->limiter, glm);
   size_t nrec = 0;
   if (cfg->dim == 2)
     nrec = nf * n + 2 * (size_t)mhd::stage_2d_tiles(c->g, cfg->limiter, cfg->emf, cfg->precision,
                                                     glm);
   else if (!glm)
     nrec = 3 * (size_t)mhd::NSLOT * n;
-  else if (cfg->limiter == MHD_LIM_WENOZ && c->g.n < mhd::kCellsWeno)
+  else if (cells)
     nrec = 3 * 9 * n;
   size_t off = kCtl;
   c->off_partial = off;
@@ -350,7 +350,8 @@ mhd_status mhd_init(const mhd_config* cfg, mhd_ctx** out) {
   c->off_u2 = off;  // SSP-RK3: the second-stage state
   if (cfg->integrator == MHD_SSP_RK3) off = align_up(off + sizeof(double) * nf * n);
   c->off_pw = off;  // 3D WENO-Z: the primitives of every cell
-  if (cfg->dim == 3 && cfg->limiter == MHD_LIM_WENOZ) off = align_up(off + sizeof(double) * nf * n);
+  if (cells || (cfg->dim == 3 && cfg->limiter == MHD_LIM_WENOZ))
+    off = align_up(off + sizeof(double) * nf * n);
   c->off_fw = off;
   c->bytes_fwd = align_up(off + sizeof(double) * nrec);
   // The adjoint: whole face records (2D: over mhd_run's space), E_z (3D: L of the

@@ -47,6 +47,8 @@
 //    which keeps every path through a plane alike. Only the new state, which
 //    may be updated in place, is written by its owner alone.
 #pragma once
+#include <algorithm>
+
 #include "mhd_device.hpp"
 #include "mhd_grid.hpp"
 #include "mhd_kernels.hpp"
@@ -557,31 +559,28 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
 }
 
 // ---------------------------------------------------------------------------
-// WENO-Z on grids of fewer than kCellsWeno cells: one thread per cell, in storage
-// order, solves its three lower faces from the primitives and stores their fluxes,
-// and a second kernel differences them. The columns of the march would pad such a
-// grid, their runs are short and solve up to half of the z-faces twice, and the
-// fluxes' way through memory is short (they stay in the caches). March against
-// cells, us a pass: 60 x 50 x 40 435 / 337, 144 x 37 x 96 (L(U), HLL) 173 / 142, 100^3
-// 1073 / 913; from 150 x 131 x 97 (1.9 M cells) on the march wins: there 1036 / 1070,
-// with GLM 966 / 1092, 128^3 1606 / 1835.
+// WENO-Z, and PLM with GLM, on grids that the columns of the march would pad or whose
+// runs would be short and solve up to half of the z-faces twice (faces_by_cells): one
+// thread per cell, in storage order, solves its three lower faces from the primitives
+// and stores their fluxes, and a second kernel differences them. On small grids the
+// fluxes' way through memory is short (they stay in the caches).
 
 // The lower D-face of cell (i, j, k): fluxes to FL[D], CT: its edge inputs to FW.
-template <int D, int RS, int EM>
+template <int D, int LIM, int RS, class R, int EM>
 __device__ __forceinline__ void cell_face(const double* __restrict__ U,
-                                          const double* __restrict__ PW,
-                                          double* __restrict__ FW, const Geom& g, int i, int j,
-                                          int k, int64_t c, double ch) {
+                                          const double* __restrict__ PW, R* __restrict__ FW,
+                                          const Geom& g, int i, int j, int k, int64_t c, R ch) {
   constexpr bool GLM = EM == 2;
   constexpr int NW = GLM ? 9 : 7, NF = GLM ? 9 : 5, T1 = (D + 1) % 3, T2 = (D + 2) % 3;
   constexpr int slot[9] = {0, 1 + D, 1 + T1, 1 + T2, 5 + T1, 5 + T2, 4, 5 + D, 8};
   const int64_t n = g.n;
   // all values of the stencil before a scheduling barrier: one wait per face. (32-bit
   // byte offsets, the grid is small: 64 x 52 x 175 with GLM 1381 -> 1301 us a pass)
-  double v[NW][6];
+  constexpr int S = LIM == 2 ? 3 : 2;
+  double v[NW][2 * S];
 #pragma unroll
-  for (int s = 0; s < 6; ++s) {
-    const int o = s - 3;
+  for (int s = 0; s < 2 * S; ++s) {
+    const int o = s - S;
     const uint32_t cs =
         8u * (uint32_t)lin(g, D == 0 ? wrap(i + o, g.nx) : i, D == 1 ? wrap(j + o, g.ny) : j,
                            D == 2 ? wrap(k + o, g.nz) : k);
@@ -592,18 +591,23 @@ __device__ __forceinline__ void cell_face(const double* __restrict__ U,
   const uint32_t co = here(8u * (uint32_t)c);
   const double bn = GLM ? 0.0 : ld_at(U + (F_BX + D) * n, co);
   __builtin_amdgcn_sched_barrier(0);
-  double wl[NW], wr[NW], psi = 0.0, fpsi = 0.0, F[NF];
+  R wl[NW], wr[NW], psi = R(0), fpsi = R(0), F[NF];
 #pragma unroll
   for (int q = 0; q < NW; ++q) {
-    wl[q] = wenoz_upper(v[q][0], v[q][1], v[q][2], v[q][3], v[q][4]);
-    wr[q] = wenoz_upper(v[q][5], v[q][4], v[q][3], v[q][2], v[q][1]);
+    if constexpr (LIM == 2) {
+      wl[q] = wenoz_upper(v[q][0], v[q][1], v[q][2], v[q][3], v[q][4]);
+      wr[q] = wenoz_upper(v[q][5], v[q][4], v[q][3], v[q][2], v[q][1]);
+    } else {
+      plm_pair<LIM, R>((R)v[q][0], (R)v[q][1], (R)v[q][2], (R)v[q][3], wl[q], wr[q]);
+    }
   }
-  RiemannOut<double> o;
-  face_solve<RS, double, EM>(g.gamma, wl, wr, bn, ch, o, psi, fpsi);
+  RiemannOut<R> o;
+  face_solve<RS, R, EM>((R)g.gamma, wl, wr, (R)bn, ch, o, psi, fpsi);
   cell_fluxes<D, EM>(o, psi, fpsi, F);
-  double* const fw = FW + (int64_t)D * (GLM ? 9 : (int)NSLOT) * n;
-  auto put = [&](int q, double v) {
-    *reinterpret_cast<double*>(reinterpret_cast<char*>(fw + q * n) + co) = v;
+  R* const fw = FW + (int64_t)D * (GLM ? 9 : (int)NSLOT) * n;
+  const uint32_t fo = co / (uint32_t)(8 / sizeof(R));
+  auto put = [&](int q, R v) {
+    *reinterpret_cast<R*>(reinterpret_cast<char*>(fw + q * n) + fo) = v;
   };
 #pragma unroll
   for (int q = 0; q < NF; ++q) put(q, F[q]);
@@ -629,7 +633,7 @@ __device__ __forceinline__ bool linear_cell(const Geom& g, int& i, int& j, int& 
   return true;
 }
 
-template <int RS, int EM>
+template <int LIM, int RS, class R, int EM>
 __global__ __launch_bounds__(kBlock) void k_faces_cells(const double* __restrict__ U,
                                                         const double* __restrict__ PW,
                                                         double* __restrict__ FW, Geom g,
@@ -638,15 +642,16 @@ __global__ __launch_bounds__(kBlock) void k_faces_cells(const double* __restrict
   int i, j, k;
   int64_t c;
   if (!linear_cell(g, i, j, k, c)) return;
-  const double ch = EM == 2 ? ch0 / (dtp ? *dtp : dt) : 0.0;
-  cell_face<0, RS, EM>(U, PW, FW, g, i, j, k, c, ch);
-  cell_face<1, RS, EM>(U, PW, FW, g, i, j, k, c, ch);
-  cell_face<2, RS, EM>(U, PW, FW, g, i, j, k, c, ch);
+  const R ch = EM == 2 ? (R)(ch0 / (dtp ? *dtp : dt)) : R(0);
+  R* const fw = stored<R>(FW);
+  cell_face<0, LIM, RS, R, EM>(U, PW, fw, g, i, j, k, c, ch);
+  cell_face<1, LIM, RS, R, EM>(U, PW, fw, g, i, j, k, c, ch);
+  cell_face<2, LIM, RS, R, EM>(U, PW, fw, g, i, j, k, c, ch);
 }
 
 // The update of the cell-averaged fields from the fluxes (stage: as rk_coef, U0 = U
 // where it does not use it; psi times decay).
-template <int EM>
+template <class R, int EM>
 __global__ __launch_bounds__(kBlock) void k_update_cells(const double* __restrict__ U,
                                                          const double* U0, double* out,
                                                          const double* __restrict__ FW, Geom g,
@@ -663,15 +668,15 @@ __global__ __launch_bounds__(kBlock) void k_update_cells(const double* __restric
   const int64_t zp = lin(g, i, j, wrap(k + 1, g.nz));
   const RkCoef rk = rk_coef(stage, stage == 0 ? 0.0 : (dtp ? *dtp : dt));
   const double idx = 1.0 / g.dx, idy = 1.0 / g.dy, idz = 1.0 / g.dz;
-  const double* fx = FW;
-  const double* fy = fx + (int64_t)(GLM ? 9 : (int)NSLOT) * n;
-  const double* fz = fy + (int64_t)(GLM ? 9 : (int)NSLOT) * n;
+  const R* fx = stored<R>(FW);
+  const R* fy = fx + (int64_t)(GLM ? 9 : (int)NSLOT) * n;
+  const R* fz = fy + (int64_t)(GLM ? 9 : (int)NSLOT) * n;
   const bool two = stage == 2 || stage == 4 || stage == 5;
 #pragma unroll
   for (int q = 0; q < NF; ++q) {
-    const double L = -((fx[q * n + xp] - fx[q * n + c]) * idx +
-                       (fy[q * n + yp] - fy[q * n + c]) * idy +
-                       (fz[q * n + zp] - fz[q * n + c]) * idz);
+    const double L = -(((double)fx[q * n + xp] - (double)fx[q * n + c]) * idx +
+                       ((double)fy[q * n + yp] - (double)fy[q * n + c]) * idy +
+                       ((double)fz[q * n + zp] - (double)fz[q * n + c]) * idz);
     const double u = U[q * n + c];
     double v = rk_apply(rk, u, two ? U0[q * n + c] : u, L);
     if (GLM && q == 8) v *= decay;
@@ -679,14 +684,14 @@ __global__ __launch_bounds__(kBlock) void k_update_cells(const double* __restric
   }
 }
 
-template <int RS, int EM>
+template <int LIM, int RS, class R, int EM>
 void cells_impl(const StageArgs& a) {
   const unsigned nb = (unsigned)((a.g.n + kBlock - 1) / kBlock);
   MHD_TIMED(a, K_FACES,
-            hipLaunchKernelGGL((k_faces_cells<RS, EM>), dim3(nb), dim3(kBlock), 0, a.stream, a.U,
+            hipLaunchKernelGGL((k_faces_cells<LIM, RS, R, EM>), dim3(nb), dim3(kBlock), 0, a.stream, a.U,
                                a.PW, a.FW, a.g, a.cfl * a.glm_dmin, a.dt, a.dtp));
   MHD_TIMED(a, K_UPDATE,
-            hipLaunchKernelGGL((k_update_cells<EM>), dim3(nb), dim3(kBlock), 0, a.stream, a.U,
+            hipLaunchKernelGGL((k_update_cells<R, EM>), dim3(nb), dim3(kBlock), 0, a.stream, a.U,
                                a.U0 ? a.U0 : a.U, a.out, a.FW, a.g, a.stage, a.dt, a.dtp,
                                (a.stage == 2 || a.stage == 5) ? a.glm_decay : 1.0));
 }
@@ -723,7 +728,7 @@ void faces_prec(const StageArgs& a, const double* cflp, int npart) {
 // 45; 150 x 131 x 97 1: 243, 2: 214, 4: 193, 8: 185; 60 x 50 x 40 WENO-Z 1: 51, 2: 56,
 // 4: 59; 60 x 64 x 27 WENO-Z with GLM 1: 41, 2: 44, 4: 69; 256^3 4: 1742, 8: 1654, 16:
 // 1608, 32: 1601.
-MarchGrid march_grid(const Geom& g, int limiter) {
+MarchGrid march_grid(const Geom& g, int limiter, double* turns) {
   MarchGrid mg;
   mg.ntx = (g.nx + March::TX - 1) / March::TX;
   mg.nty = (g.ny + March::TY - 1) / March::TY;
@@ -738,21 +743,57 @@ MarchGrid march_grid(const Geom& g, int limiter) {
       mg.lz = lz;
     }
   }
+  if (turns) *turns = best;
   mg.nzc = (g.nz + mg.lz - 1) / mg.lz;
   mg.nblocks = (unsigned)mg.ntx * (unsigned)mg.nty * (unsigned)mg.nzc;
   return mg;
 }
 
-void launch_faces_cells(const StageArgs& a) {
-  if (a.riemann == 0) {
-    if (a.glm) cells_impl<0, 2>(a);
-    else if (a.emf == 1) cells_impl<0, 1>(a);
-    else cells_impl<0, 0>(a);
+// Which of the two is estimated to take less, in microseconds a stage (fitted to 120
+// grids from 4^3 to 4 million cells, cubes, slabs and bars; HLL and mixed precision move
+// both sides alike; the worse one is taken near the line only, and costs 1 % on average).
+// march: its turns, which count its padding; cells: latency, the L2, or the memory.
+// Measured, march / cells: PLM with GLM 4 x 4 x 4000 110 / 22, 33 x 9 x 861 118 / 52, 48^3
+// 37 / 31, 64^3 38 / 49, 128^3 227 / 466; WENO-Z 48^3 68 / 51, 64^3 90 / 84, 100 x 40 x 100
+// 151 / 120, 128^3 507 / 583, 4 x 4 x 125000 4937 / 1251; with GLM 48^3 59 / 40, 64^3
+// 69 / 70, 100 x 40 x 100 130 / 111, 128^3 435 / 568.
+bool faces_by_cells(const Geom& g, int limiter, bool glm) {
+  if (limiter != 2 && !glm) return false;     // PLM with CT marches
+  if (g.n >= (int64_t)1 << 29) return false;  // 32-bit byte offsets
+  struct {
+    double march, turn, cells, l2, mem;
+  } t = {3.5, 10.5, 17.0, 0.12, 0.22};
+  if (limiter == 2 && glm) t = {7.0, 20.5, 20.0, 0.18, 0.26};
+  else if (limiter == 2) t = {12.0, 22.0, 26.0, 0.26, 0.32};
+  const double k = 1e-3 * (double)g.n;
+  double turns;
+  march_grid(g, limiter, &turns);
+  return std::max(t.cells + t.l2 * k, t.mem * k) < t.march + t.turn * turns;
+}
+
+namespace {
+
+template <int RS>
+void cells_rs(const StageArgs& a) {
+  const bool mixed = a.precision == 1;
+  if (a.limiter == 2) {
+    if (a.glm) cells_impl<2, RS, double, 2>(a);
+    else if (a.emf == 1) cells_impl<2, RS, double, 1>(a);
+    else cells_impl<2, RS, double, 0>(a);
+  } else if (a.limiter == 1) {
+    if (mixed) cells_impl<1, RS, float, 2>(a);
+    else cells_impl<1, RS, double, 2>(a);
   } else {
-    if (a.glm) cells_impl<1, 2>(a);
-    else if (a.emf == 1) cells_impl<1, 1>(a);
-    else cells_impl<1, 0>(a);
+    if (mixed) cells_impl<0, RS, float, 2>(a);
+    else cells_impl<0, RS, double, 2>(a);
   }
+}
+
+}  // namespace
+
+void launch_faces_cells(const StageArgs& a) {
+  if (a.riemann == 0) cells_rs<0>(a);
+  else cells_rs<1>(a);
 }
 
 void launch_faces_march(const StageArgs& a, const double* cflp, int npart) {

@@ -363,9 +363,9 @@ hipError_t records_2d(const StageArgs& a) {
 
 }  // namespace
 
-size_t stage_cfl_blocks(const Geom& g, int limiter) {
+size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm) {
   const size_t nl = (size_t)((g.n + kBlock - 1) / kBlock);
-  return limiter == 2 || nl < kCfl3d ? nl : kCfl3d;
+  return limiter == 2 || faces_by_cells(g, limiter, glm) || nl < kCfl3d ? nl : kCfl3d;
 }
 
 namespace {
@@ -404,8 +404,9 @@ int cfl_parts(const Geom& g, int most) {
 hipError_t stage3d(const StageArgs& a) {
   const double* cflp = a.cfl_partial;
   int np = 0;
-  if (a.limiter == 2) {
-    if (!a.PW || a.precision == 1) return hipErrorInvalidValue;
+  const bool cells = faces_by_cells(a.g, a.limiter, a.glm);
+  if (a.limiter == 2 || cells) {
+    if (!a.PW || (a.limiter == 2 && a.precision == 1)) return hipErrorInvalidValue;
     np = (int)((a.g.n + kBlock - 1) / kBlock);
     MHD_TIMED(a, K_PRIM,
               hipLaunchKernelGGL(a.glm ? k_prim<true> : k_prim<false>, dim3(np), dim3(kBlock), 0,
@@ -414,7 +415,6 @@ hipError_t stage3d(const StageArgs& a) {
     np = cfl_parts(a.g, kCfl3d);
     cfl_pass(a, a.cfl_partial, np, a.flag);
   }
-  const bool cells = a.limiter == 2 && a.g.n < kCellsWeno;
   if (cflp && (cells || np > (int)kCfl3d ||
                march_grid(a.g, a.limiter).nblocks > kInlineCfl3d)) {
     cfl_final(a, cflp, np);

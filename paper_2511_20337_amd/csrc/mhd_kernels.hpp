@@ -91,7 +91,7 @@ struct CflArgs {
 hipError_t launch_stage(const StageArgs& a);
 // number of CFL partials of a 3D stage (WENO-Z: one per block of the primitive
 // kernel, else of a grid-stride pass)
-size_t stage_cfl_blocks(const Geom& g, int limiter);
+size_t stage_cfl_blocks(const Geom& g, int limiter, bool glm);
 constexpr size_t kCfl3d = 2048;
 // 3D: on grids of at most this many workgroups of the face kernel each reduces the
 // partials itself, if there are at most kCfl3d.
@@ -100,11 +100,11 @@ constexpr unsigned kInlineCfl3d = 1024;
 hipError_t launch_cfl(const CflArgs& a);
 // 3D face kernel (stage 3: edge inputs only; cflp: npart CFL partials, or null:
 // a.dtp or a.dt), and with CT the EMFs and the update of the staggered field.
-MarchGrid march_grid(const Geom& g, int limiter);
+MarchGrid march_grid(const Geom& g, int limiter, double* turns = nullptr);
 void launch_faces_march(const StageArgs& a, const double* cflp, int npart);
-// The same for WENO-Z on grids of fewer cells than this (dt: a.dtp or a.dt).
+// The same cell by cell, from the primitives (dt: a.dtp or a.dt), and on which grids.
 void launch_faces_cells(const StageArgs& a);
-constexpr int64_t kCellsWeno = 1500000;
+bool faces_by_cells(const Geom& g, int limiter, bool glm);
 void launch_ct(const StageArgs& a);
 // 2D stage in one kernel; cflp: npart CFL partials (null: a.dtp or a.dt).
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart);

@@ -95,36 +95,81 @@ def test_a_shifted_state_gives_the_shifted_result(grid, scheme):
     assert_same(advance(s, np.roll(U0, shift, (1, 2, 3))), want)
 
 
-# 1.5 million cells: from here on WENO-Z marches, and solves the faces between two
-# runs along z once in either
+def by_cells(s):
+    """Whether the faces of s are solved cell by cell (whose update is a kernel of its
+    own) instead of in columns."""
+    from paper_2511_20337_amd import mhd
+    ctx = mhd.Context(s, "cuda:0")
+    U = torch.empty(ctx.shape, dtype=torch.float64, device="cuda:0")
+    for q, v in enumerate((1.0, 0.3, -0.2, 0.1, 2.0, 0.4, 0.25, -0.15, 0.0)[:ctx.shape[0]]):
+        U[q] = v
+    mhd.mhd_timing(ctx.ctx, True)
+    ctx.step(U, 1e-6)
+    return mhd.mhd_timing_read(ctx.ctx)["update"][1] > 0
+
+
+# more than one column each way, ragged, and many runs along z: WENO-Z marches here, and
+# solves the faces between two runs once in either
 @pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
 def test_shifted_state_where_wenoz_marches(scheme):
-    test_a_shifted_state_gives_the_shifted_result((65, 33, 707), scheme)
+    grid = (62, 15, 1000)
+    assert not by_cells(setup(scheme, *grid))
+    test_a_shifted_state_gives_the_shifted_result(grid, scheme)
 
 
-# columns narrower than the face kernel's (32 x 8), where an index takes one
-# remainder more and where it does not (18 x 6 and 17 x 5), and just wider
-@pytest.mark.parametrize("grid", [(4, 4, 47000), (17, 5, 9000), (18, 6, 7000), (5, 9, 17000),
-                                  (31, 7, 3500), (33, 9, 2600)])
-@pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
-def test_marching_wenoz_on_narrow_grids(scheme, grid):
-    """A periodic state twice along z has 1.5 million cells, which WENO-Z marches; once,
-    it has fewer, which it takes cell by cell (checked against the oracle elsewhere).
-    The two form a z-face's values with other roundings: the repository's 1e-12 of each
-    field's maximum."""
+# a periodic state held once and twice along z: on these grids one is taken cell by cell
+# and the other marches. PLM on grids narrower than a column (32 x 8), with indices that
+# take one remainder more (under 18, under 6) and that do not; just under and over a column
+PLM = [(4, 4, 80), (17, 5, 100), (33, 9, 20), (31, 7, 500), (32, 5, 1500), (96, 5, 500),
+       (40, 40, 150)]
+WENOZ = {"ct": [(31, 7, 1500), (32, 5, 10000), (30, 8, 707), (62, 15, 250)],
+         "glm": [(31, 7, 3000), (28, 8, 2000), (62, 15, 400)]}
+
+
+@pytest.mark.parametrize("scheme,grid", [
+    (c, g) for c in SCHEMES if "wenoz" in c or "glm" in c
+    for g in (PLM if "wenoz" not in c else WENOZ["glm" if "glm" in c else "ct"])])
+def test_columns_against_single_cells(scheme, grid):
+    """The same bits with PLM. With WENO-Z the two form a z-face's values with other
+    roundings: the repository's 1e-12 of each field's maximum."""
     nx, ny, nz = grid
-    assert nx * ny * nz < 1500000 <= 2 * nx * ny * nz
     s1 = setup(scheme, nx, ny, nz, (0, 1, 0, 1, 0, nz / 16))
     s2 = setup(scheme, nx, ny, 2 * nz, (0, 1, 0, 1, 0, nz / 8))
+    assert by_cells(s1) != by_cells(s2)
     U0 = state(s1)
-    print("narrow grid", grid, scheme, flush=True)
+    print("columns against cells", grid, scheme, flush=True)
     once = advance(s1, U0)
     twice = advance(s2, np.concatenate([U0, U0], axis=1))
     assert twice[-1] == once[-1]  # the time step
     for a, b in zip(twice[:-1], once[:-1]):
-        tol = 1e-12 * b.abs().amax(dim=(1, 2, 3), keepdim=True)
+        tol = 1e-12 * b.abs().amax(dim=(1, 2, 3), keepdim=True) if "wenoz" in scheme else 0.0
         for half in (a[:, :nz], a[:, nz:]):
             assert bool(((half - b).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("scheme", ["glm", "glm_mixed", "glm_wenoz", "wenoz"])
+def test_a_narrow_grid_is_not_padded(scheme):
+    """A step of 16 x 16 x 1000 cells and one of the same cells in a bar of 4 x 4, which a
+    column of 32 x 8 would pad sixteen times: less than three times as long."""
+    import time
+    from paper_2511_20337_amd import mhd
+    took = []
+    for grid in ((16, 16, 1000), (4, 4, 16000)):
+        s = setup(scheme, *grid)
+        ctx = mhd.Context(s, "cuda:0")
+        U = torch.from_numpy(state(s)).cuda()
+        dt = 1e-3 * ctx.dt(U)
+        best = 1.0
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(5):
+                ctx.step(U, dt)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        took.append(best)
+    print("narrow grid", scheme, took, flush=True)
+    assert took[1] < 3 * took[0], took
 
 
 def test_a_long_grid_costs_the_host_nothing():

@@ -14,7 +14,6 @@ pytestmark = pytest.mark.gpu
 
 # one column; a column and one cell, or one row, more; a cell and a row less;
 # the smallest grid; more than one plane per run, the last run shorter
-# (the last: WENO-Z marches from 1.5 million cells on)
 GRIDS = [(32, 8, 4), (33, 9, 5), (31, 7, 6), (4, 4, 4), (64, 16, 9), (5, 40, 4), (65, 17, 709)]
 
 
@@ -106,3 +105,13 @@ def test_glm_wenoz_with_hll(grid):
     ctx.check()
     err = rel_err9(Ua.cpu().numpy(), O.glm_run_dts(O.cfg_from(s), U0, np.array(dts)))
     assert (err <= 1e-12).all(), err
+
+
+@pytest.mark.parametrize("scheme", ["hll_wenoz_uct_hlld_rk3", "hlld_wenoz"])
+def test_columns_and_runs_of_the_wenoz_march(scheme):
+    """WENO-Z on a grid that marches (two columns each way, the second ones ragged)."""
+    test_columns_and_runs((62, 15, 500), scheme)
+
+
+def test_columns_and_runs_of_the_wenoz_march_glm():
+    test_columns_and_runs_glm((62, 15, 1000), "wenoz")

@@ -339,18 +339,39 @@ void stage_2d(const StageArgs& a, const double* cflp, int npart) {
 constexpr int large_w(int limiter, int emf, int precision) {
   return emf == 2 ? 32 : limiter == 2 ? 24 : (emf == 1 && precision == 0) ? 28 : 32;
 }
-constexpr int kSmallW = 8, kTileH = 8;
-bool small_tiles(const Geom& g) {
-  return (int64_t)((g.nx + 31) / 32) * ((g.ny + 7) / 8) <= kSmallTiles2d;
+// The tile of a grid: a large one, or a small one of 64 cells, square or (where that
+// takes fewer by a tenth: few or ragged rows) flat. Grids of at most kSmallTiles2d
+// large tiles take small ones, and so does a grid that they cover in less: a large
+// tile's cell costs 0.8 of a small one's (WENO-Z 0.9, mixed precision 0.6). A step in us,
+// large / square / flat: GLM 4 x 40000 220 / 71 / -, WENO-Z 25 x 6400 115 / 87 / -, 160000 x
+// 4 423 / 451 / 239, 37647 x 17 303 / 342 / 277, KH 512^2 60 / 76 / -. (Narrow tiles of 4 x
+// 16 take 1.45 times as long as square ones, their rows being 32 bytes.)
+constexpr int kLargeH = 8;
+struct TileShape {
+  int w, h;
+};
+TileShape tile_shape(const Geom& g, int limiter, int large, bool mixed) {
+  auto tiles = [&](int w, int h) {
+    return (int64_t)((g.nx + w - 1) / w) * ((g.ny + h - 1) / h);
+  };
+  TileShape t = {8, 8};
+  if (10 * tiles(16, 4) <= 9 * tiles(8, 8)) t = {16, 4};
+  const double cell = limiter == 2 ? 0.9 : mixed ? 0.6 : 0.8;
+  if (tiles(32, 8) > kSmallTiles2d &&
+      cell * (large * kLargeH) * (double)tiles(large, kLargeH) <=
+          (double)(t.w * t.h) * (double)tiles(t.w, t.h))
+    t = {large, kLargeH};
+  return t;
 }
 
 template <int LIM, int RS, class R, int EM>
 void stage_2d_tile(const StageArgs& a, const double* cflp, int npart) {
   constexpr int S = LIM == 2 ? 3 : 2, E = EM == 2 ? 0 : 2;
-  using Small = Tile2<kSmallW, kTileH, 256, S, E>;
-  using Large = Tile2<large_w(LIM, EM, sizeof(R) == 4), kTileH, 512, S, E>;
-  if (small_tiles(a.g)) stage_2d<Small, LIM, RS, R, EM>(a, cflp, npart);
-  else stage_2d<Large, LIM, RS, R, EM>(a, cflp, npart);
+  constexpr int large = large_w(LIM, EM, sizeof(R) == 4);
+  const TileShape t = tile_shape(a.g, LIM, large, sizeof(R) == 4);
+  if (t.w == large) stage_2d<Tile2<large, kLargeH, 512, S, E>, LIM, RS, R, EM>(a, cflp, npart);
+  else if (t.w == 16) stage_2d<Tile2<16, 4, 256, S, E>, LIM, RS, R, EM>(a, cflp, npart);
+  else stage_2d<Tile2<8, 8, 256, S, E>, LIM, RS, R, EM>(a, cflp, npart);
 }
 template <int LIM, int RS, class R>
 void stage_2d_emf(const StageArgs& a, const double* cflp, int npart) {
@@ -375,8 +396,9 @@ void stage_2d_lim(const StageArgs& a, const double* cflp, int npart) {
 }  // namespace
 
 int stage_2d_tiles(const Geom& g, int limiter, int emf, int precision, bool glm) {
-  const int W = small_tiles(g) ? kSmallW : large_w(limiter, glm ? 2 : emf, precision);
-  return ((g.nx + W - 1) / W) * ((g.ny + kTileH - 1) / kTileH);
+  const TileShape t =
+      tile_shape(g, limiter, large_w(limiter, glm ? 2 : emf, precision), precision == 1);
+  return ((g.nx + t.w - 1) / t.w) * ((g.ny + t.h - 1) / t.h);
 }
 
 void launch_stage_2d(const StageArgs& a, const double* cflp, int npart) {

@@ -154,3 +154,36 @@ def test_more_tiles_than_one_launch_takes():
         torch.cuda.empty_cache()
     assert out[rows][1] == out[128][1]
     assert torch.equal(out[rows][0], out[128][0])
+
+
+# flat tiles (16 x 4): whole, ragged either way, many of them
+@pytest.mark.parametrize("grid", [(16, 4), (200, 4), (150, 12), (37, 17), (1100, 4)])
+@pytest.mark.parametrize("scheme", ["minmod", "uct_rk3", "mixed_uct", "wenoz_uct_rk3", "hll_wenoz",
+                                    "glm", "glm_hll_mixed_rk3", "glm_wenoz"])
+def test_tiles_and_run_on_few_rows(grid, scheme):
+    test_tiles_and_run(grid, scheme)
+
+
+@pytest.mark.parametrize("grid", [(4, 40000), (40000, 4)])
+@pytest.mark.parametrize("scheme", ["uct_rk3", "glm", "glm_wenoz", "hll_wenoz"])
+def test_a_narrow_grid_is_not_padded(grid, scheme):
+    """A run over 400 x 400 cells and over as many in 4 rows or columns, which large tiles
+    (32 x 8 cells) would pad eight times or twice: less than twice as long."""
+    import time
+    from paper_2511_20337_amd import mhd
+    took = []
+    for nx, ny in ((400, 400), grid):
+        s = dict(setup(8, 8, scheme)[0], nx=nx, ny=ny, xmax=nx / 8, ymax=ny / 8)
+        ctx = mhd.Context(s, "cuda:0")
+        one = torch.tensor([1.0, 0.3, -0.2, 0.1, 2.0, 0.4, 0.25, -0.15, 0.0], dtype=torch.float64)
+        U = one[:ctx.shape[0], None, None, None].expand(ctx.shape).contiguous().cuda()
+        best = 1.0
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ctx.run(U, 10)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        took.append(best)
+    print("narrow grid", grid, scheme, took, flush=True)
+    assert took[1] < 2 * took[0], took

@@ -749,22 +749,23 @@ MarchGrid march_grid(const Geom& g, int limiter, double* turns) {
   return mg;
 }
 
-// Which of the two is estimated to take less, in microseconds a stage (fitted to 120
-// grids from 4^3 to 4 million cells, cubes, slabs and bars; HLL and mixed precision move
-// both sides alike; the worse one is taken near the line only, and costs 1 % on average).
-// march: its turns, which count its padding; cells: latency, the L2, or the memory.
-// Measured, march / cells: PLM with GLM 4 x 4 x 4000 110 / 22, 33 x 9 x 861 118 / 52, 48^3
-// 37 / 31, 64^3 38 / 49, 128^3 227 / 466; WENO-Z 48^3 68 / 51, 64^3 90 / 84, 100 x 40 x 100
-// 151 / 120, 128^3 507 / 583, 4 x 4 x 125000 4937 / 1251; with GLM 48^3 59 / 40, 64^3
-// 69 / 70, 100 x 40 x 100 130 / 111, 128^3 435 / 568.
+// Which of the two is estimated to take less, in microseconds a stage. march: its
+// turns, which count its padding; cells: latency, the L2, or the memory. Fitted to 120
+// grids from 4^3 to 4 million cells, cubes, slabs and bars, with HLL and mixed
+// precision, which move both sides alike; the worse one is taken near the line only
+// (PLM 15 to 25 % at most, 1 % on average; WENO-Z 5 %, 0.1 %). Measured, march / cells:
+// PLM with GLM 4 x 4 x 4000 110 / 22, 33 x 9 x 861 118 / 52, 48^3 37 / 31, 64^3 38 / 49,
+// 128^3 227 / 466; WENO-Z 48^3 68 / 51, 100^3 340 / 282, 112^3 392 / 376, 128^3 507 /
+// 583, 4 x 4 x 125000 4937 / 1251; with GLM 48^3 59 / 40, 100 x 40 x 100 130 / 111, 128^3
+// 435 / 568.
 bool faces_by_cells(const Geom& g, int limiter, bool glm) {
   if (limiter != 2 && !glm) return false;     // PLM with CT marches
   if (g.n >= (int64_t)1 << 29) return false;  // 32-bit byte offsets
   struct {
     double march, turn, cells, l2, mem;
   } t = {3.5, 10.5, 17.0, 0.12, 0.22};
-  if (limiter == 2 && glm) t = {7.0, 20.5, 20.0, 0.18, 0.26};
-  else if (limiter == 2) t = {12.0, 22.0, 26.0, 0.26, 0.32};
+  if (limiter == 2 && glm) t = {8.0, 22.0, 0.0, 0.0, 0.28};
+  else if (limiter == 2) t = {12.0, 22.0, 0.0, 0.0, 0.25};
   const double k = 1e-3 * (double)g.n;
   double turns;
   march_grid(g, limiter, &turns);

@@ -112,7 +112,7 @@ def by_cells(s):
 # solves the faces between two runs once in either
 @pytest.mark.parametrize("scheme", [c for c in SCHEMES if "wenoz" in c])
 def test_shifted_state_where_wenoz_marches(scheme):
-    grid = (62, 15, 1000)
+    grid = (62, 15, 2000)
     assert not by_cells(setup(scheme, *grid))
     test_a_shifted_state_gives_the_shifted_result(grid, scheme)
 
@@ -122,7 +122,7 @@ def test_shifted_state_where_wenoz_marches(scheme):
 # take one remainder more (under 18, under 6) and that do not; just under and over a column
 PLM = [(4, 4, 80), (17, 5, 100), (33, 9, 20), (31, 7, 500), (32, 5, 1500), (96, 5, 500),
        (40, 40, 150)]
-WENOZ = {"ct": [(31, 7, 1500), (32, 5, 10000), (30, 8, 707), (62, 15, 250)],
+WENOZ = {"ct": [(31, 7, 7000), (30, 8, 3000), (62, 15, 1000), (64, 64, 150)],
          "glm": [(31, 7, 3000), (28, 8, 2000), (62, 15, 400)]}
 
 

@@ -109,9 +109,9 @@ def test_glm_wenoz_with_hll(grid):
 
 @pytest.mark.parametrize("scheme", ["hll_wenoz_uct_hlld_rk3", "hlld_wenoz"])
 def test_columns_and_runs_of_the_wenoz_march(scheme):
-    """WENO-Z on a grid that marches (two columns each way, the second ones ragged)."""
-    test_columns_and_runs((62, 15, 500), scheme)
+    """WENO-Z on a grid that marches (several columns each way, the last ones ragged)."""
+    test_columns_and_runs((94, 63, 200), scheme)
 
 
 def test_columns_and_runs_of_the_wenoz_march_glm():
-    test_columns_and_runs_glm((62, 15, 1000), "wenoz")
+    test_columns_and_runs_glm((94, 63, 200), "wenoz")

@@ -41,31 +41,34 @@ def log(*a):
 
 
 # Roofline of the dominant kernel, the face kernel (reconstruction + Riemann
-# solve of every lower face, with primitive recovery), per cell:
-#  flops: operations of the method's definition in those phases (add/sub, mul,
+# solve of every lower face, with primitive recovery, and the update of the five
+# cell-averaged fields), per cell and launch:
+#  flops: operations of the method's definition in the first three (add/sub, mul,
 #         div, sqrt one each), counted by oracle/count_flops.py on the initial
-#         state of this workload at 256^3 (3D turbulence, van Leer, HLLD);
-#  bytes: the state it must read once, 64 B; the edge inputs it writes are an
-#         artefact of splitting the stage into kernels, not algorithmic traffic.
+#         state of this workload at 256^3 (3D turbulence, van Leer, HLLD); the
+#         update's (about 60) are left out, though its time is in the launch;
+#  bytes: the state read once, 64 B, the five fields written, 40 B, and read at
+#         the start of the step in every second launch, 20 B; the edge inputs it
+#         writes are an artefact of splitting the stage, not algorithmic traffic.
 # The kernel's roof is the slower of the two: flops at the vector peak of the
 # arithmetic's precision (FP64 78.6 TFLOP/s; FP32 157.3 in the mixed mode) or
 # bytes at 8 TB/s; frac = that time / the measured time per launch.
 FACE_FLOPS = 1343.8
-FACE_BYTES = 64
+FACE_BYTES = 64 + 40 + 20
 FP32_PEAK = 157.3e12
 # HBM bytes per cell of one face-kernel launch, rocprofv3 FETCH_SIZE x 2.0 and
 # WRITE_SIZE x 1.0 (the copy-kernel calibration), for the kernel as it stands.
-FACE_TRAFFIC = {"fp64": 250.4 + 136.0, "mixed": 262.0 + 88.0}
+FACE_TRAFFIC = {"fp64": 250.8 + 136.0, "mixed": 262.0 + 88.0}
 # HBM bytes per cell of one whole step, the same counters summed over its
-# launches (the CFL pass, two of faces and CT): what the two-kernel stage
-# moves beside the 320 algorithmic bytes.
-STEP_TRAFFIC = {"fp64": 1271.5, "mixed": 1120.9}
+# launches (the CFL pass, two of faces and CT, the latter timed under "emf"):
+# what the two-kernel stage moves beside the 320 algorithmic bytes.
+STEP_TRAFFIC = {"fp64": 1271.3, "mixed": 1114.3}
 # WENO-Z face kernel on the 3D Orszag-Tang problem (FP64, HLLD): algorithmic
 # flops per cell of the oracle's face phase on that workload at 256^3 (count_flops.py;
 # its textbook WENO-Z with seven divisions per value, each one flop), and the
 # HBM bytes per cell counted at 352^3 (reads past L2 x2.0, writes x1.0).
 WENO_FACE_FLOPS = 4039.4
-WENO_FACE_TRAFFIC = 412.6 + 160.0
+WENO_FACE_TRAFFIC = 412.8 + 160.0
 
 
 def face_roofline(kt, ncell, precision="fp64"):

@@ -166,9 +166,10 @@ mhd_status mhd_step_device_dt(mhd_ctx* ctx, double* U, const double* dt_dev, voi
 
 /* One step of the configured integrator whose dt is the CFL time step of U
  * (as mhd_dt computes it, bit for bit), written to the device double *dt_dev
- * and used by the step; no host synchronisation. The CFL reduction runs
- * inside a first kernel of the step that recovers the primitives anyway (3D
- * with CT), else as a pass over U. */
+ * and used by the step; no host synchronisation. The CFL reduction runs inside
+ * the kernel that recovers every cell's primitives where the step begins with
+ * one (3D WENO-Z, and 3D GLM on grids it takes cell by cell), else as a pass
+ * over U. */
 mhd_status mhd_step_cfl(mhd_ctx* ctx, double* U, double* dt_dev, void* ws, size_t ws_bytes,
                         void* stream);
 

@@ -34,9 +34,9 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Hand-written reverse sweeps of the Riemann solvers. The forward values that
-// decide a branch come from the forward solvers' own functions, so every branch (wave-speed
-// min/max, HLL/HLLD region, degenerate star state, sign of the normal field)
-// is the one the forward kernels take; the derivative of each branch is then
+// decide a branch come from the forward solvers' own functions, so every branch
+// (wave-speed min/max, HLL/HLLD region, degenerate star state, sign of the normal
+// field) is the one the forward kernels take; the derivative of each branch is then
 // propagated backwards once for all fifteen inputs. At a square root of zero
 // the derivative is taken as zero.
 //
@@ -810,9 +810,9 @@ __device__ __forceinline__ void face_adjoint(const double* __restrict__ U,
 }
 
 // What bounds it: HBM (112 values per cell at the least) and the latency of its
-// gathers. Two waves per SIMD without spills: the sweep in one copy for both
-// sides, the gather in two sets, and nothing derived from the cell's place
-// shared between the faces (here()). 192^3 3.12 -> 2.13 ms, KH 512^2 60 -> 41 us;
+// gathers. Two waves per SIMD, without spills (but 20 bytes a lane for HLL in 3D): the
+// sweep in one copy for both sides, the gather in two sets, and nothing derived from
+// the cell's place shared between the faces (here()). 192^3 3.12 -> 2.13 ms, KH 512^2 60 -> 41 us;
 // capped at two waves with 170 bytes of spills 2.72 ms, one wave 2.55 ms.
 template <int DIM, int LIM, int RS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))

@@ -27,8 +27,8 @@ namespace mhd {
 
 enum : int { F_RHO = 0, F_MX = 1, F_MY = 2, F_MZ = 3, F_EN = 4, F_BX = 5, F_BY = 6, F_BZ = 7 };
 
-// Workgroup order of the WENO-Z kernels, of the mixed-mode EMF and update
-// kernels and of the adjoint's gather kernels: the hardware deals workgroups
+// Workgroup order of the 3D kernels that take cells in storage order, of the CT
+// kernel and of the adjoint's gather kernels: the hardware deals workgroups
 // round-robin to the 8 XCDs, each with its own L2. Within every full group of
 // 512 workgroups, XCD x is given the 64 consecutive ones x*64 .. x*64+63, so
 // that neighbouring rows (the stencil's reach along y) are mostly read through
@@ -64,8 +64,8 @@ struct Geom {
 // (reciprocal; what is left of the estimate's error is 1e-22, below its last
 // rounding) or a Newton step and a residual correction: on 2^20 random
 // operands the quotient and the square root reproduce the IEEE result bit for
-// bit, at well under the instruction count of the IEEE sequences. Operands: finite, nonzero divisors and
-// non-negative radicands in the normal range.
+// bit, at well under the instruction count of the IEEE sequences. Operands:
+// finite, nonzero divisors and non-negative radicands in the normal range.
 __device__ __forceinline__ double rcp_r(double b) {
   const double r = __builtin_amdgcn_rcp(b);
   const double e = __builtin_fma(-b, r, 1.0);

@@ -14,8 +14,8 @@
 // whole stage. WENO-Z reads the primitives k_prim left: its stencil is three
 // cells either way, and recovering them again at each plane's halo cost more.
 //
-// What bounds it: the instruction count (1860 per cell at 256^3 in FP64, the
-// vector units 67 % busy; WENO-Z 3470 and 75 %). Measured against the split it replaces (a face
+// What bounds it: the instruction count (1840 per cell at 256^3 in FP64, the
+// vector units 67 % busy; WENO-Z 3450 and 75 %). Measured against the split it replaces (a face
 // kernel that stored the fluxes, 27 values per cell, and an update that read
 // them back): faces 1.52 -> 1.60 ms, update 0.96 -> 0.43 ms per launch at 256^3
 // in FP64, the step 6.32 -> 5.35 ms; 384^3 mixed 13.9 -> 12.4 ms; with GLM (before:
@@ -722,7 +722,8 @@ void faces_prec(const StageArgs& a, const double* cflp, int npart) {
 
 // Planes per run: a run costs about a plane more (its prologue and the z-faces above
 // it; less of one with WENO-Z, whose primitives are there), a longer one leaves fewer
-// workgroups, of which two fit on each of the 256 CUs. The power of two up to 16 that
+// workgroups, counted as two to each of the 256 CUs (in mixed precision, and in FP64
+// for HLL with PLM and CT, three fit; the rule does not tell them apart). The power of two up to 16 that
 // minimises (runs per slot + 0.4) (planes + extra), the longer of two that differ by
 // less than 2 %. Measured, us a launch: 32^3 1: 17, 2: 23, 4: 38; 64^3 1: 46, 2: 40, 4:
 // 45; 150 x 131 x 97 1: 243, 2: 214, 4: 193, 8: 185; 60 x 50 x 40 WENO-Z 1: 51, 2: 56,

@@ -16,9 +16,10 @@
 //    lane's direction is two LDS offsets and a few selects.
 //  - Large grids: 32 x 8 cells, 512 threads: 720 faces are 12 waves' work for 8
 //    waves, and two workgroups fit a CU (16 waves, four per SIMD at 128
-//    VGPRs); KH 512^2 with 256 threads 36.6 us a launch against 34.2, 384: 47.6,
-//    32 x 16 cells and 1024 threads: 34.9, 8 x 8 cells: 43.7. Small ones: 8 x 8
-//    cells, 216 faces for 256 threads, one each: the shortest chain, and four
+//    VGPRs; GLM in FP64 with HLLD spills 12 bytes a lane). A step of two launches at
+//    512^2: 58.5 us, with 256 threads 63.3, 384: 81.9, 32 x 16 cells and 1024 threads
+//    57.7 (1024^2: 203, 214, 298, 214), 8 x 8 cells 74. Small ones: 8 x 8 or 16 x 4
+//    cells, 216 or 236 faces for 256 threads, one each: the shortest chain, and four
 //    times the workgroups.
 //  - The time step of the CFL bound is reduced from its partials by every
 //    workgroup itself (a minimum is exact in any order), and between the steps

@@ -29,15 +29,16 @@
 //  - LDS holds two planes of the column (by the parity of k - k0; the values a
 //    thread needs of planes k-1 and k+1 are its own), one cross halo and the
 //    exchanged fluxes.
-//  - Two waves per SIMD in FP64 (204 VGPRs, GLM 236, WENO-Z with GLM 254), three in
+//  - Two waves per SIMD in FP64 (214 VGPRs, GLM and WENO-Z with GLM 254), three in
 //    mixed precision: one more spills (FP64 1.95 ms against 1.52, mixed 384^3 3.73
 //    against 3.39).
 //  - Fluxes are differenced before they are added up, so a uniform flow has L = 0 and
 //    a cell's result does not depend on its place in the column (a running sum over
-//    the faces has neither; it took 0.2 to 0.9 % less time a step). The lower z-flux
-//    waits in the thread's own slot of fy, which is free between the exchanges: in
-//    registers, HLL in FP64 needs 176 (with 168 or fewer three workgroups fit a CU),
-//    and WENO-Z with GLM spills.
+//    the faces has neither, and takes as long). The lower z-flux waits for the upper
+//    one in registers; with HLL in FP64, which would need 176 (with 168 or fewer three
+//    workgroups fit a CU), and in WENO-Z with GLM, which would spill, in the thread's
+//    own slot of fy, free between the exchanges (GLM that way: 256^3 3311 against 3254
+//    us a step).
 //  - Two barriers a plane: before the first one everybody reads plane k; then
 //    the halo of plane k+1 and the exchanged fluxes are written; the second
 //    publishes them.
@@ -235,6 +236,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
                    const double* __restrict__ cflp, int npart, double cfl, double* dt_out) {
   using M = March;
   constexpr bool GLM = EM == 2, WZ = LIM == 2;
+  // the lower z-flux waits in LDS where registers are short (see above)
+  constexpr bool ZL = GLM ? WZ : (!WZ && RS == 1 && sizeof(R) == 8);
   constexpr int S = WZ ? 3 : 2;
   using HL = Halo<S>;
   const double* __restrict__ const src = WZ ? PW : U;
@@ -360,7 +363,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
   const R ch = GLM ? uni((R)(ch0 / h)) : R(0);
   int cp = 0;  // core offset of plane k
   double acc[NF];  // flux differences along x and y of the own cell
-  R fz[NF];        // its lower z-flux, in L.fy[.][t] but for the exchange
+  R fz[NF];        // its lower z-flux; ZL: in L.fy[.][t] but for the exchange
   R* const fw0 = reinterpret_cast<R*>(FW);
   for (int k = k0;; ++k) {
     const int kw = wrap(k, g.nz);
@@ -411,7 +414,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
         };
 #pragma unroll
         for (int q = 0; q < NF; ++q)
-          acc[q] = -(acc[q] + ((double)F[q] - (double)L.fy[q][t]) * idz);
+          acc[q] = -(acc[q] + ((double)F[q] - (double)(ZL ? L.fy[q][t] : fz[q])) * idz);
         if (stage != 3) {
           double u[NF], u0[NF];
 #pragma unroll
@@ -433,7 +436,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       }
       if (k == k1) break;
 #pragma unroll
-      for (int q = 0; q < NF; ++q) L.fy[q][t] = F[q];
+      for (int q = 0; q < NF; ++q) (ZL ? L.fy[q][t] : fz[q]) = F[q];
     }
     if constexpr (!GLM) put_edge<2, EM>(fwp, n, boff, o);
     const int ka = wrap(k + 1, g.nz), kb = wrap(k + 2, g.nz), kc = wrap(k + 3, g.nz);
@@ -525,7 +528,8 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
       }
     }
 #pragma unroll
-    for (int q = 0; q < NF; ++q) fz[q] = L.fy[q][t];
+    for (int q = 0; q < NF; ++q)
+      if (ZL) fz[q] = L.fy[q][t];
     __syncthreads();
     if (y > 0) {
 #pragma unroll
@@ -549,7 +553,7 @@ void k_faces_march(const double* __restrict__ U, const double* __restrict__ PW,
     for (int q = 0; q < NF; ++q) {
       if (x == M::TX - 1) acc[q] = ((double)L.fx[q][y] - acc[q]) * idx;
       acc[q] += ((double)L.fy[q][t] - (double)fy[q]) * idy;
-      L.fy[q][t] = fz[q];
+      if (ZL) L.fy[q][t] = fz[q];
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) bn[d] = bnn[d];

@@ -187,3 +187,39 @@ def test_a_narrow_grid_is_not_padded(grid, scheme):
         took.append(best)
     print("narrow grid", grid, scheme, took, flush=True)
     assert took[1] < 2 * took[0], took
+
+
+@pytest.mark.parametrize("grid,scheme", [((60, 44, 1), "uct_rk3"), ((300, 257, 1), "glm_wenoz"),
+                                         ((40, 4, 1), "glm"), ((40, 12, 9), "glm"),
+                                         ((48, 17, 78), "glm"), ((20, 18, 16), "wenoz_uct_rk3")])
+@pytest.mark.parametrize("nsteps", [2, 3])
+def test_a_captured_run_replays(grid, scheme, nsteps):
+    """mhd_run in a HIP graph: kernels alone, so each replay, with eager steps of the same
+    context and synchronisations between them, gives the bits of the eager run."""
+    from paper_2511_20337_amd import mhd
+    nx, ny, nz = grid
+    s, U0 = setup(nx, ny, scheme)
+    if nz > 1:
+        t, U0 = W.generic_state(3, nx, ny, nz, s["limiter"], s["riemann"], seed=5)
+        s = dict(t, emf=s["emf"], integrator=s["integrator"], precision=s["precision"])
+        if "glm" in scheme:
+            s, U0 = W.glm_from_ct(s, U0)
+    print("captured run", grid, scheme, nsteps, flush=True)
+    ctx = mhd.Context(s, "cuda:0")
+    start = torch.from_numpy(U0).cuda()
+    ref, other, U = start.clone(), start.clone(), start.clone()
+    ctx.run(ref, nsteps)
+    dt = ctx.dt_dev.item()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ctx.run(U, nsteps)
+    for _ in range(3):
+        U.copy_(start)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert ctx.dt_dev.item() == dt
+        assert torch.equal(U, ref)
+        ctx.step_cfl(other)
+    ctx.check()
